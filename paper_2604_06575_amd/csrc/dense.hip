@@ -217,11 +217,11 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
 // Reverse mode of Y = C V for a cotangent gY [P x N]:
 //   dC = gY V^T            [P x K]: MFMA over points, V^T built per step
 //   dX[pt][j] = sum_k W[k][pt] d v_k / d x_j (x_pt),   W = C^T gY [K x N]
-// dX never stores W: a workgroup owns a tile of points, forms W for one
-// tile of monomials at a time on MFMA (contraction over the polynomials),
-// and contracts it at once with the monomials' first derivatives.
+// W is formed on MFMA (contraction over the polynomials) for one chunk of
+// points at a time and stored; k_dx_from_w then contracts the chunk with the
+// monomials' first derivatives.
 
-constexpr int DB_BM = 64, DB_BN = 128, DB_KS = 16, DB_THREADS = 256;
+constexpr int DB_BN = 128, DB_KS = 16, DB_THREADS = 256;
 
 // dC tile: rows p (64), columns k (128), contraction over points in steps
 // of 16.  Each thread owns one monomial column (its factor list held in
@@ -345,124 +345,91 @@ __device__ inline void add_monomial_grad(const uint64_t w0, const uint64_t w1, c
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-// dX for one tile of 128 points.  Per monomial tile (64): W tile on MFMA
-// (A = C^T rows k, B = gY rows p, contraction over P in steps of 16), then
-// each lane's W entries times the derivatives of their monomials at their
-// points, added into its wave's accumulator block [n][64 points] (LDS adds:
-// one wave's adds apply in program and lane order, so the sums do not
-// depend on scheduling).  The two waves covering the same points are added
-// in a fixed order at the end.  Dynamic LDS: points [(n + 1)][128] and four
-// accumulator blocks [n][64].
-__global__ void __launch_bounds__(DB_THREADS) k_dense_bwd_dx(int n, int64_t K, const uint8_t *basis,
-                                                            const uint64_t *senc, int64_t P, const double *C,
-                                                            const double *gY, int64_t N, const double *X, double *dX)
+// W = C^T gY for one chunk of points, W[k * ldw + c], c < Nc: a plain FP64
+// product on v_mfma_f64_16x16x4f64 with both operands read along their rows
+// (C^T along k, gY along the points).  128 x 128 tile, each wave 64 x 64; the
+// operand tiles of 16 polynomials are double-buffered in LDS (one barrier per
+// step) and the next ones are in flight, in registers, while a step's 64 MFMAs
+// per wave run.  Bound by the FP64 MFMA pipe.  Storing W and contracting it in
+// k_dx_from_w replaced a kernel that contracted each 64 x 128 tile with the
+// monomials' derivatives in place: that one held a workgroup's whole K range
+// (N / 128 workgroups in all) and left the MFMA pipe idle during the
+// contraction.  The K monomials are columns of C, ldc apart per row.  grid:
+// point tiles (fastest) x monomial tiles.
+constexpr int WG_T = 128, WG_KS = 16, WG_THREADS = 256;
+
+__global__ void __launch_bounds__(WG_THREADS) k_dense_w(int64_t K, int64_t ldc, int64_t P, const double *C, int64_t N,
+                                                        int64_t c0, int64_t Nc, const double *gY, double *W,
+                                                        int64_t ldw)
 {
-    extern __shared__ double s_dyn[];
-    double *s_x = s_dyn;                                    // [n + 1][DB_BN]
-    double *s_acc = s_dyn + (size_t)(n + 1) * DB_BN;        // [4][n][64]
-    __shared__ double s_a[DB_BM][DB_KS + 1];                // C^T tile: [k][p]
-    __shared__ double s_b[DB_KS][DB_BN + 2];                // gY tile: [p][pt]
-    __shared__ uint64_t s_enc[DB_BM][2];
+    __shared__ double s_a[2][WG_KS][WG_T + 2];   // C tile: [p][k]
+    __shared__ double s_b[2][WG_KS][WG_T + 2];   // gY tile: [p][pt]
+    constexpr int LPT = WG_KS * WG_T / WG_THREADS;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int wr = w >> 1, wc = w & 1;
-    const int64_t n0 = (int64_t)blockIdx.x * DB_BN;
-    for (int idx = tid; idx < (n + 1) * DB_BN; idx += DB_THREADS) {
-        const int i = idx / DB_BN, c = idx % DB_BN;
-        const int64_t pt = n0 + c;
-        s_x[idx] = i == n ? 1.0 : (pt < N ? X[pt * n + i] : 0.0);
-    }
-    for (int idx = tid; idx < 4 * n * kWave; idx += DB_THREADS) s_acc[idx] = 0.0;
-    double *my_acc = s_acc + (size_t)w * n * kWave;
-    for (int64_t k0 = 0; k0 < K; k0 += DB_BM) {
+    const int64_t ntiles = (Nc + WG_T - 1) / WG_T;
+    const int64_t k0 = (int64_t)blockIdx.x / ntiles * WG_T;
+    const int64_t n0 = (int64_t)blockIdx.x % ntiles * WG_T;
+    const int col = tid & (WG_T - 1), prow = tid / WG_T;   // this thread's column, rows prow + 2 q
+    const bool ka = k0 + col < K, kb = n0 + col < Nc;
+    const double *pa = C + (ka ? k0 + col : 0), *pb = gY + c0 + (kb ? n0 + col : 0);
+    double ra[LPT], rb[LPT];
+    auto load_tiles = [&](int64_t p0) {
+#pragma unroll
+        for (int q = 0; q < LPT; ++q) {
+            const int64_t p = p0 + prow + 2 * q;
+            ra[q] = (ka && p < P) ? pa[p * ldc] : 0.0;
+            rb[q] = (kb && p < P) ? pb[p * N] : 0.0;
+        }
+    };
+    auto store_tiles = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < LPT; ++q) {
+            s_a[buf][prow + 2 * q][col] = ra[q];
+            s_b[buf][prow + 2 * q][col] = rb[q];
+        }
+    };
+    d4v acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = (d4v){0.0, 0.0, 0.0, 0.0};
+    load_tiles(0);
+    store_tiles(0);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t p0 = 0; p0 < P; p0 += WG_KS, buf ^= 1) {
+        const bool more = p0 + WG_KS < P;
+        if (more) load_tiles(p0 + WG_KS);
+#pragma unroll
+        for (int k4 = 0; k4 < WG_KS; k4 += 4) {
+            double a[4], b[4];
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) a[rt] = s_a[buf][k4 + (lane >> 4)][wr * 64 + rt * 16 + (lane & 15)];
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) b[ct] = s_b[buf][k4 + (lane >> 4)][wc * 64 + ct * 16 + (lane & 15)];
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct)
+                    acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ct], acc[rt][ct], 0, 0, 0);
+        }
+        // the other buffer was last read before the previous step's barrier
+        if (more) store_tiles(buf ^ 1);
         __syncthreads();
-        if (tid < DB_BM) {
-            const int64_t k = k0 + tid;
-            s_enc[tid][0] = k < K ? senc[2 * k] : 0ull;
-            s_enc[tid][1] = k < K ? senc[2 * k + 1] : 0ull;
-        }
-        d4v acc[2][4];
+    }
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+    for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = (d4v){0.0, 0.0, 0.0, 0.0};
-        // operand tiles of a step: C^T (16 polynomials x 64 monomials, read
-        // along k) and gY (16 polynomials x 128 points, read along the points);
-        // the next step's are loaded into registers while this step's MFMAs run
-        double ra[4], rb[8];
-        auto load_tiles = [&](int64_t p0) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int idx = tid + q * DB_THREADS;
-                const int pp = idx / DB_BM, kr = idx % DB_BM;
-                const int64_t p = p0 + pp, k = k0 + kr;
-                ra[q] = (p < P && k < K) ? C[p * K + k] : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int idx = tid + q * DB_THREADS;
-                const int pp = idx / DB_BN, c = idx % DB_BN;
-                const int64_t p = p0 + pp, pt = n0 + c;
-                rb[q] = (p < P && pt < N) ? gY[p * N + pt] : 0.0;
-            }
-        };
-        load_tiles(0);
-        for (int64_t p0 = 0; p0 < P; p0 += DB_KS) {
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int idx = tid + q * DB_THREADS;
-                s_a[idx % DB_BM][idx / DB_BM] = ra[q];
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int idx = tid + q * DB_THREADS;
-                s_b[idx / DB_BN][idx % DB_BN] = rb[q];
-            }
-            __syncthreads();
-            if (p0 + DB_KS < P) load_tiles(p0 + DB_KS);
-#pragma unroll
-            for (int k4 = 0; k4 < DB_KS; k4 += 4) {
-                double a[2], b[4];
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt) a[rt] = s_a[wr * 32 + rt * 16 + (lane & 15)][k4 + (lane >> 4)];
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) b[ct] = s_b[k4 + (lane >> 4)][wc * 64 + ct * 16 + (lane & 15)];
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                    for (int ct = 0; ct < 4; ++ct)
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ct], acc[rt][ct], 0, 0, 0);
-            }
-        }
-        // W tile entries times the monomials' derivatives at their points
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int kr = wr * 32 + rt * 16 + (lane >> 4) + 4 * v;
-                const int64_t k = k0 + kr;
-                if (k >= K) continue;
-                const uint64_t e0 = s_enc[kr][0], e1 = s_enc[kr][1];
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    const int pl = ct * 16 + (lane & 15);   // point within the wave's 64
-                    add_monomial_grad(e0, e1, basis + k * n, n, s_x + wc * 64 + pl, DB_BN, acc[rt][ct][v],
-                                      my_acc + pl);
-                }
+                const int64_t k = k0 + wr * 64 + rt * 16 + (lane >> 4) + 4 * v;
+                const int64_t c = n0 + wc * 64 + ct * 16 + (lane & 15);
+                if (k < K && c < Nc) W[k * ldw + c] = acc[rt][ct][v];
             }
-    }
-    __syncthreads();
-    // waves (0, wc) and (1, wc) cover the same 64 points: add in that order
-    for (int idx = tid; idx < DB_BN * n; idx += DB_THREADS) {
-        const int pl = idx / n, j = idx % n;
-        const int c = pl >> 6, l = pl & 63;
-        const int64_t pt = n0 + pl;
-        if (pt < N)
-            dX[pt * n + j] = s_acc[((size_t)(0 * 2 + c) * n + j) * kWave + l] +
-                             s_acc[((size_t)(1 * 2 + c) * n + j) * kWave + l];
-    }
 }
 
 // ------------------------------------------------------------ split kernels
@@ -1230,58 +1197,103 @@ __global__ void __launch_bounds__(SP_THREADS) k_split_gemm(int64_t R, int64_t RB
         }
 }
 
-constexpr int DW_WAVES = 4, DW_KSPLIT = 16;
+constexpr int DW_WAVES = 4;
+
+// K ranges of k_dx_from_w for a chunk of Nc points: about 1,024 workgroups
+inline int dw_ksplit(int64_t Nc) { return (int)std::max<int64_t>(1, std::min<int64_t>(64, 65536 / std::max<int64_t>(Nc, 1))); }
 
 // Partial dX of a chunk of points from W [K x ldw] (FP64): block (point
-// tile of 64, K range q of DW_KSPLIT), wave w the w-th quarter of that range;
+// tile of 64, K range q of gridDim.y), wave w the w-th quarter of that range;
 // lane = point.  Each wave adds W[k][pt] d v_k / d x_j into its accumulator
-// block [n][64] in LDS in the order of k, then the four blocks are added in
-// wave order into part[q][pt][j].  Dynamic LDS: points [n + 1][64] (last row
-// ones), accumulators [DW_WAVES][n][64].
+// block [n + 1][64] in LDS in the order of k, then the four blocks are added
+// in wave order into part[q][pt][j].  A monomial of degree <= 4 is its factor
+// list (padded with n, the row of ones): each factor slot adds the product of
+// the other three, so a repeated variable gets its multiplicity by itself and
+// nothing depends on the degree; padding slots add into row n, which is not
+// read.  That is 4 coordinate reads, 10 multiplications and 4 LDS adds per
+// monomial and wave, eight monomials' W in flight; the general form (support
+// encoding, eight slots) takes over where a list is longer.  Bound by LDS.
+// Dynamic LDS: points [n + 1][64] (last row ones), accumulators
+// [DW_WAVES][n + 1][64].
 __global__ void __launch_bounds__(DW_WAVES * 64) k_dx_from_w(int n, int64_t K, const uint8_t *basis,
-                                                             const uint64_t *senc, const double *W, int64_t ldw,
-                                                             int64_t Nc, const double *X, double *part)
+                                                             const uint4 *__restrict__ fenc,
+                                                             const uint64_t *__restrict__ senc,
+                                                             const double *__restrict__ W, int64_t ldw, int64_t Nc,
+                                                             const double *X, double *part)
 {
     extern __shared__ double s_dyn[];
-    double *s_x = s_dyn;                              // [n + 1][64]
-    double *s_acc = s_dyn + (size_t)(n + 1) * 64;     // [DW_WAVES][n][64]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int np1 = n + 1;
+    double *s_x = s_dyn;                          // [n + 1][64]
+    double *s_acc = s_dyn + (size_t)np1 * 64;     // [DW_WAVES][n + 1][64]
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
     const int64_t p0 = (int64_t)blockIdx.x * 64;
     const int q = blockIdx.y;
-    for (int idx = tid; idx < (n + 1) * 64; idx += DW_WAVES * 64) {
+    for (int idx = tid; idx < np1 * 64; idx += DW_WAVES * 64) {
         const int i = idx / 64, c = idx % 64;
         s_x[idx] = i == n ? 1.0 : (p0 + c < Nc ? X[(p0 + c) * n + i] : 0.0);
     }
-    for (int idx = tid; idx < DW_WAVES * n * 64; idx += DW_WAVES * 64) s_acc[idx] = 0.0;
+    for (int idx = tid; idx < DW_WAVES * np1 * 64; idx += DW_WAVES * 64) s_acc[idx] = 0.0;
     __syncthreads();
-    const int64_t per = ceil_div(K, (int64_t)DW_KSPLIT * DW_WAVES);
+    const int64_t per = ceil_div(K, (int64_t)gridDim.y * DW_WAVES);
     const int64_t kb = ((int64_t)q * DW_WAVES + w) * per;
     const int64_t ke = kb + per < K ? kb + per : K;
     const int64_t pt = p0 + lane;
-    double *my_acc = s_acc + (size_t)w * n * 64 + lane;
-    if (pt < Nc)
-        for (int64_t k = kb; k < ke; ++k) {
-            const double wv = W[k * ldw + pt];
-            add_monomial_grad(senc[2 * k], senc[2 * k + 1], basis + k * n, n, s_x + lane, 64, wv, my_acc);
+    const double *xl = s_x + lane;
+    double *my_acc = s_acc + (size_t)w * np1 * 64 + lane;
+    auto add = [&](int i, double v) {
+        __hip_atomic_fetch_add(my_acc + i * 64, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    };
+    if (pt < Nc) {
+        const double *Wp = W + pt;
+        constexpr int UN = 8;
+        for (int64_t k = kb; k < ke; k += UN) {
+            const int cnt = (int)(ke - k < UN ? ke - k : UN);
+            double wv[UN];
+            uint4 e[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int64_t ku = k + (u < cnt ? u : 0);
+                wv[u] = Wp[ku * ldw];
+                e[u] = fenc[ku];
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if (u >= cnt) break;
+                if (e[u].w <= 4u) {
+                    const int f0 = (int)(e[u].x & 0xffu), f1 = (int)((e[u].x >> 8) & 0xffu);
+                    const int f2 = (int)((e[u].x >> 16) & 0xffu), f3 = (int)(e[u].x >> 24);
+                    const double x0 = xl[f0 * 64], x1 = xl[f1 * 64], x2 = xl[f2 * 64], x3 = xl[f3 * 64];
+                    const double x01 = x0 * x1, x23 = x2 * x3;
+                    add(f0, wv[u] * (x1 * x23));
+                    add(f1, wv[u] * (x0 * x23));
+                    add(f2, wv[u] * (x01 * x3));
+                    add(f3, wv[u] * (x01 * x2));
+                } else {
+                    add_monomial_grad(senc[2 * (k + u)], senc[2 * (k + u) + 1], basis + (k + u) * n, n, xl, 64, wv[u],
+                                      my_acc);
+                }
+            }
         }
+    }
     __syncthreads();
     for (int idx = tid; idx < 64 * n; idx += DW_WAVES * 64) {
         const int pl = idx / n, j = idx % n;
         if (p0 + pl >= Nc) continue;
         double a = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < DW_WAVES; ++ww) a += s_acc[((size_t)ww * n + j) * 64 + pl];
+        for (int ww = 0; ww < DW_WAVES; ++ww) a += s_acc[((size_t)ww * np1 + j) * 64 + pl];
         part[((size_t)q * Nc + p0 + pl) * n + j] = a;
     }
 }
 
-// dX rows of a chunk: the DW_KSPLIT partial sums added in order
-__global__ void k_dx_reduce(const double *part, int64_t Nc, int n, double *dX)
+// dX rows of a chunk: the ksplit partial sums added in order, to zero or
+// (add) to what earlier monomials left there
+__global__ void k_dx_reduce(const double *part, int ksplit, int64_t Nc, int n, bool add, double *dX)
 {
     const int64_t m = Nc * n;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        double a = 0.0;
-        for (int q = 0; q < DW_KSPLIT; ++q) a += part[q * m + i];
+        double a = add ? dX[i] : 0.0;
+        for (int q = 0; q < ksplit; ++q) a += part[q * m + i];
         dX[i] = a;
     }
 }
@@ -1410,24 +1422,38 @@ poly_status dense_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_ex
 
 // ------------------------------------------------- reverse mode: host side
 
-// dynamic LDS of the dX kernel: points [(n + 1)][128], four accumulator blocks [n][64]
-inline size_t dense_bwd_dx_lds(int n) { return ((size_t)(n + 1) * DB_BN + 4 * (size_t)n * kWave) * 8; }
-constexpr size_t DB_DX_LDS_MAX = 130 * 1024;   // beside ~27 KB of static LDS
+// dX: n <= 43 (points and accumulators of k_dx_from_w then take at most 113 KB of LDS)
+constexpr int DB_DX_MAX_N = 43;
+inline size_t dx_from_w_lds(int n) { return (size_t)(1 + DW_WAVES) * (n + 1) * 64 * 8; }
 
 namespace {
 
-constexpr int64_t DX_CHUNK = 4096;   // points per W chunk of the split dX
+// A W chunk of dX: at most 4,096 points.  In FP64 also at most 512 MB: first
+// by fewer points (N cut evenly, no chunk below one tile), then by at most
+// DX_K_CHUNK monomials.
+constexpr int64_t DX_CHUNK = 4096;
+constexpr int64_t DX_W_BYTES = int64_t(512) << 20;
+constexpr int64_t DX_K_CHUNK = DX_W_BYTES / (8 * WG_T);
+
+int64_t dx_chunk(int64_t K, int64_t N, poly_prec prec)
+{
+    if (prec == POLY_SPLIT_BF16) return std::min<int64_t>((int64_t)align_up((size_t)N, 64), DX_CHUNK);
+    const int64_t fit = DX_W_BYTES / (8 * std::max<int64_t>(K, 1)) / WG_T * WG_T;
+    const int64_t most = std::max<int64_t>(WG_T, std::min(DX_CHUNK, fit));
+    const int64_t chunks = std::max<int64_t>(1, ceil_div(N, most));
+    return (int64_t)align_up((size_t)std::max<int64_t>(1, ceil_div(N, chunks)), WG_T);
+}
 
 struct DenseBwdPlan {
     size_t fenc, senc, gs, sigw, ct, gyt, w, part, total;
-    int64_t Np, Pp, Nc;
+    int64_t Np, Pp, Nc, Kc;
 };
 
 // workspace: status word, factor lists and support encodings of the basis;
 // split: for dC the gY digit planes [S][ceil(P / 32) * 32][Np] and the scales
 // of V^T [ceil(N / DN_KB)][K]; for dX the digit planes of C^T [S][ceil(K /
-// 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp], one W chunk [K][Nc]
-// and the partial sums [DW_KSPLIT][Nc][n]
+// 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp]; both precisions: one W
+// chunk [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n]
 DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S)
 {
     size_t off = kWsHeadBytes;
@@ -1442,14 +1468,17 @@ DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
     d.gs = d.sigw = d.ct = d.gyt = d.w = d.part = 0;
     d.Np = (int64_t)align_up((size_t)N, SP_KS);
     d.Pp = (int64_t)align_up((size_t)P, SP_KS);
-    d.Nc = std::min<int64_t>((int64_t)align_up((size_t)N, 64), DX_CHUNK);
+    d.Nc = dx_chunk(K, N, prec);
+    d.Kc = prec == POLY_SPLIT_BF16 ? K : std::min(K, DX_K_CHUNK);
     if (prec == POLY_SPLIT_BF16) {
         d.gs = take((size_t)S * ceil_div(P, 32) * 32 * d.Np * 2);
         d.sigw = take((size_t)ceil_div(N, DN_KB) * K * 4);
         d.ct = take((size_t)S * ceil_div(K, 32) * 32 * d.Pp * 2);
         d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
-        d.w = take((size_t)K * d.Nc * 8);
-        d.part = take((size_t)DW_KSPLIT * d.Nc * n * 8);
+    }
+    if (n <= DB_DX_MAX_N) {
+        d.w = take((size_t)d.Kc * d.Nc * 8);
+        d.part = take((size_t)dw_ksplit(d.Nc) * d.Nc * n * 8);
     }
     d.total = align_up(off, 256);
     return d;
@@ -1519,7 +1548,7 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
     if (max_exp < 0 || max_exp > 255) return POLY_ERR_ARG;
     if ((K > 0 && !basis) || (P > 0 && K > 0 && !C) || (N > 0 && !X) || (P > 0 && N > 0 && !gY)) return POLY_ERR_ARG;
     if (!ws || ws_bytes < need) return POLY_ERR_WORKSPACE;
-    if (dX && dense_bwd_dx_lds(n) > DB_DX_LDS_MAX) return POLY_ERR_UNSUPPORTED;
+    if (dX && n > DB_DX_MAX_N) return POLY_ERR_UNSUPPORTED;
     const DenseBwdPlan d = plan_dense_bwd(n, K, P, N, prec, S);
     // split dC: a step's coordinates are at most SW_XR_MAX per thread (n <= 64),
     // and a workgroup's rows of one gY plane stay below 2^31 bytes
@@ -1531,8 +1560,7 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
     if (prec == POLY_SPLIT_BF16 && dX && d.Pp * 512 + 256 > INT32_MAX) return POLY_ERR_UNSUPPORTED;
     static bool attr = false;
     if (!attr) {
-        (void)hipFuncSetAttribute((const void *)k_dense_bwd_dx, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)DB_DX_LDS_MAX);
+        (void)hipFuncSetAttribute((const void *)k_dx_from_w, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         (void)hipFuncSetAttribute((const void *)k_dense_bwd_dc<64>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   64 * 1024);
         (void)hipFuncSetAttribute((const void *)k_dense_bwd_dc<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1584,39 +1612,43 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
             tl.done(s);
         }
     }
-    if (dX && N > 0 && prec == POLY_SPLIT_BF16 && P > 0 && K > 0) {
+    if (dX && N > 0 && (P == 0 || K == 0)) {
+        hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)ceil_div(N * n, 256)), dim3(256), 0, s, (unsigned long long *)dX,
+                           0ull, N * n);
+    } else if (dX && N > 0) {
         unsigned short *Cts = (unsigned short *)((char *)ws + d.ct);
         unsigned short *Gts = (unsigned short *)((char *)ws + d.gyt);
         double *Wc = (double *)((char *)ws + d.w);
         double *part = (double *)((char *)ws + d.part);
-        static bool xattr = false;
-        if (!xattr) {
-            (void)hipFuncSetAttribute((const void *)k_dx_from_w, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      160 * 1024);
-            xattr = true;
+        if (prec == POLY_SPLIT_BF16) {
+            const int64_t nkb = ceil_div(d.Pp, DN_KB);
+            hipLaunchKernelGGL(k_split_ct, dim3((unsigned)(ceil_div(K, 32) * nkb)), dim3(DN_KB), 0, s, C, K, K, P,
+                               d.Pp, S, Cts);
+            hipLaunchKernelGGL(k_split_ct, dim3((unsigned)(ceil_div(N, 32) * nkb)), dim3(DN_KB), 0, s, gY, N, N, P,
+                               d.Pp, S, Gts);
         }
-        const int64_t nkb = ceil_div(d.Pp, DN_KB);
-        hipLaunchKernelGGL(k_split_ct, dim3((unsigned)(ceil_div(K, 32) * nkb)), dim3(DN_KB), 0, s, C, K, K, P, d.Pp,
-                           S, Cts);
-        hipLaunchKernelGGL(k_split_ct, dim3((unsigned)(ceil_div(N, 32) * nkb)), dim3(DN_KB), 0, s, gY, N, N, P, d.Pp,
-                           S, Gts);
-        const size_t xlds = ((size_t)(n + 1) * 64 + (size_t)DW_WAVES * n * 64) * 8;
-        for (int64_t c0 = 0; c0 < N; c0 += d.Nc) {
-            const int64_t nc = std::min<int64_t>(d.Nc, N - c0);
-            switch (S) {
-            case 3: launch_split_gemm<3>(K, Cts, nc, ceil_div(N, 32), c0 / 32, Gts, d.Pp, Wc, d.Nc, s); break;
-            case 4: launch_split_gemm<4>(K, Cts, nc, ceil_div(N, 32), c0 / 32, Gts, d.Pp, Wc, d.Nc, s); break;
-            default: launch_split_gemm<5>(K, Cts, nc, ceil_div(N, 32), c0 / 32, Gts, d.Pp, Wc, d.Nc, s); break;
+        const int ksplit = dw_ksplit(d.Nc);
+        for (int64_t c0 = 0; c0 < N; c0 += d.Nc)
+            for (int64_t k0 = 0; k0 < K; k0 += d.Kc) {   // split: one range
+                const int64_t nc = std::min<int64_t>(d.Nc, N - c0), kc = std::min<int64_t>(d.Kc, K - k0);
+                if (prec == POLY_FP64) {
+                    hipLaunchKernelGGL(k_dense_w, dim3((unsigned)(ceil_div(nc, WG_T) * ceil_div(kc, WG_T))),
+                                       dim3(WG_THREADS), 0, s, kc, K, P, C + k0, N, c0, nc, gY, Wc, d.Nc);
+                } else {
+                    const int64_t rb = ceil_div(N, 32), cb = c0 / 32;
+                    switch (S) {
+                    case 3: launch_split_gemm<3>(K, Cts, nc, rb, cb, Gts, d.Pp, Wc, d.Nc, s); break;
+                    case 4: launch_split_gemm<4>(K, Cts, nc, rb, cb, Gts, d.Pp, Wc, d.Nc, s); break;
+                    default: launch_split_gemm<5>(K, Cts, nc, rb, cb, Gts, d.Pp, Wc, d.Nc, s); break;
+                    }
+                }
+                hipLaunchKernelGGL(k_dx_from_w, dim3((unsigned)ceil_div(nc, 64), (unsigned)ksplit),
+                                   dim3(DW_WAVES * 64), dx_from_w_lds(n), s, n, kc, basis + k0 * n,
+                                   (const uint4 *)fenc + k0, (const uint64_t *)senc + 2 * k0, (const double *)Wc,
+                                   d.Nc, nc, X + c0 * n, part);
+                hipLaunchKernelGGL(k_dx_reduce, dim3((unsigned)std::min<int64_t>(ceil_div(nc * n, 256), 65535)),
+                                   dim3(256), 0, s, (const double *)part, ksplit, nc, n, k0 > 0, dX + c0 * n);
             }
-            hipLaunchKernelGGL(k_dx_from_w, dim3((unsigned)ceil_div(nc, 64), (unsigned)DW_KSPLIT),
-                               dim3(DW_WAVES * 64), xlds, s, n, K, basis, (const uint64_t *)senc,
-                               (const double *)Wc, d.Nc, nc, X + c0 * n, part);
-            hipLaunchKernelGGL(k_dx_reduce, dim3((unsigned)std::min<int64_t>(ceil_div(nc * n, 256), 65535)),
-                               dim3(256), 0, s, (const double *)part, nc, n, dX + c0 * n);
-        }
-    } else if (dX && N > 0) {
-        hipLaunchKernelGGL(k_dense_bwd_dx, dim3((unsigned)ceil_div(N, DB_BN)), dim3(DB_THREADS), dense_bwd_dx_lds(n), s,
-                           n, K, basis, (const uint64_t *)senc, P, C, gY, N, X, dX);
     }
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_ERR_HIP;
 }
