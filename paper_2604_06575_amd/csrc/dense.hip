@@ -92,19 +92,43 @@ __device__ inline unsigned short bf16_bits_exact(float f)
 
 constexpr int D64_BN = 128, D64_KS = 16, D64_THREADS = 256;   // rows per workgroup: BM, 64 or 128
 
+// A step's V values of this thread from one factor word each (degree <= 4),
+// with no branch, so that the scheduler can spread them among the MFMAs of
+// the step before; a value past `live` is exactly 0.
+__device__ inline double short_value(uint32_t word, const double *x, int xs, bool live)
+{
+    const double x0 = x[(word & 0xffu) * xs];
+    const double x1 = x[((word >> 8) & 0xffu) * xs];
+    const double x2 = x[((word >> 16) & 0xffu) * xs];
+    const double x3 = x[(word >> 24) * xs];
+    const double v = ((x0 * x1) * x2) * x3;
+    return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) & (live ? ~0ull : 0ull));
+}
+
 // grid: x = N tiles (fastest, so concurrently running workgroups share a C
 // row panel), y = P tiles of BM rows (64 or 128: each wave holds BM / 32
 // row tiles of 16 against four column tiles, so a V tile formed in LDS feeds
-// BM rows).  Dynamic LDS: (n + 1) * D64_BN doubles for the
+// BM rows), z = ranges of `kz` monomials: with more than one, range z leaves
+// its partial sums in Y + z * P * N (a workspace; ys = 1) for
+// k_dense_reduce.  Dynamic LDS: (n + 1) * D64_BN doubles for the
 // points and a row of ones.  Each K step: the C tile and the factor lists of
 // the step after next are loaded into registers (buffer loads, so the only
 // per-thread addresses are 32-bit offsets and no load waits on another),
-// the MFMAs of this step run, and the V tile of the next step is formed from
-// factor lists staged in LDS one step ahead.
+// and the MFMAs of this step run with the V values of the next step formed
+// among them, from factor lists staged in LDS one step ahead: the scheduling
+// groups at the end of the step put LDS reads and vector instructions behind
+// each MFMA (64 cycles of the FP64 pipe), where the compiler had issued the
+// MFMAs in one run and the values after them, in the pipe's idle time.  The
+// values are those of one factor word; a step that holds a longer list is
+// formed again, in general form, as it is stored.  Bound by the FP64 MFMA
+// pipe.  500 x 10,626 x 5,000 (3 ranges of K): 1.14 ms with the reduction, 47
+// TFLOP/s (one range on 160 of 256 CUs, values formed after the MFMAs: 2.81
+// ms); 4,096 x 46,376 x 8,192, one range: 58 TFLOP/s (43).
 template <int BM>
 __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, const uint8_t *basis,
-                                                           const uint4 *enc, int64_t P, const double *C,
-                                                           int64_t N, const double *X, double *Y, int64_t ys)
+                                                              const uint4 *enc, int64_t P, const double *C,
+                                                              int64_t N, const double *X, double *Y, int64_t ys,
+                                                              int64_t kz)
 {
     constexpr int RT = BM / 32;                        // 16-row MFMA tiles per wave
     constexpr int TPR = D64_THREADS / BM, CPT = D64_KS / TPR;   // C tile loads: threads per row, entries per thread
@@ -112,12 +136,16 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
     __shared__ double s_c[BM][D64_KS + 1];
     __shared__ double s_v[D64_KS][D64_BN + 2];
     __shared__ uint4 s_enc[2][D64_KS];
+    __shared__ int s_high[2];                          // a factor list of the step has degree > 4
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int wr = w >> 1, wc = w & 1;                 // wave: BM / 2 rows x 64 points
     const int64_t r0 = (int64_t)blockIdx.y * BM;
     const int64_t n0 = (int64_t)blockIdx.x * D64_BN;
+    const int64_t kb = (int64_t)blockIdx.z * kz;       // this range: monomials kb .. ke
+    const int64_t ke = kb + kz < K ? kb + kz : K;
+    Y += (int64_t)blockIdx.z * P * N;
     for (int idx = tid; idx < (n + 1) * D64_BN; idx += D64_THREADS) {
         const int i = idx / D64_BN, c = idx % D64_BN;
         const int64_t pt = n0 + c;
@@ -141,7 +169,7 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
     uint4 ereg = make_uint4(0, 0, 0, 0);
     auto load_c = [&](int64_t kk) {
 #pragma unroll
-        for (int q = 0; q < CPT; ++q)   // entries past K (next row's) are masked when stored
+        for (int q = 0; q < CPT; ++q)   // entries past the range (or the row) are masked when stored
             creg[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rc, cbase + ((int)kk + q) * 8, 0, 0));
     };
     auto load_enc = [&](int64_t kk) {   // factor lists of k = kk + tid, tid < D64_KS (zero past K)
@@ -152,50 +180,72 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
             ereg = make_uint4(e[0], e[1], e[2], e[3]);
         }
     };
-    auto form_v = [&](int64_t kk, const uint4 *le) {
+    auto store_enc = [&](int buf) {
+        if (tid < D64_KS) {
+            s_enc[buf][tid] = ereg;
+            const unsigned long long hi = __ballot(ereg.w > 4u);
+            if (tid == 0) s_high[buf] = hi != 0;
+        }
+    };
+    auto form_v = [&](int64_t kk, const uint4 *le) {   // degree <= 4
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-            vreg[q] = kk + vkb + q < K ? factor_value(le[vkb + q], basis + (kk + vkb + q) * n, n, s_x + vcol, D64_BN)
-                                       : 0.0;
+            vreg[q] = short_value(le[vkb + q].x, s_x + vcol, D64_BN, kk + vkb + q < ke);
+    };
+    auto mfma_k4 = [&](int k4) {
+        double a[RT], b[4];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) a[rt] = s_c[wr * (BM / 2) + rt * 16 + (lane & 15)][k4 + (lane >> 4)];
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) b[ct] = s_v[k4 + (lane >> 4)][wc * 64 + ct * 16 + (lane & 15)];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+                acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ct], acc[rt][ct], 0, 0, 0);
     };
     // stage 0 operands; factor lists of step 1 in flight
-    load_enc(0);
-    load_c(0);
+    load_enc(kb);
+    load_c(kb);
     __syncthreads();
-    if (tid < D64_KS) s_enc[0][tid] = ereg;
-    load_enc(D64_KS);
+    store_enc(0);
+    load_enc(kb + D64_KS);
     __syncthreads();
-    form_v(0, s_enc[0]);
+    form_v(kb, s_enc[0]);
     int par = 1;   // s_enc buffer of the next step's factor lists
-    for (int64_t k0 = 0; k0 < K; k0 += D64_KS) {
+    for (int64_t k0 = kb; k0 < ke; k0 += D64_KS) {
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < CPT; ++q) s_c[crow][ckk + q] = k0 + ckk + q < K ? creg[q] : 0.0;
+        for (int q = 0; q < CPT; ++q) s_c[crow][ckk + q] = k0 + ckk + q < ke ? creg[q] : 0.0;
 #pragma unroll
         for (int q = 0; q < 8; ++q) s_v[vkb + q][vcol] = vreg[q];
-        if (tid < D64_KS) s_enc[par][tid] = ereg;
+        if (__builtin_amdgcn_readfirstlane(s_high[par ^ 1])) {   // degrees above 4: the general form
+            const uint4 *le = s_enc[par ^ 1];
+#pragma unroll 1
+            for (int q = 0; q < 8; ++q) {
+                const int64_t k = k0 + vkb + q;
+                if (k < ke) s_v[vkb + q][vcol] = factor_value(le[vkb + q], basis + k * n, n, s_x + vcol, D64_BN);
+            }
+        }
+        store_enc(par);
         __syncthreads();
         const int64_t k1 = k0 + D64_KS;
         // next stage's C tile and the factor lists after it: in flight while the MFMAs run
-        if (k1 < K) {
+        if (k1 < ke) {
             load_c(k1);
             load_enc(k1 + D64_KS);
         }
+        // the MFMAs of this step and the V values of the next, one
+        // straight-line block
+        form_v(k1, s_enc[par]);
 #pragma unroll
-        for (int k4 = 0; k4 < D64_KS; k4 += 4) {
-            double a[RT], b[4];
+        for (int k4 = 0; k4 < D64_KS; k4 += 4) mfma_k4(k4);
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) a[rt] = s_c[wr * (BM / 2) + rt * 16 + (lane & 15)][k4 + (lane >> 4)];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) b[ct] = s_v[k4 + (lane >> 4)][wc * 64 + ct * 16 + (lane & 15)];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
-                    acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ct], acc[rt][ct], 0, 0, 0);
+        for (int i = 0; i < 16 * RT; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // vector instructions
         }
-        // next stage's V tile (VALU work beside the MFMAs)
-        if (k1 < K) form_v(k1, s_enc[par]);
         par ^= 1;
     }
 #pragma unroll
@@ -212,6 +262,16 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
             }
 }
 
+// out[i * os] = sum over the ranges z of part[z * L + i], in order
+__global__ void k_dense_reduce(const double *part, int64_t L, int nz, double *out, int64_t os)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < L; i += (int64_t)gridDim.x * blockDim.x) {
+        double a = part[i];
+        for (int z = 1; z < nz; ++z) a += part[(int64_t)z * L + i];
+        out[i * os] = a;
+    }
+}
+
 // ------------------------------------------------------- FP64 reverse mode
 //
 // Reverse mode of Y = C V for a cotangent gY [P x N]:
@@ -223,53 +283,117 @@ __global__ void __launch_bounds__(D64_THREADS) k_dense_f64(int n, int64_t K, con
 
 constexpr int DB_BN = 128, DB_KS = 16, DB_THREADS = 256;
 
-// dC tile: rows p (64), columns k (128), contraction over points in steps
-// of 16.  Each thread owns one monomial column (its factor list held in
+// dC tile: rows p (BM), columns k (128), contraction over points in steps of
+// 16.  Each thread owns one monomial column (its factor list held in
 // registers) and forms 8 of its values per step from the step's points,
-// staged in LDS (dynamic: (n + 1) * 16 doubles, last row ones).
+// staged point-major in LDS (a wave's lanes read one point's coordinates at
+// the variables their monomials name, which spreads over the banks; stored
+// variable-major they shared two).  As in k_dense_f64 the next step's gY
+// tile, points and values are fetched and formed among this step's MFMAs;
+// coordinates go through registers for n <= 32 and straight to LDS beyond.
+// z = ranges of `nzp` points, whose partial sums k_dense_reduce adds.
+// Dynamic LDS: [2][DB_KS][n + 1] doubles, the last of each point one.
+// Bound by the FP64 MFMA pipe.  500 x 10,626 x 5,000: 1.17 ms with the
+// reduction (45 TFLOP/s; before, one range, no prefetch: 2.02 ms); 4,096 x
+// 46,376 x 8,192: 53 TFLOP/s (43).
 template <int BM>
 __global__ void __launch_bounds__(DB_THREADS) k_dense_bwd_dc(int n, int64_t K, const uint8_t *basis, const uint4 *enc,
                                                             int64_t P, const double *gY, int64_t N, const double *X,
-                                                            double *dC)
+                                                            double *dC, int64_t nzp)
 {
     constexpr int RT = BM / 32;                      // 16-row MFMA tiles per wave
     constexpr int TPR = DB_THREADS / BM, CPT = DB_KS / TPR;   // gY tile loads: threads per row, points per thread
-    extern __shared__ double s_xp[];                 // [n + 1][DB_KS]
+    constexpr int XR = 2;                            // coordinates per thread and step held in registers (n <= 32)
+    extern __shared__ double s_xp[];                 // [2][DB_KS][n + 1]
     __shared__ double s_a[BM][DB_KS + 1];
     __shared__ double s_b[DB_KS][DB_BN + 2];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = tid >> 6;
     const int wr = w >> 1, wc = w & 1;
+    const int np1 = n + 1;
     const int64_t r0 = (int64_t)blockIdx.y * BM;
     const int64_t k0 = (int64_t)blockIdx.x * DB_BN;
+    const int64_t pb = (int64_t)blockIdx.z * nzp;    // this range: points pb .. pe
+    const int64_t pe = pb + nzp < N ? pb + nzp : N;
+    dC += (int64_t)blockIdx.z * P * K;
     const int vcol = tid & (DB_BN - 1), vpb = (tid >> 7) * 8;
     const int64_t kcol = k0 + vcol;
     const uint4 my_enc = kcol < K ? enc[kcol] : make_uint4(0, 0, 0, 0);
+    const uint8_t *my_row = basis + (kcol < K ? kcol : 0) * n;
+    const bool high = my_enc.w > 4u;
     const int arow = tid / TPR, acol = (tid % TPR) * CPT;
+    const bool arow_live = r0 + arow < P;
+    const double *ga = gY + (arow_live ? r0 + arow : 0) * N;
+    const bool xregs = n * DB_KS <= XR * DB_THREADS;
+    for (int idx = tid; idx < 2 * DB_KS; idx += DB_THREADS) s_xp[idx * np1 + n] = 1.0;
+    int xo[XR];   // LDS slot of this thread's coordinates of a step, or -1
+#pragma unroll
+    for (int q = 0; q < XR; ++q) {
+        const int e = tid + q * DB_THREADS;
+        xo[q] = e < DB_KS * n ? (e / n) * np1 + e % n : -1;
+    }
+    double areg[CPT], xreg[XR], breg[8];
+    // loads are unconditional (index clamped into the array), masked when stored
+    auto load_a = [&](int64_t pp) {
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) {
+            const int64_t pt = pp + acol + q;
+            areg[q] = ga[pt < N ? pt : N - 1];
+        }
+    };
+    auto load_x = [&](int64_t pp) {
+        const int64_t last = N * n - 1;
+#pragma unroll
+        for (int q = 0; q < XR; ++q) {
+            const int64_t g = pp * n + tid + q * DB_THREADS;
+            xreg[q] = X[g < last ? g : last];
+        }
+    };
+    auto store_x = [&](int64_t pp, int buf) {
+        double *x = s_xp + buf * DB_KS * np1;
+        if (xregs) {
+#pragma unroll
+            for (int q = 0; q < XR; ++q)
+                if (xo[q] >= 0) x[xo[q]] = pp * n + tid + q * DB_THREADS < N * n ? xreg[q] : 0.0;
+        } else {
+            for (int e = tid; e < DB_KS * n; e += DB_THREADS)
+                x[(e / n) * np1 + e % n] = pp * n + e < N * n ? X[pp * n + e] : 0.0;
+        }
+    };
+    auto form_b = [&](int buf) {   // degree <= 4
+        const double *x = s_xp + (buf * DB_KS + vpb) * np1;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) breg[q] = short_value(my_enc.x, x + q * np1, 1, true);
+    };
     d4v acc[RT][4];
 #pragma unroll
     for (int a = 0; a < RT; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = (d4v){0.0, 0.0, 0.0, 0.0};
-    for (int64_t p0 = 0; p0 < N; p0 += DB_KS) {
+    if (xregs) load_x(pb);
+    store_x(pb, 0);
+    __syncthreads();
+    load_a(pb);
+    if (xregs) load_x(pb + DB_KS);
+    form_b(0);
+    int buf = 0;
+    for (int64_t p0 = pb; p0 < pe; p0 += DB_KS, buf ^= 1) {
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-            const int64_t r = r0 + arow, pt = p0 + acol + q;
-            s_a[arow][acol + q] = (r < P && pt < N) ? gY[r * N + pt] : 0.0;
-        }
-        for (int idx = tid; idx < (n + 1) * DB_KS; idx += DB_THREADS) {
-            const int i = idx / DB_KS, l = idx % DB_KS;
-            const int64_t pt = p0 + l;
-            s_xp[idx] = i == n ? 1.0 : (pt < N ? X[pt * n + i] : 0.0);
-        }
-        __syncthreads();
+        for (int q = 0; q < CPT; ++q) s_a[arow][acol + q] = arow_live && p0 + acol + q < pe ? areg[q] : 0.0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            s_b[vpb + q][vcol] =
-                kcol < K ? factor_value(my_enc, basis + kcol * n, n, s_xp + vpb + q, DB_KS) : 0.0;
+        for (int q = 0; q < 8; ++q) s_b[vpb + q][vcol] = breg[q];
+        if (high) {   // degrees above 4: the general form
+            const double *x = s_xp + (buf * DB_KS + vpb) * np1;
+#pragma unroll 1
+            for (int q = 0; q < 8; ++q) s_b[vpb + q][vcol] = factor_value(my_enc, my_row, n, x + q * np1, 1);
+        }
+        store_x(p0 + DB_KS, buf ^ 1);
         __syncthreads();
+        load_a(p0 + DB_KS);
+        if (xregs) load_x(p0 + 2 * DB_KS);
+        form_b(buf ^ 1);
 #pragma unroll
         for (int k4 = 0; k4 < DB_KS; k4 += 4) {
             double a[RT], b[4];
@@ -282,6 +406,12 @@ __global__ void __launch_bounds__(DB_THREADS) k_dense_bwd_dc(int n, int64_t K, c
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct)
                     acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ct], acc[rt][ct], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 16 * RT; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // vector instructions
         }
     }
 #pragma unroll
@@ -1302,8 +1432,42 @@ __global__ void k_dx_reduce(const double *part, int ksplit, int64_t Nc, int n, b
 
 namespace {
 
+// Ranges that a dense FP64 contraction of `steps` K steps over `tiles` output
+// tiles is cut into.  A CU's MFMA pipe is the bound, so a launch takes as long
+// as its busiest CU: blocks on it times (steps per range + a few for the
+// prologue and epilogue), a quarter more where one block is alone on it and
+// nothing fills its waits.  Ranges leave partial sums of `bytes` each that
+// k_dense_reduce reads again (counted at 4 TB/s, in steps of step_us).  The
+// fewest ranges of the lowest cost, at most 512 MB of partial sums and never
+// fewer than eight steps.  500 x 10,626 x 5,000: 160 tiles, 3 ranges (the
+// times at k_dense_f64).  The CU count is gfx950's, so that a workspace query
+// without a device agrees.
+int dense_ranges(int64_t tiles, int64_t steps, double bytes, double step_us)
+{
+    const double cus = 256.0;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int z = 1; z <= 16; ++z) {
+        if (z > 1 && (steps < 8 * z || z * bytes > 512.0 * 1024 * 1024)) break;
+        const double b = ceil((double)tiles * z / cus);
+        const double per = (double)ceil_div(steps, (int64_t)z) + 3.0;
+        double cost = b * per * (b < 2.0 ? 1.25 : 1.0);
+        if (z > 1) cost += ((z + 1) * bytes / 4e6 + 4.0) / step_us;
+        if (z == 1 || cost < 0.97 * best_cost) {
+            best = z;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// rows of C (or gY) per workgroup of the FP64 contractions
+inline int dense_f64_bm() { return tunables().dense_f64_rows == 128 ? 128 : 64; }
+
 struct DensePlan {
-    size_t enc, cs, sigv, total;
+    size_t enc, cs, sigv, part, total;
+    int nz;       // K ranges of the FP64 contraction
+    int64_t kz;   // monomials per range
 };
 
 DensePlan plan_dense(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S)
@@ -1316,12 +1480,20 @@ DensePlan plan_dense(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec,
     };
     DensePlan d;
     d.enc = take(16 * (size_t)K);
-    d.cs = 0;
-    d.sigv = 0;
+    d.cs = d.sigv = d.part = 0;
+    d.nz = 1;
+    d.kz = K;
     if (prec == POLY_SPLIT_BF16) {
         const int64_t Kp = align_up((size_t)K, 32);
         d.cs = take((size_t)S * ceil_div(P, 32) * 32 * Kp * 2);
         d.sigv = take((size_t)ceil_div(Kp, DN_KB) * N * 4);
+    } else if (K > 0 && P > 0 && N > 0) {
+        const int bm = dense_f64_bm();
+        const int64_t steps = ceil_div(K, D64_KS);
+        d.nz = dense_ranges(ceil_div(N, D64_BN) * ceil_div(P, bm), steps, 8.0 * (double)P * (double)N,
+                            1.7 * bm / 128);
+        d.kz = ceil_div(steps, (int64_t)d.nz) * D64_KS;
+        if (d.nz > 1) d.part = take((size_t)d.nz * P * N * 8);
     }
     d.total = align_up(off, 256);
     return d;
@@ -1371,7 +1543,7 @@ poly_status dense_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_ex
     if (prec == POLY_SPLIT_BF16 && split_lds_bytes(n, S) > 160 * 1024) return POLY_ERR_UNSUPPORTED;
     // both kernels address one block's rows of C (up to 128 x K doubles, or
     // 256 x Kp BF16 digits of one plane) with 32-bit byte offsets
-    const int bm = prec == POLY_FP64 && tunables().dense_f64_rows == 128 ? 128 : 64;
+    const int bm = prec == POLY_FP64 ? dense_f64_bm() : 64;
     if ((int64_t)align_up((size_t)K, 32) * 8 * bm + 256 > INT32_MAX) return POLY_ERR_UNSUPPORTED;
     const DensePlan d = plan_dense(n, K, P, N, prec, S);
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, (unsigned long long *)ws, 0ull, (int64_t)1);
@@ -1391,15 +1563,20 @@ poly_status dense_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_ex
                                       96 * 1024);
             attr = true;
         }
-        const dim3 grid((unsigned)ceil_div(N, D64_BN), (unsigned)ceil_div(P, bm));
+        const dim3 grid((unsigned)ceil_div(N, D64_BN), (unsigned)ceil_div(P, bm), (unsigned)d.nz);
+        double *out = d.nz > 1 ? (double *)((char *)ws + d.part) : Y;
+        const int64_t os = d.nz > 1 ? 1 : ys;
         TimedLaunch tl(POLY_TIMING_DENSE, s);
         if (bm == 128)
             hipLaunchKernelGGL(k_dense_f64<128>, grid, dim3(D64_THREADS), (size_t)(n + 1) * D64_BN * 8, s, n, K,
-                               basis, (const uint4 *)enc, P, C, N, X, Y, ys);
+                               basis, (const uint4 *)enc, P, C, N, X, out, os, d.kz);
         else
             hipLaunchKernelGGL(k_dense_f64<64>, grid, dim3(D64_THREADS), (size_t)(n + 1) * D64_BN * 8, s, n, K,
-                               basis, (const uint4 *)enc, P, C, N, X, Y, ys);
+                               basis, (const uint4 *)enc, P, C, N, X, out, os, d.kz);
         tl.done(s);
+        if (d.nz > 1)
+            hipLaunchKernelGGL(k_dense_reduce, dim3((unsigned)std::min<int64_t>(ceil_div(P * N, 256), 8192)), dim3(256),
+                               0, s, (const double *)out, P * N, d.nz, Y, ys);
     } else {
         unsigned short *Cs = (unsigned short *)((char *)ws + d.cs);
         int32_t *sig_v = (int32_t *)((char *)ws + d.sigv);
@@ -1445,15 +1622,18 @@ int64_t dx_chunk(int64_t K, int64_t N, poly_prec prec)
 }
 
 struct DenseBwdPlan {
-    size_t fenc, senc, gs, sigw, ct, gyt, w, part, total;
+    size_t fenc, senc, gs, sigw, ct, gyt, w, part, cpart, total;
     int64_t Np, Pp, Nc, Kc;
+    int nz;        // point ranges of the FP64 dC
+    int64_t nzp;   // points per range
 };
 
 // workspace: status word, factor lists and support encodings of the basis;
 // split: for dC the gY digit planes [S][ceil(P / 32) * 32][Np] and the scales
 // of V^T [ceil(N / DN_KB)][K]; for dX the digit planes of C^T [S][ceil(K /
 // 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp]; both precisions: one W
-// chunk [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n]
+// chunk [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n]; FP64: the
+// partial sums of dC's point ranges [nz][P][K]
 DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S)
 {
     size_t off = kWsHeadBytes;
@@ -1475,6 +1655,16 @@ DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
         d.sigw = take((size_t)ceil_div(N, DN_KB) * K * 4);
         d.ct = take((size_t)S * ceil_div(K, 32) * 32 * d.Pp * 2);
         d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
+    }
+    d.cpart = 0;
+    d.nz = 1;
+    d.nzp = N;
+    if (prec == POLY_FP64 && K > 0 && P > 0 && N > 0) {
+        const int bm = dense_f64_bm();
+        const int64_t steps = ceil_div(N, DB_KS);
+        d.nz = dense_ranges(ceil_div(K, DB_BN) * ceil_div(P, bm), steps, 8.0 * (double)P * (double)K, 1.7 * bm / 128);
+        d.nzp = ceil_div(steps, (int64_t)d.nz) * DB_KS;
+        if (d.nz > 1) d.cpart = take((size_t)d.nz * P * K * 8);
     }
     if (n <= DB_DX_MAX_N) {
         d.w = take((size_t)d.Kc * d.Nc * 8);
@@ -1562,9 +1752,9 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
     if (!attr) {
         (void)hipFuncSetAttribute((const void *)k_dx_from_w, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         (void)hipFuncSetAttribute((const void *)k_dense_bwd_dc<64>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  64 * 1024);
+                                  96 * 1024);
         (void)hipFuncSetAttribute((const void *)k_dense_bwd_dc<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  64 * 1024);
+                                  96 * 1024);
         attr = true;
     }
     uint4 *fenc = (uint4 *)((char *)ws + d.fenc);
@@ -1600,16 +1790,21 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
             default: launch_bwd_dc_split<5>(n, K, basis, fenc, P, Gs, N, d.Np, X, sig_w, dC, s); break;
             }
         } else {
-            const int bm = tunables().dense_f64_rows == 128 ? 128 : 64;
-            const dim3 grid((unsigned)ceil_div(K, DB_BN), (unsigned)ceil_div(P, bm));
+            const int bm = dense_f64_bm();
+            const dim3 grid((unsigned)ceil_div(K, DB_BN), (unsigned)ceil_div(P, bm), (unsigned)d.nz);
+            const size_t lds = (size_t)2 * DB_KS * (n + 1) * 8;
+            double *out = d.nz > 1 ? (double *)((char *)ws + d.cpart) : dC;
             TimedLaunch tl(POLY_TIMING_DENSE, s);
             if (bm == 128)
-                hipLaunchKernelGGL(k_dense_bwd_dc<128>, grid, dim3(DB_THREADS), (size_t)(n + 1) * DB_KS * 8, s, n, K,
-                                   basis, (const uint4 *)fenc, P, gY, N, X, dC);
+                hipLaunchKernelGGL(k_dense_bwd_dc<128>, grid, dim3(DB_THREADS), lds, s, n, K, basis,
+                                   (const uint4 *)fenc, P, gY, N, X, out, d.nzp);
             else
-                hipLaunchKernelGGL(k_dense_bwd_dc<64>, grid, dim3(DB_THREADS), (size_t)(n + 1) * DB_KS * 8, s, n, K,
-                                   basis, (const uint4 *)fenc, P, gY, N, X, dC);
+                hipLaunchKernelGGL(k_dense_bwd_dc<64>, grid, dim3(DB_THREADS), lds, s, n, K, basis,
+                                   (const uint4 *)fenc, P, gY, N, X, out, d.nzp);
             tl.done(s);
+            if (d.nz > 1)
+                hipLaunchKernelGGL(k_dense_reduce, dim3((unsigned)std::min<int64_t>(ceil_div(P * K, 256), 8192)),
+                                   dim3(256), 0, s, (const double *)out, P * K, d.nz, dC, (int64_t)1);
         }
     }
     if (dX && N > 0 && (P == 0 || K == 0)) {
