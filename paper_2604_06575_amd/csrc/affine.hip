@@ -13,21 +13,39 @@
 // Q_T is taken from the Householder reflector P = I - beta v v' that maps e
 // to -s e_n (s the sign of e_n): its first n - 1 columns are orthonormal and
 // orthogonal to e, so A is the leading block of P H P (a rank-two update of
-// H) and M = P [A^-1 0; 0 0] P (another one).  The direction does not depend
-// on the choice of Q_T.
+// H) and M = P [A^-1 0; 0 0] P (applied as such, never formed).  The
+// direction does not depend on the choice of Q_T.
 //
-// One workgroup per point; H (from the Hessian path), then the tangent
-// block, its inverse (Gauss-Jordan with partial pivoting) and M live in LDS
-// in place for n <= AN_MAX_N_LDS, and in the point's own Hessian slot in
-// global memory (row stride n, kept coherent within the workgroup by its
-// barriers) beyond that.  w is accumulated term by term from each monomial's factor list
-// (variables in ascending order, degree <= EV_MAX_DEG) with per-point power
-// tables.
+// One workgroup per point does all of it.  The gradient and the Hessian are
+// added up term by term in LDS from each monomial's factor list (variables in
+// ascending order, degree <= EV_MAX_DEG): every pair of factor slots adds the
+// product of the other factors, so repeated variables get their multiplicity
+// by themselves.  (Streaming the formed derivative polynomials over all
+// points, and passing the Hessians through memory, took 0.42 of 1.48 ms at
+// n = 64, 4,096 points, most of it in 29 small launches.)  A is inverted in
+// place by a blocked Gauss-Jordan elimination with partial pivoting:
+//   * a panel of NB columns is eliminated with one row per lane in registers,
+//     the pivot row broadcast by readlane (one wave) or through LDS (several);
+//     rows are not swapped, the pivots' permutation is applied when the
+//     inverse is read;
+//   * the panel then holds D = (pivot block)^-1 in the pivot rows and -A D in
+//     the others (G), and every other column is updated at once,
+//     A <- mask A + G U, with U the pivot rows' old entries and the mask
+//     dropping them: a product of depth NB on v_mfma_f64_16x16x4f64.
+// The matrix lives in LDS up to n = AN_MAX_N_LDS and in the workgroup's slot
+// of the workspace beyond.  n <= AN_WAVE_N takes one wave per point (no
+// barrier waits, four points per CU, so that one point's panel runs beside
+// another's MFMAs), larger n eight waves.  Bound by the panels' serial chain:
+// a pivot search, a reciprocal and a row update per column.
+// n = 64, 320 terms, 4,096 points: AFF64.  n = 160, 800 terms, 256 points:
+// AFF160.
 #include <limits.h>
 
 #include "kernels.h"
 
 namespace polyhip {
+
+typedef double d4v __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -39,315 +57,479 @@ __device__ inline double readlane_d(double v, int lane)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-template <int THREADS>
-__device__ inline double block_sum_d(double v, double *scratch)
+// v of the lane that the DPP control names; lanes without a source keep v
+template <int CTRL>
+__device__ inline double dpp_d(double v)
 {
-    double tot;
-    (void)block_exclusive_scan<THREADS>(v, scratch, tot);
-    return tot;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const int lo = (int)(unsigned)b, hi = (int)(unsigned)(b >> 32);
+    const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const unsigned h = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
+}
+
+// largest v of the wave (no NaN): row shifts, then row broadcasts, end in lane 63
+__device__ inline double wave_max_d(double v)
+{
+    v = fmax(v, dpp_d<0x111>(v));
+    v = fmax(v, dpp_d<0x112>(v));
+    v = fmax(v, dpp_d<0x114>(v));
+    v = fmax(v, dpp_d<0x118>(v));
+    v = fmax(v, dpp_d<0x142>(v));
+    v = fmax(v, dpp_d<0x143>(v));
+    return readlane_d(v, 63);
+}
+
+template <int NW>
+__device__ inline double sum_block(double v, double *red)
+{
+    v = wave_sum(v);
+    if (NW == 1) return v;
+    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) t += red[i];
+    __syncthreads();
+    return t;
+}
+
+__device__ inline void lds_add(double *p, double v)
+{
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// distinct variables and exponents of a factor list (ascending variables)
+__device__ inline int term_support(const uint4 &f, int d, int *var, int *mul)
+{
+    const uint32_t words[3] = {f.x, f.y, f.z};
+    int s = 0;
+    for (int r = 0; r < d; ++r) {
+        const int vi = (int)((words[r >> 2] >> (8 * (r & 3))) & 0xffu);
+        if (s > 0 && var[s - 1] == vi) {
+            ++mul[s - 1];
+        } else {
+            var[s] = vi;
+            mul[s] = 1;
+            ++s;
+        }
+    }
+    return s;
+}
+
+__device__ inline double power_product(const double *x, const int *var, const int *mul, int s, int a, int b, int l)
+{
+    double val = 1.0;
+    for (int r = 0; r < s; ++r)
+        for (int q = mul[r] - (a == r) - (b == r) - (l == r); q > 0; --q) val *= x[var[r]];
+    return val;
 }
 
 }  // namespace
 
-__global__ void __launch_bounds__(AN_THREADS) k_affine_normal(int n, const uint4 *enc, const double *coefs, int64_t T,
-                                                             const double *X, const double *G, double *H,
-                                                             double reg, double *D, double *gnorm, int32_t *status)
+template <int NW, int NB, bool LDSM>
+__global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const uint4 *__restrict__ enc,
+                                                              const double *__restrict__ coefs, int64_t T,
+                                                              const double *__restrict__ X, int64_t N, double *slots,
+                                                              double reg, double *D, double *gnorm, int32_t *status)
 {
+    constexpr int NT = NW * kWave;
+    constexpr int KK = NB / 4;                       // MFMAs per tile and panel
+    constexpr int PW = NW == 1 ? 1 : 4;              // waves that hold panel rows
+    constexpr int MAXU = 4;                          // column blocks (one wave) or half blocks per wave
     extern __shared__ double s_dyn[];
-    const bool in_lds = n <= AN_MAX_N_LDS;
-    const int ld = in_lds ? n + 1 : n;            // row stride of the matrix (padded in LDS)
-    constexpr int KP = EV_MAX_DEG + 1;            // powers x^0 .. x^EV_MAX_DEG
-    double *Hp = H + (size_t)blockIdx.x * n * n;
-    double *S = in_lds ? s_dyn : Hp;              // [n][ld]
-    double *e = in_lds ? S + (size_t)n * ld : s_dyn;   // [n] unit gradient
-    double *v = e + n;                            // [n] Householder vector
-    double *t = v + n;                            // [n] H v, then K v
-    double *u = t + n;                            // [n] v' K
-    double *he = u + n;                           // [n] H e
-    double *w = he + n;                           // [n] third-derivative contraction
-    double *col = w + n;                          // [n] pivot column
-    double *xp = col + n;                         // [n][KP] powers
-    __shared__ double s_red[AN_THREADS / kWave];
-    __shared__ int s_piv[AN_MAX_N];
-    __shared__ int s_kinv[kWave];
-    __shared__ int s_ip;
-    __shared__ double s_rowbuf[2][AN_THREADS / kWave][kWave];
-    __shared__ double s_cval[2][AN_THREADS / kWave];
-    __shared__ int s_crow[2][AN_THREADS / kWave];
+    const AffineShape sh = affine_shape(n);
+    const int ld = sh.ld, mp = sh.mp;
+    double *S = LDSM ? s_dyn : slots + (size_t)blockIdx.x * sh.L * ld;   // [L][ld]
+    double *e = LDSM ? s_dyn + (size_t)sh.L * ld : s_dyn + AN_BLOCK_DOUBLES;   // [n] unit gradient
+    double *v = e + n;                               // [n] Householder vector
+    double *t = v + n;                               // [n] H v, then K v
+    double *u = t + n;                               // [n] v' K
+    double *he = u + n;                              // [n] H e
+    double *w = he + n;                              // [n] third-derivative contraction
+    double *z = w + n;                               // [n] vectors multiplied by K
+    double *x = z + n;                               // [n + 1] coordinates, 1
+    int *piv = (int *)(x + n + 1);                   // [mp] pivot row of step k
+    int *kinv = piv + mp;                            // [mp] step of pivot row i
+    __shared__ double s_red[NW];
+    __shared__ double s_row[2][PW][NB];
+    __shared__ double s_cval[2][PW];
+    __shared__ int s_crow[2][PW];
     const int tid = threadIdx.x;
-    // matrix loops: rows by wave, columns by lane (no index division)
-    const int ty = tid / kWave, tx = tid % kWave;
-    constexpr int NW = AN_THREADS / kWave;
-    const int64_t pt = blockIdx.x;
+    const int lane = lane_id(), wv = NW == 1 ? 0 : wave_id();
     const int m = n - 1;
-    if (in_lds)
-        for (int i = ty; i < n; i += NW)
-            for (int j = tx; j < n; j += kWave) S[i * ld + j] = Hp[i * n + j];
-    for (int i = tid; i < n; i += AN_THREADS) {
-        const double xi = X[pt * n + i];
-        double p = 1.0;
-        for (int k = 0; k < KP; ++k) {
-            xp[i * KP + k] = p;
-            p = p * xi;
+    for (int64_t pt = blockIdx.x; pt < N; pt += gridDim.x) {
+        __syncthreads();
+        for (int i = tid; i < n; i += NT) {
+            x[i] = X[pt * n + i];
+            e[i] = 0.0;
+            w[i] = he[i] = t[i] = 0.0;
         }
-        e[i] = G[pt * n + i];
-        w[i] = 0.0;
-    }
-    __syncthreads();
-    double part = 0.0;
-    for (int i = tid; i < n; i += AN_THREADS) part += e[i] * e[i];
-    const double gn = sqrt(block_sum_d<AN_THREADS>(part, s_red));
-    const double sgn = e[m] / gn >= 0.0 ? 1.0 : -1.0;
-    for (int i = tid; i < n; i += AN_THREADS) {
-        const double ei = e[i] / gn;
-        v[i] = i == m ? ei + sgn : ei;
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += AN_THREADS) e[i] = e[i] / gn;
-    // H e and H v from the untouched Hessian
-    for (int i = tid; i < n; i += AN_THREADS) {
-        double a = 0.0, b = 0.0;
-        for (int j = 0; j < n; ++j) {
-            const double hij = S[i * ld + j];
-            a += hij * (j == m ? v[j] - sgn : v[j]);
-            b += hij * v[j];
-        }
-        he[i] = a;
-        t[i] = b;
-    }
-    __syncthreads();
-    part = 0.0;
-    for (int i = tid; i < n; i += AN_THREADS) part += v[i] * v[i];
-    const double vv = block_sum_d<AN_THREADS>(part, s_red);
-    part = 0.0;
-    for (int i = tid; i < n; i += AN_THREADS) part += v[i] * t[i];
-    const double vhv = block_sum_d<AN_THREADS>(part, s_red);
-    const double beta = 2.0 / vv;
-    // P H P = H - beta (v t' + t v') + beta^2 (v'Hv) v v', in place; then the
-    // regularized tangent block A in the leading (n-1) x (n-1) corner
-    for (int i = ty; i < n; i += NW)
-        for (int j = tx; j < n; j += kWave) {
-            double b = S[i * ld + j] - beta * (v[i] * t[j] + t[i] * v[j]) + beta * beta * vhv * v[i] * v[j];
-            if (i == j && i < m) b += reg;
-            S[i * ld + j] = b;
-        }
-    __syncthreads();
-    // ---- A^-1 in place: Gauss-Jordan with partial (row) pivoting
-    if (m <= kWave) {
-        // Register-resident for n <= 65: lane tx holds column tx of rows
-        // ty, ty + NW, ... (RPT rows).  Rows are not swapped: each step's
-        // pivot is the unused row with the largest entry in column k (the
-        // smallest row index on ties).  Every wave offers its best row in LDS
-        // (double-buffered by step parity, so one barrier per step), and the
-        // column-k multipliers come from lane k by readlane.  Afterwards the
-        // entry in row i, column j belongs at (kinv[i], piv[j]) of the inverse,
-        // where row i was the pivot of step kinv[i] and piv[j] the pivot row of
-        // step j.
-        constexpr int RPT = kWave / NW;
-        double a[RPT];
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const int i = ty + NW * r;
-            a[r] = (i < m && tx < m) ? S[i * ld + tx] : 0.0;
-        }
-        uint64_t used = 0;
-        for (int k = 0; k < m; ++k) {
-            const int par = k & 1;
-            // this wave's candidate (computed on every lane, lane k's counts)
-            double bv = -1.0;
-            int br = -1;
-#pragma unroll
-            for (int r = 0; r < RPT; ++r) {
-                const int i = ty + NW * r;
-                const double v = fabs(a[r]);
-                if (i < m && !((used >> i) & 1ull) && (br < 0 || v > bv)) {
-                    bv = v;
-                    br = r;
-                }
-            }
-            bv = readlane_d(bv, k);
-            br = __builtin_amdgcn_readlane(br, k);
-            if (br >= 0) {
-                double v = a[0];
-#pragma unroll
-                for (int r = 1; r < RPT; ++r) v = r == br ? a[r] : v;
-                s_rowbuf[par][ty][tx] = v;
-            }
-            if (tx == 0) {
-                s_cval[par][ty] = bv;
-                s_crow[par][ty] = br >= 0 ? ty + NW * br : INT_MAX;
-            }
+        if (tid == 0) x[n] = 1.0;
+        // ---- gradient (into e) and Hessian, term by term: the upper triangle
+        // adds up in LDS (in row blocks where the matrix does not fit), then
+        // both triangles are stored
+        const int rows = LDSM ? n : AN_BLOCK_DOUBLES / (n | 1);
+        const int pitch = LDSM ? ld : (n | 1);
+        for (int r0 = 0; r0 < n; r0 += rows) {
+            const int r1 = r0 + rows < n ? r0 + rows : n;
+            double *A = s_dyn;
+            for (int i = r0 + wv; i < r1; i += NW)
+                for (int j = lane; j < n; j += kWave) A[(i - r0) * pitch + j] = 0.0;
             __syncthreads();
-            double best = -1.0;
-            int ip = INT_MAX, wsel = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const double c = s_cval[par][w];
-                const int ci = s_crow[par][w];
-                if (ci == INT_MAX) continue;
-                if (ip == INT_MAX || c > best || (c == best && ci < ip)) {
-                    best = c;
-                    ip = ci;
-                    wsel = w;
-                }
-            }
-            used |= 1ull << ip;
-            const double pinv = 1.0 / s_rowbuf[par][wsel][k];
-            const double pl = s_rowbuf[par][wsel][tx] * pinv;   // scaled pivot row, column tx
-#pragma unroll
-            for (int r = 0; r < RPT; ++r) {
-                const int i = ty + NW * r;
-                if (i == ip) {
-                    a[r] = tx == k ? pinv : pl;
+            for (int64_t q = tid; q < T; q += NT) {
+                const uint4 f = enc[q];
+                const int d = (int)f.w;
+                const double c = coefs[q];
+                if (d > EV_MAX_DEG) {
+                    set_status(status, POLY_ERR_UNSUPPORTED);
+                } else if (d <= 4) {
+                    const int fi[4] = {(int)(f.x & 0xffu), (int)((f.x >> 8) & 0xffu), (int)((f.x >> 16) & 0xffu),
+                                       (int)(f.x >> 24)};
+                    const double y0 = x[fi[0]], y1 = x[fi[1]], y2 = x[fi[2]], y3 = x[fi[3]];
+                    if (r0 == 0) {
+                        const double c01 = c * y0 * y1, c23 = c * y2 * y3;
+                        if (d > 0) lds_add(&e[fi[0]], y1 * c23);
+                        if (d > 1) lds_add(&e[fi[1]], y0 * c23);
+                        if (d > 2) lds_add(&e[fi[2]], y3 * c01);
+                        if (d > 3) lds_add(&e[fi[3]], y2 * c01);
+                    }
+                    auto pair = [&](int a, int b, double val) {
+                        if (b < d && (LDSM || (fi[a] >= r0 && fi[a] < r1)))
+                            lds_add(&A[(fi[a] - r0) * pitch + fi[b]], fi[a] == fi[b] ? 2.0 * val : val);
+                    };
+                    pair(0, 1, c * (y2 * y3));
+                    pair(0, 2, c * (y1 * y3));
+                    pair(1, 2, c * (y0 * y3));
+                    pair(0, 3, c * (y1 * y2));
+                    pair(1, 3, c * (y0 * y2));
+                    pair(2, 3, c * (y0 * y1));
                 } else {
-                    const double c = readlane_d(a[r], k);
-                    a[r] = tx == k ? -c * pinv : a[r] - c * pl;
-                }
-            }
-            if (tid == 0) {
-                s_piv[k] = ip;
-                s_kinv[ip] = k;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const int i = ty + NW * r;
-            if (i < m && tx < m) S[s_kinv[i] * ld + s_piv[tx]] = a[r];
-        }
-        __syncthreads();
-    } else {
-        // larger n: the matrix stays in LDS, rows swapped, swaps undone after
-        for (int k = 0; k < m; ++k) {
-            if (tid < kWave) {
-                double best = -1.0;
-                int bi = k;
-                for (int i = k + tid; i < m; i += kWave) {
-                    const double a = fabs(S[i * ld + k]);
-                    if (a > best) {
-                        best = a;
-                        bi = i;
+                    int var[EV_MAX_DEG], mul[EV_MAX_DEG];
+                    const int s = term_support(f, d, var, mul);
+                    for (int a = 0; a < s; ++a) {
+                        if (r0 == 0)
+                            lds_add(&e[var[a]], c * (double)mul[a] * power_product(x, var, mul, s, a, -1, -1));
+                        if (var[a] < r0 || var[a] >= r1) continue;
+                        for (int b = a; b < s; ++b) {
+                            const int k = mul[a] * (mul[b] - (a == b));
+                            if (k > 0)
+                                lds_add(&A[(var[a] - r0) * pitch + var[b]],
+                                        c * (double)k * power_product(x, var, mul, s, a, b, -1));
+                        }
                     }
                 }
-    #pragma unroll
-                for (int o = kWave / 2; o > 0; o >>= 1) {
-                    const double ob = __shfl_xor(best, o, kWave);
-                    const int oi = __shfl_xor(bi, o, kWave);
-                    if (ob > best || (ob == best && oi < bi)) {
-                        best = ob;
-                        bi = oi;
-                    }
-                }
-                if (tid == 0) {
-                    s_ip = bi;
-                    s_piv[k] = bi;
-                }
             }
             __syncthreads();
-            const int ip = s_ip;
-            if (ip != k)
-                for (int j = tid; j < m; j += AN_THREADS) {
-                    const double a = S[k * ld + j];
-                    S[k * ld + j] = S[ip * ld + j];
-                    S[ip * ld + j] = a;
-                }
-            __syncthreads();
-            const double pinv = 1.0 / S[k * ld + k];
-            for (int i = tid; i < m; i += AN_THREADS) col[i] = S[i * ld + k];
-            __syncthreads();
-            for (int j = tid; j < m; j += AN_THREADS) S[k * ld + j] = j == k ? pinv : S[k * ld + j] * pinv;
-            __syncthreads();
-            for (int i = ty; i < m; i += NW) {
-                if (i == k) continue;
-                const double ci = col[i];
-                for (int j = tx; j < m; j += kWave)
-                    S[i * ld + j] = j == k ? -ci * pinv : S[i * ld + j] - ci * S[k * ld + j];
-            }
-            __syncthreads();
-        }
-        for (int k = m - 1; k >= 0; --k) {   // undo the row swaps as column swaps, last first
-            const int ip = s_piv[k];
-            if (ip != k)
-                for (int i = tid; i < m; i += AN_THREADS) {
-                    const double a = S[i * ld + k];
-                    S[i * ld + k] = S[i * ld + ip];
-                    S[i * ld + ip] = a;
-                }
-            __syncthreads();
-        }
-    }
-    // ---- M = P K P with K = [A^-1 0; 0 0]
-    for (int i = tid; i < n; i += AN_THREADS) {
-        S[m * ld + i] = 0.0;
-        S[i * ld + m] = 0.0;
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += AN_THREADS) {
-        double kv = 0.0, vk = 0.0;
-        for (int j = 0; j < n; ++j) {
-            kv += S[i * ld + j] * v[j];
-            vk += v[j] * S[j * ld + i];
-        }
-        t[i] = kv;
-        u[i] = vk;
-    }
-    __syncthreads();
-    part = 0.0;
-    for (int i = tid; i < n; i += AN_THREADS) part += v[i] * t[i];
-    const double vkv = block_sum_d<AN_THREADS>(part, s_red);
-    for (int i = ty; i < n; i += NW)
-        for (int j = tx; j < n; j += kWave)
-            S[i * ld + j] = S[i * ld + j] - beta * (t[i] * v[j] + v[i] * u[j]) + beta * beta * vkv * v[i] * v[j];
-    __syncthreads();
-    // ---- w_l = sum_jk M_jk f_jkl(x), term by term
-    for (int64_t q = tid; q < T; q += AN_THREADS) {
-        const uint4 f = enc[q];
-        const int d = (int)f.w;
-        if (d > EV_MAX_DEG) {
-            set_status(status, POLY_ERR_UNSUPPORTED);
-            continue;
-        }
-        if (d < 3) continue;
-        const uint32_t words[3] = {f.x, f.y, f.z};
-        int var[EV_MAX_DEG], mul[EV_MAX_DEG];
-        int s = 0;
-        for (int r = 0; r < d; ++r) {
-            const int vi = (int)((words[r >> 2] >> (8 * (r & 3))) & 0xffu);
-            if (s > 0 && var[s - 1] == vi) {
-                ++mul[s - 1];
+            if (LDSM) {
+                for (int i = wv; i < n; i += NW)
+                    for (int j = lane; j < i; j += kWave) S[i * ld + j] = A[j * pitch + i];
             } else {
-                var[s] = vi;
-                mul[s] = 1;
-                ++s;
+                for (int i = r0 + wv; i < r1; i += NW)
+                    for (int j = i + lane; j < n; j += kWave) S[i * ld + j] = A[(i - r0) * pitch + j];
+                for (int j = r0 + 1 + wv; j < n; j += NW)
+                    for (int i = r0 + lane; i < (j < r1 ? j : r1); i += kWave) S[j * ld + i] = A[(i - r0) * pitch + j];
+            }
+            __syncthreads();
+        }
+        double part = 0.0;
+        for (int i = tid; i < n; i += NT) part += e[i] * e[i];
+        const double gn = sqrt(sum_block<NW>(part, s_red));
+        const double sgn = e[m] / gn >= 0.0 ? 1.0 : -1.0;
+        __syncthreads();
+        for (int i = tid; i < n; i += NT) {
+            const double ei = e[i] / gn;
+            e[i] = ei;
+            v[i] = i == m ? ei + sgn : ei;
+        }
+        __syncthreads();
+        // H e and H v (H is symmetric: columns read along rows)
+        for (int i = lane; i < n; i += kWave) {
+            double a = 0.0, b = 0.0;
+#pragma unroll 4
+            for (int j = wv; j < n; j += NW) {
+                const double hij = S[j * ld + i];
+                a += hij * e[j];
+                b += hij * v[j];
+            }
+            if (NW == 1) {
+                he[i] = a;
+                t[i] = b;
+            } else {
+                lds_add(&he[i], a);
+                lds_add(&t[i], b);
             }
         }
-        const double c = coefs[q];
-        for (int a = 0; a < s; ++a)
-            for (int b = 0; b < s; ++b) {
-                const int kb = mul[b] - (a == b);
-                if (mul[a] <= 0 || kb <= 0) continue;
-                const double mab = S[var[a] * ld + var[b]];
-                for (int l = 0; l < s; ++l) {
-                    const int kl = mul[l] - (a == l) - (b == l);
-                    if (kl <= 0) continue;
-                    double val = c * (double)(mul[a] * kb * kl) * mab;
-                    for (int r = 0; r < s; ++r)
-                        val *= xp[var[r] * KP + (mul[r] - (a == r) - (b == r) - (l == r))];
-                    atomicAdd(&w[var[l]], val);
+        __syncthreads();
+        part = 0.0;
+        double part2 = 0.0;
+        for (int i = tid; i < n; i += NT) {
+            part += v[i] * v[i];
+            part2 += v[i] * t[i];
+        }
+        const double beta = 2.0 / sum_block<NW>(part, s_red);
+        const double bv = beta * beta * sum_block<NW>(part2, s_red);   // beta^2 v'Hv
+        // P H P = H - beta (v t' + t v') + beta^2 (v'Hv) v v', in place: the
+        // regularized tangent block A in the leading m x m corner, padded to a
+        // multiple of 16 by the identity
+        for (int i = wv; i < mp; i += NW)
+            for (int j = lane; j < mp; j += kWave) {
+                double b = i == j ? 1.0 : 0.0;
+                if (i < m && j < m) {
+                    b = S[i * ld + j] - beta * (v[i] * t[j] + t[i] * v[j]) + bv * v[i] * v[j];
+                    if (i == j) b += reg;
+                }
+                S[i * ld + j] = b;
+            }
+        __syncthreads();
+        // ---- A^-1 in place
+        const int row = tid;                        // this lane's panel row
+        bool used = row >= mp;
+        for (int kb = 0; kb < mp; kb += NB) {
+            if (NW == 1 || wv < PW) {
+                double a[NB];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) a[j] = row < mp ? S[row * ld + kb + j] : 0.0;
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    // the unused row with the largest entry in column k (the
+                    // smallest row on ties; NaN last)
+                    const double mag = fabs(a[k]);
+                    const double key = used ? -1.0 : (mag >= 0.0 ? mag : -0.5);
+                    const double best = wave_max_d(key);
+                    const int il = __ffsll((long long)__ballot(key == best)) - 1;
+                    double prow[NB];
+                    int ip = il;
+                    if (NW == 1) {
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) prow[j] = readlane_d(a[j], il);
+                    } else {
+                        const int par = k & 1;
+                        if (lane == il) {
+#pragma unroll
+                            for (int j = 0; j < NB; ++j) s_row[par][wv][j] = a[j];
+                            s_cval[par][wv] = best;
+                            s_crow[par][wv] = row;
+                        }
+                        __syncthreads();
+                        double bb = s_cval[par][0];
+                        int ws = 0;
+#pragma unroll
+                        for (int q = 1; q < PW; ++q) {
+                            const double c = s_cval[par][q];
+                            if (c > bb) {
+                                bb = c;
+                                ws = q;
+                            }
+                        }
+                        ip = s_crow[par][ws];
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) prow[j] = s_row[par][ws][j];
+                    }
+                    const double pinv = 1.0 / prow[k];
+                    const double f = a[k];
+                    const bool mine = row == ip;
+                    a[k] = 0.0;
+                    prow[k] = 1.0;
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        const double pl = prow[j] * pinv;          // scaled pivot row
+                        const double r = a[j] - f * pl;
+                        a[j] = mine ? pl : r;
+                    }
+                    used = used || mine;
+                    if (mine) {
+                        piv[kb + k] = row;
+                        kinv[row] = kb + k;
+                    }
+                }
+                if (row < mp)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) S[row * ld + kb + j] = a[j];
+            } else {
+                for (int k = 0; k < NB; ++k) __syncthreads();
+            }
+            __syncthreads();
+            // pivot rows of the panel: this lane's rows of U, and bit masks
+            int ur[KK];
+#pragma unroll
+            for (int q = 0; q < KK; ++q) ur[q] = piv[kb + 4 * q + (lane >> 4)];
+            unsigned long long pm[PW] = {};
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int p = __builtin_amdgcn_readfirstlane(piv[kb + j]);
+#pragma unroll
+                for (int q = 0; q < PW; ++q) pm[q] |= (p >> 6) == q ? 1ull << (p & 63) : 0ull;
+            }
+            const int ncb = mp >> 4;
+            const int col = lane & 15, lr = lane >> 4;
+            // this wave's units: column blocks (one wave) or halves of them,
+            // their U entries read before any tile is overwritten
+            const int units = NW == 1 ? ncb : 2 * ncb;
+            double bu[MAXU][KK];
+#pragma unroll
+            for (int q = 0; q < MAXU; ++q) {
+                const int un = wv + q * NW;
+                const int cb = NW == 1 ? un : un >> 1;
+#pragma unroll
+                for (int k = 0; k < KK; ++k) bu[q][k] = un < units ? S[ur[k] * ld + cb * 16 + col] : 0.0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < MAXU; ++q) {
+                const int un = wv + q * NW;
+                if (un >= units) break;
+                const int cb = NW == 1 ? un : un >> 1;
+                if (NB == 16 && cb * 16 == kb) continue;
+                const int half = (ncb + 1) >> 1;
+                const int ra = NW == 1 ? 0 : (un & 1) * half;
+                const int rb = NW == 1 ? ncb : ((un & 1) ? ncb : half);
+                // panel columns keep G
+                const bool live = NB == 16 || (unsigned)(cb * 16 + col - kb) >= (unsigned)NB;
+                constexpr int RU = 4;               // tiles in flight
+                for (int rt = ra; rt < rb; rt += RU) {
+                    d4v c[RU];
+                    double ga[RU][KK];
+#pragma unroll
+                    for (int r = 0; r < RU; ++r) {
+                        const int tr = rt + r < rb ? rt + r : rb - 1;
+#pragma unroll
+                        for (int k = 0; k < KK; ++k) ga[r][k] = S[(tr * 16 + col) * ld + kb + 4 * k + lr];
+                        unsigned long long mk = pm[0];
+#pragma unroll
+                        for (int p = 1; p < PW; ++p) mk = (tr >> 2) == p ? pm[p] : mk;
+                        mk >>= (tr & 3) * 16 + lr;
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) {
+                            const double s = S[(tr * 16 + lr + 4 * y) * ld + cb * 16 + col];
+                            c[r][y] = (mk >> (4 * y)) & 1ull ? 0.0 : s;
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < RU; ++r)
+#pragma unroll
+                        for (int k = 0; k < KK; ++k)
+                            c[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[r][k], bu[q][k], c[r], 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < RU; ++r)
+                        if (rt + r < rb && live)
+#pragma unroll
+                            for (int y = 0; y < 4; ++y) S[((rt + r) * 16 + lr + 4 * y) * ld + cb * 16 + col] = c[r][y];
                 }
             }
+            __syncthreads();
+        }
+        // ---- K = A^-1: K_ab = S[piv[a]][kinv[b]] for a, b < m, else 0.
+        // t = K v, u = v' K
+        if (NW > 1)
+            for (int i = tid; i < n; i += NT) t[i] = u[i] = 0.0;
+        __syncthreads();
+        auto kv = [&](const double *y, int q) { return q < m ? y[q] : 0.0; };
+        for (int i = lane; i < n; i += kWave) {
+            double a = 0.0, b = 0.0;
+            if (i < m) {
+                const double *Sr = S + piv[i] * ld;
+                const int ci = kinv[i];
+#pragma unroll 4
+                for (int c = wv; c < mp; c += NW) {
+                    a += Sr[c] * kv(v, piv[c]);
+                    b += kv(v, kinv[c]) * S[c * ld + ci];
+                }
+            }
+            if (NW == 1) {
+                t[i] = a;
+                u[i] = b;
+            } else {
+                lds_add(&t[i], a);
+                lds_add(&u[i], b);
+            }
+        }
+        __syncthreads();
+        part = 0.0;
+        for (int i = tid; i < n; i += NT) part += v[i] * t[i];
+        const double bk = beta * beta * sum_block<NW>(part, s_red);   // beta^2 v'Kv
+        // ---- w_l = sum_jk M_jk f_jkl(x), term by term, M = P K P
+        auto entry = [&](int a, int b) {
+            const double k = a < m && b < m ? S[piv[a] * ld + kinv[b]] : 0.0;
+            return k - beta * (t[a] * v[b] + v[a] * u[b]) + bk * v[a] * v[b];
+        };
+        for (int64_t q = tid; q < T; q += NT) {
+            const uint4 f = enc[q];
+            const int d = (int)f.w;
+            if (d < 3 || d > EV_MAX_DEG) continue;
+            const double c = coefs[q];
+            if (d <= 4) {
+                const int f0 = (int)(f.x & 0xffu), f1 = (int)((f.x >> 8) & 0xffu), f2 = (int)((f.x >> 16) & 0xffu);
+                const double m01 = c * (entry(f0, f1) + entry(f1, f0)), m02 = c * (entry(f0, f2) + entry(f2, f0)),
+                             m12 = c * (entry(f1, f2) + entry(f2, f1));
+                if (d == 3) {
+                    lds_add(&w[f0], m12);
+                    lds_add(&w[f1], m02);
+                    lds_add(&w[f2], m01);
+                } else {
+                    const int f3 = (int)(f.x >> 24);
+                    const double m03 = c * (entry(f0, f3) + entry(f3, f0)), m13 = c * (entry(f1, f3) + entry(f3, f1)),
+                                 m23 = c * (entry(f2, f3) + entry(f3, f2));
+                    const double y0 = x[f0], y1 = x[f1], y2 = x[f2], y3 = x[f3];
+                    lds_add(&w[f0], m12 * y3 + m13 * y2 + m23 * y1);
+                    lds_add(&w[f1], m02 * y3 + m03 * y2 + m23 * y0);
+                    lds_add(&w[f2], m01 * y3 + m03 * y1 + m13 * y0);
+                    lds_add(&w[f3], m01 * y2 + m02 * y1 + m12 * y0);
+                }
+            } else {
+                int var[EV_MAX_DEG], mul[EV_MAX_DEG];
+                const int s = term_support(f, d, var, mul);
+                for (int a = 0; a < s; ++a)
+                    for (int b = 0; b < s; ++b) {
+                        const int kb = mul[b] - (a == b);
+                        if (kb <= 0) continue;
+                        const double mab = entry(var[a], var[b]);
+                        for (int l = 0; l < s; ++l) {
+                            const int kl = mul[l] - (a == l) - (b == l);
+                            if (kl <= 0) continue;
+                            lds_add(&w[var[l]], c * (double)(mul[a] * kb * kl) * mab *
+                                                    power_product(x, var, mul, s, a, b, l));
+                        }
+                    }
+            }
+        }
+        __syncthreads();
+        // ---- nu = P K P (H e - |g| / (n + 1) w) - e
+        const double cg = gn / (double)(n + 1);
+        part = 0.0;
+        for (int i = tid; i < n; i += NT) {
+            const double r = he[i] - cg * w[i];
+            z[i] = r;
+            part += v[i] * r;
+        }
+        const double bz = beta * sum_block<NW>(part, s_red);
+        for (int i = tid; i < n; i += NT) {
+            z[i] -= bz * v[i];
+            t[i] = 0.0;
+        }
+        __syncthreads();
+        for (int i = lane; i < m; i += kWave) {
+            const double *Sr = S + piv[i] * ld;
+            double a = 0.0;
+#pragma unroll 4
+            for (int c = wv; c < mp; c += NW) a += Sr[c] * kv(z, piv[c]);
+            if (NW == 1) t[i] = a;
+            else lds_add(&t[i], a);
+        }
+        __syncthreads();
+        part = 0.0;
+        for (int i = tid; i < n; i += NT) part += v[i] * t[i];
+        const double by = beta * sum_block<NW>(part, s_red);
+        for (int i = tid; i < n; i += NT) D[pt * n + i] = (t[i] - by * v[i]) - e[i];
+        if (gnorm && tid == 0) gnorm[pt] = gn;
     }
-    __syncthreads();
-    // ---- nu = M (H e - |g| / (n + 1) w) - e
-    const double cg = gn / (double)(n + 1);
-    for (int i = tid; i < n; i += AN_THREADS) col[i] = he[i] - cg * w[i];
-    __syncthreads();
-    for (int i = tid; i < n; i += AN_THREADS) {
-        double r = 0.0;
-        for (int j = 0; j < n; ++j) r += S[i * ld + j] * col[j];
-        D[pt * n + i] = r - e[i];
-    }
-    if (gnorm && tid == 0) gnorm[pt] = gn;
 }
+
+template __global__ void k_affine_normal<1, 8, true>(int, const uint4 *, const double *, int64_t, const double *,
+                                                     int64_t, double *, double, double *, double *, int32_t *);
+template __global__ void k_affine_normal<8, 16, true>(int, const uint4 *, const double *, int64_t, const double *,
+                                                      int64_t, double *, double, double *, double *, int32_t *);
+template __global__ void k_affine_normal<8, 16, false>(int, const uint4 *, const double *, int64_t, const double *,
+                                                       int64_t, double *, double, double *, double *, int32_t *);
 
 }  // namespace polyhip

@@ -674,8 +674,10 @@ void ensure_lds_attrs()
                               (int)DV_LDS_MAX);
     (void)hipFuncSetAttribute((const void *)k_mul_buckets_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)MB_LDS_LIMIT);
-    (void)hipFuncSetAttribute((const void *)k_affine_normal, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)affine_lds_bytes(AN_MAX_N_LDS));
+    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 16, true>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N_LDS));
+    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 16, false>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N));
     (void)hipFuncSetAttribute((const void *)k_affine_stochastic, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)AS_LDS_BUDGET);
     lds_attr_done = true;
@@ -2021,22 +2023,23 @@ poly_status poly_hess(const poly_csr *f, const double *X, int64_t N, double *H, 
 
 // ------------------------------------------------------------ affine normal
 
-// The gradient and Hessian paths, then one workgroup per point.
+// Factor lists, then one workgroup per point; matrix slots past AN_MAX_N_LDS.
 struct AffinePlan {
-    GradPlan g;
-    HessPlan h;
-    size_t G, H, enc;
+    size_t enc, slots;
+    int64_t blocks;
 };
 
 static AffinePlan plan_affine(const poly_csr *f, int64_t N, Layout &L)
 {
     AffinePlan a;
-    const int n = f->nvars;
-    a.g = plan_grad(f, N, L);
-    a.h = plan_hess(f, N, L);
-    a.G = L.take(8 * (size_t)N * n);
-    a.H = L.take(8 * (size_t)N * n * n);
+    const AffineShape sh = affine_shape(f->nvars);
     a.enc = L.take(16 * (size_t)std::max<int64_t>(total_terms(f), 1));
+    a.slots = 0;
+    a.blocks = N;
+    if (f->nvars > AN_MAX_N_LDS) {
+        a.blocks = std::min(N, AN_MAX_SLOTS);
+        a.slots = L.take(8 * (size_t)a.blocks * sh.L * sh.ld);
+    }
     return a;
 }
 
@@ -2249,18 +2252,20 @@ poly_status poly_affine_normal(const poly_csr *f, const double *X, int64_t N, do
     }
     const int n = f->nvars;
     const int64_t T = total_terms(f);
-    double *G = at<double>(ws, a.G);
-    double *H = at<double>(ws, a.H);
     uint32_t *enc = at<uint32_t>(ws, a.enc);
-    if ((st = run_grad(f, X, N, G, ws, a.g, s)) != POLY_OK) return st;
-    if ((st = run_hess(f, X, N, H, ws, a.h, s)) != POLY_OK) return st;
     if (T > 0)
         hipLaunchKernelGGL(k_encode_factors, dim3(grid1(T, 256)), dim3(256), 0, s, f->exps, T, n, enc,
                            (const int64_t *)nullptr, (uint32_t *)nullptr);
+    double *slots = n > AN_MAX_N_LDS ? at<double>(ws, a.slots) : nullptr;
     TimedLaunch tl(POLY_TIMING_AFFINE, s);
-    hipLaunchKernelGGL(k_affine_normal, dim3((unsigned)N), dim3(AN_THREADS), affine_lds_bytes(n), s, n,
-                       (const uint4 *)enc, f->coefs, T, X, (const double *)G, H, reg, D, gnorm,
-                       status);
+    auto launch = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(a.blocks, INT32_MAX)), dim3(waves * kWave),
+                           affine_lds_bytes(n), s, n, (const uint4 *)enc, f->coefs, T, X, N, slots, reg, D, gnorm,
+                           status);
+    };
+    if (n <= AN_WAVE_N) launch(k_affine_normal<1, 8, true>, 1);
+    else if (n <= AN_MAX_N_LDS) launch(k_affine_normal<AN_WAVES, 16, true>, AN_WAVES);
+    else launch(k_affine_normal<AN_WAVES, 16, false>, AN_WAVES);
     tl.done(s);
     LAUNCH_CHECK();
     return POLY_OK;

@@ -237,18 +237,38 @@ __global__ void k_ws_rowptr(int64_t P, uint64_t span, const uint64_t *keys, int6
                             const int64_t *seg_count, const int64_t *out_off, int64_t nb, const uint64_t *st_ckey,
                             int64_t *row_ptr);
 
-// affine-normal direction (affine.hip): one workgroup per point
-constexpr int AN_THREADS = 256;
+// affine-normal direction (affine.hip): one workgroup per point.  One wave for
+// n <= AN_WAVE_N (a tangent block of at most 64 rows: one row per lane), else
+// AN_WAVES; the matrix in LDS for n <= AN_MAX_N_LDS, else in one of at most
+// AN_MAX_SLOTS workspace slots, each kept by one workgroup.
 constexpr int AN_MAX_N = 255;       // every nvars the batches allow
-constexpr int AN_MAX_N_LDS = 128;   // largest n whose n x (n+1) matrix is kept in LDS
+constexpr int AN_WAVE_N = 65;
+constexpr int AN_MAX_N_LDS = 129;
+constexpr int AN_WAVES = 8;
+constexpr int AN_BLOCK_DOUBLES = 12288;   // LDS for a row block of H where the matrix is in a slot
+constexpr int64_t AN_MAX_SLOTS = 1024;
+struct AffineShape {
+    int mp;   // rows of the tangent block, n - 1, up to a multiple of 16
+    int L;    // rows of the work matrix (it holds H, then the padded tangent block)
+    int ld;   // its row stride (odd in LDS)
+};
+__host__ __device__ constexpr AffineShape affine_shape(int n)
+{
+    AffineShape s{(n + 14) / 16 * 16, 0, 0};
+    s.L = n > s.mp ? n : s.mp;
+    s.ld = n <= AN_MAX_N_LDS ? (s.L | 1) : s.L;
+    return s;
+}
 __host__ __device__ constexpr size_t affine_lds_bytes(int n)
 {
-    return ((n <= AN_MAX_N_LDS ? (size_t)n * (n + 1) : 0) + 8 * (size_t)n + (size_t)n * (EV_MAX_DEG + 1)) *
-           sizeof(double);
+    const AffineShape s = affine_shape(n);
+    return ((n <= AN_MAX_N_LDS ? (size_t)s.L * s.ld : (size_t)AN_BLOCK_DOUBLES) + 8 * (size_t)n + 1) * sizeof(double) +
+           2 * (size_t)s.mp * sizeof(int);
 }
-__global__ void k_affine_normal(int n, const uint4 *enc, const double *coefs, int64_t T, const double *X,
-                                const double *G, double *H, double reg, double *D, double *gnorm,
-                                int32_t *status);
+template <int NW, int NB, bool LDSM>
+__global__ void k_affine_normal(int n, const uint4 *__restrict__ enc, const double *__restrict__ coefs, int64_t T,
+                                const double *__restrict__ X, int64_t N, double *slots, double reg, double *D,
+                                double *gnorm, int32_t *status);
 // affine-normal direction, stochastic route (stochastic.hip): one workgroup
 // per point, probes solved AS slots at a time
 constexpr int AS_THREADS = 256;
