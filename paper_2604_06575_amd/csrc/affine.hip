@@ -25,7 +25,7 @@
 // n = 64, 4,096 points, most of it in 29 small launches.)  A is inverted in
 // place by a blocked Gauss-Jordan elimination with partial pivoting:
 //   * a panel of NB columns is eliminated with one row per lane in registers,
-//     the pivot row broadcast by readlane (one wave) or through LDS (several);
+//     the pivot row broadcast by readlane (one panel wave) or through LDS (several);
 //     rows are not swapped, the pivots' permutation is applied when the
 //     inverse is read;
 //   * the panel then holds D = (pivot block)^-1 in the pivot rows and -A D in
@@ -33,9 +33,10 @@
 //     A <- mask A + G U, with U the pivot rows' old entries and the mask
 //     dropping them: a product of depth NB on v_mfma_f64_16x16x4f64.
 // The matrix lives in LDS up to n = AN_MAX_N_LDS and in the workgroup's slot
-// of the workspace beyond.  n <= AN_WAVE_N takes one wave per point (no
-// barrier waits, four points per CU, so that one point's panel runs beside
-// another's MFMAs), larger n eight waves.  Bound by the panels' serial chain:
+// of the workspace beyond.  n <= AN_WAVE_N takes four waves per point, one of
+// which holds the whole panel (no barrier within it), and four points per CU,
+// so that one point's panel runs beside another's MFMAs; larger n eight waves,
+// four of them for the panel.  Bound by the panels' serial chain:
 // a pivot search, a reciprocal and a row update per column.
 // n = 64, 320 terms, 4,096 points: AFF64.  n = 160, 800 terms, 256 points:
 // AFF160.
@@ -84,7 +85,6 @@ template <int NW>
 __device__ inline double sum_block(double v, double *red)
 {
     v = wave_sum(v);
-    if (NW == 1) return v;
     if (lane_id() == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double t = 0.0;
@@ -99,44 +99,31 @@ __device__ inline void lds_add(double *p, double v)
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// distinct variables and exponents of a factor list (ascending variables)
-__device__ inline int term_support(const uint4 &f, int d, int *var, int *mul)
+// factor r of a list, and the product of a list's d factors but for three
+__device__ inline int factor(const uint4 &f, int r)
 {
-    const uint32_t words[3] = {f.x, f.y, f.z};
-    int s = 0;
-    for (int r = 0; r < d; ++r) {
-        const int vi = (int)((words[r >> 2] >> (8 * (r & 3))) & 0xffu);
-        if (s > 0 && var[s - 1] == vi) {
-            ++mul[s - 1];
-        } else {
-            var[s] = vi;
-            mul[s] = 1;
-            ++s;
-        }
-    }
-    return s;
+    const uint32_t w = r < 4 ? f.x : (r < 8 ? f.y : f.z);
+    return (int)((w >> (8 * (r & 3))) & 0xffu);
 }
 
-__device__ inline double power_product(const double *x, const int *var, const int *mul, int s, int a, int b, int l)
+__device__ inline double product_but(const uint4 &f, int d, const double *x, int a, int b, int l)
 {
     double val = 1.0;
-    for (int r = 0; r < s; ++r)
-        for (int q = mul[r] - (a == r) - (b == r) - (l == r); q > 0; --q) val *= x[var[r]];
+    for (int r = 0; r < d; ++r) val *= r == a || r == b || r == l ? 1.0 : x[factor(f, r)];
     return val;
 }
 
 }  // namespace
 
-template <int NW, int NB, bool LDSM>
-__global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const uint4 *__restrict__ enc,
+template <int NW, int PW, int NB, bool LDSM>
+__global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(int n, const uint4 *__restrict__ enc,
                                                               const double *__restrict__ coefs, int64_t T,
                                                               const double *__restrict__ X, int64_t N, double *slots,
                                                               double reg, double *D, double *gnorm, int32_t *status)
 {
     constexpr int NT = NW * kWave;
     constexpr int KK = NB / 4;                       // MFMAs per tile and panel
-    constexpr int PW = NW == 1 ? 1 : 4;              // waves that hold panel rows
-    constexpr int MAXU = 4;                          // column blocks (one wave) or half blocks per wave
+    constexpr int MAXU = PW == 1 ? 2 : 4;            // half column blocks per wave (at most PW * 4 blocks)
     extern __shared__ double s_dyn[];
     const AffineShape sh = affine_shape(n);
     const int ld = sh.ld, mp = sh.mp;
@@ -156,7 +143,10 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
     __shared__ double s_cval[2][PW];
     __shared__ int s_crow[2][PW];
     const int tid = threadIdx.x;
-    const int lane = lane_id(), wv = NW == 1 ? 0 : wave_id();
+    const int lane = lane_id(), wv = wave_id();
+    // the panel wave where there is one: workgroups that share a CU (numbers
+    // 256 apart at first) put theirs on different SIMDs
+    const int pw = (int)(blockIdx.x >> 8) % NW;
     const int m = n - 1;
     for (int64_t pt = blockIdx.x; pt < N; pt += gridDim.x) {
         __syncthreads();
@@ -205,17 +195,14 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                     pair(1, 3, c * (y0 * y2));
                     pair(2, 3, c * (y0 * y1));
                 } else {
-                    int var[EV_MAX_DEG], mul[EV_MAX_DEG];
-                    const int s = term_support(f, d, var, mul);
-                    for (int a = 0; a < s; ++a) {
-                        if (r0 == 0)
-                            lds_add(&e[var[a]], c * (double)mul[a] * power_product(x, var, mul, s, a, -1, -1));
-                        if (var[a] < r0 || var[a] >= r1) continue;
-                        for (int b = a; b < s; ++b) {
-                            const int k = mul[a] * (mul[b] - (a == b));
-                            if (k > 0)
-                                lds_add(&A[(var[a] - r0) * pitch + var[b]],
-                                        c * (double)k * power_product(x, var, mul, s, a, b, -1));
+                    for (int a = 0; a < d; ++a) {
+                        const int fa = factor(f, a);
+                        if (r0 == 0) lds_add(&e[fa], c * product_but(f, d, x, a, a, a));
+                        if (fa < r0 || fa >= r1) continue;
+                        for (int b = a + 1; b < d; ++b) {
+                            const int fb = factor(f, b);
+                            const double val = c * product_but(f, d, x, a, b, b);
+                            lds_add(&A[(fa - r0) * pitch + fb], fa == fb ? 2.0 * val : val);
                         }
                     }
                 }
@@ -252,13 +239,8 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                 a += hij * e[j];
                 b += hij * v[j];
             }
-            if (NW == 1) {
-                he[i] = a;
-                t[i] = b;
-            } else {
-                lds_add(&he[i], a);
-                lds_add(&t[i], b);
-            }
+            lds_add(&he[i], a);
+            lds_add(&t[i], b);
         }
         __syncthreads();
         part = 0.0;
@@ -272,21 +254,33 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
         // P H P = H - beta (v t' + t v') + beta^2 (v'Hv) v v', in place: the
         // regularized tangent block A in the leading m x m corner, padded to a
         // multiple of 16 by the identity
-        for (int i = wv; i < mp; i += NW)
-            for (int j = lane; j < mp; j += kWave) {
-                double b = i == j ? 1.0 : 0.0;
-                if (i < m && j < m) {
-                    b = S[i * ld + j] - beta * (v[i] * t[j] + t[i] * v[j]) + bv * v[i] * v[j];
-                    if (i == j) b += reg;
+        for (int j = lane; j < mp; j += kWave) {
+            const double vj = j < m ? v[j] : 0.0, tj = j < m ? t[j] : 0.0;
+            constexpr int UN = 4;                   // rows in flight
+            for (int i0 = wv * UN; i0 < mp; i0 += NW * UN) {   // mp is a multiple of UN
+                double h[UN], vi[UN], ti[UN];
+#pragma unroll
+                for (int r = 0; r < UN; ++r) {
+                    const int i = i0 + r < n ? i0 + r : n - 1;
+                    h[r] = S[(i0 + r) * ld + j];
+                    vi[r] = v[i];
+                    ti[r] = t[i];
                 }
-                S[i * ld + j] = b;
+#pragma unroll
+                for (int r = 0; r < UN; ++r) {
+                    const int i = i0 + r;
+                    double b = h[r] - beta * (vi[r] * tj + ti[r] * vj) + bv * vi[r] * vj;
+                    if (i == j) b += reg;
+                    S[i * ld + j] = i < m && j < m ? b : (i == j ? 1.0 : 0.0);
+                }
             }
+        }
         __syncthreads();
         // ---- A^-1 in place
-        const int row = tid;                        // this lane's panel row
+        const int row = PW == 1 ? lane : tid;       // this lane's panel row
         bool used = row >= mp;
         for (int kb = 0; kb < mp; kb += NB) {
-            if (NW == 1 || wv < PW) {
+            if (PW == 1 ? wv == pw : wv < PW) {
                 double a[NB];
 #pragma unroll
                 for (int j = 0; j < NB; ++j) a[j] = row < mp ? S[row * ld + kb + j] : 0.0;
@@ -300,7 +294,7 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                     const int il = __ffsll((long long)__ballot(key == best)) - 1;
                     double prow[NB];
                     int ip = il;
-                    if (NW == 1) {
+                    if (PW == 1) {
 #pragma unroll
                         for (int j = 0; j < NB; ++j) prow[j] = readlane_d(a[j], il);
                     } else {
@@ -327,26 +321,22 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                         for (int j = 0; j < NB; ++j) prow[j] = s_row[par][ws][j];
                     }
                     const double pinv = 1.0 / prow[k];
-                    const double f = a[k];
-                    const bool mine = row == ip;
-                    a[k] = 0.0;
-                    prow[k] = 1.0;
+                    if (row == ip) {   // the pivot row, scaled; its column holds the reciprocal
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        const double pl = prow[j] * pinv;          // scaled pivot row
-                        const double r = a[j] - f * pl;
-                        a[j] = mine ? pl : r;
-                    }
-                    used = used || mine;
-                    if (mine) {
+                        for (int j = 0; j < NB; ++j) a[j] = j == k ? pinv : a[j] * pinv;
+                        used = true;
                         piv[kb + k] = row;
                         kinv[row] = kb + k;
+                    } else {
+                        const double g = a[k] * pinv;
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) a[j] = j == k ? -g : a[j] - g * prow[j];
                     }
                 }
                 if (row < mp)
 #pragma unroll
                     for (int j = 0; j < NB; ++j) S[row * ld + kb + j] = a[j];
-            } else {
+            } else if (PW > 1) {
                 for (int k = 0; k < NB; ++k) __syncthreads();
             }
             __syncthreads();
@@ -363,14 +353,14 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
             }
             const int ncb = mp >> 4;
             const int col = lane & 15, lr = lane >> 4;
-            // this wave's units: column blocks (one wave) or halves of them,
-            // their U entries read before any tile is overwritten
-            const int units = NW == 1 ? ncb : 2 * ncb;
+            // this wave's units: halves of column blocks, their U entries read
+            // before any tile is overwritten
+            const int units = 2 * ncb;
             double bu[MAXU][KK];
 #pragma unroll
             for (int q = 0; q < MAXU; ++q) {
                 const int un = wv + q * NW;
-                const int cb = NW == 1 ? un : un >> 1;
+                const int cb = un >> 1;
 #pragma unroll
                 for (int k = 0; k < KK; ++k) bu[q][k] = un < units ? S[ur[k] * ld + cb * 16 + col] : 0.0;
             }
@@ -379,14 +369,14 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
             for (int q = 0; q < MAXU; ++q) {
                 const int un = wv + q * NW;
                 if (un >= units) break;
-                const int cb = NW == 1 ? un : un >> 1;
+                const int cb = un >> 1;
                 if (NB == 16 && cb * 16 == kb) continue;
                 const int half = (ncb + 1) >> 1;
-                const int ra = NW == 1 ? 0 : (un & 1) * half;
-                const int rb = NW == 1 ? ncb : ((un & 1) ? ncb : half);
+                const int ra = (un & 1) * half;
+                const int rb = (un & 1) ? ncb : half;
                 // panel columns keep G
                 const bool live = NB == 16 || (unsigned)(cb * 16 + col - kb) >= (unsigned)NB;
-                constexpr int RU = 4;               // tiles in flight
+                constexpr int RU = LDSM ? 2 : 4;    // tiles in flight
                 for (int rt = ra; rt < rb; rt += RU) {
                     d4v c[RU];
                     double ga[RU][KK];
@@ -406,9 +396,9 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                         }
                     }
 #pragma unroll
-                    for (int r = 0; r < RU; ++r)
+                    for (int k = 0; k < KK; ++k)
 #pragma unroll
-                        for (int k = 0; k < KK; ++k)
+                        for (int r = 0; r < RU; ++r)
                             c[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[r][k], bu[q][k], c[r], 0, 0, 0);
 #pragma unroll
                     for (int r = 0; r < RU; ++r)
@@ -421,8 +411,7 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
         }
         // ---- K = A^-1: K_ab = S[piv[a]][kinv[b]] for a, b < m, else 0.
         // t = K v, u = v' K
-        if (NW > 1)
-            for (int i = tid; i < n; i += NT) t[i] = u[i] = 0.0;
+        for (int i = tid; i < n; i += NT) t[i] = u[i] = 0.0;
         __syncthreads();
         auto kv = [&](const double *y, int q) { return q < m ? y[q] : 0.0; };
         for (int i = lane; i < n; i += kWave) {
@@ -436,13 +425,8 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                     b += kv(v, kinv[c]) * S[c * ld + ci];
                 }
             }
-            if (NW == 1) {
-                t[i] = a;
-                u[i] = b;
-            } else {
-                lds_add(&t[i], a);
-                lds_add(&u[i], b);
-            }
+            lds_add(&t[i], a);
+            lds_add(&u[i], b);
         }
         __syncthreads();
         part = 0.0;
@@ -477,19 +461,12 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
                     lds_add(&w[f3], m01 * y2 + m02 * y1 + m12 * y0);
                 }
             } else {
-                int var[EV_MAX_DEG], mul[EV_MAX_DEG];
-                const int s = term_support(f, d, var, mul);
-                for (int a = 0; a < s; ++a)
-                    for (int b = 0; b < s; ++b) {
-                        const int kb = mul[b] - (a == b);
-                        if (kb <= 0) continue;
-                        const double mab = entry(var[a], var[b]);
-                        for (int l = 0; l < s; ++l) {
-                            const int kl = mul[l] - (a == l) - (b == l);
-                            if (kl <= 0) continue;
-                            lds_add(&w[var[l]], c * (double)(mul[a] * kb * kl) * mab *
-                                                    power_product(x, var, mul, s, a, b, l));
-                        }
+                for (int a = 0; a < d; ++a)
+                    for (int b = a + 1; b < d; ++b) {
+                        const int fa = factor(f, a), fb = factor(f, b);
+                        const double mab = c * (entry(fa, fb) + entry(fb, fa));
+                        for (int l = 0; l < d; ++l)
+                            if (l != a && l != b) lds_add(&w[factor(f, l)], mab * product_but(f, d, x, a, b, l));
                     }
             }
         }
@@ -513,8 +490,7 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
             double a = 0.0;
 #pragma unroll 4
             for (int c = wv; c < mp; c += NW) a += Sr[c] * kv(z, piv[c]);
-            if (NW == 1) t[i] = a;
-            else lds_add(&t[i], a);
+            lds_add(&t[i], a);
         }
         __syncthreads();
         part = 0.0;
@@ -525,11 +501,11 @@ __global__ void __launch_bounds__(NW * kWave, 2) k_affine_normal(int n, const ui
     }
 }
 
-template __global__ void k_affine_normal<1, 8, true>(int, const uint4 *, const double *, int64_t, const double *,
+template __global__ void k_affine_normal<4, 1, 8, true>(int, const uint4 *, const double *, int64_t, const double *,
                                                      int64_t, double *, double, double *, double *, int32_t *);
-template __global__ void k_affine_normal<8, 16, true>(int, const uint4 *, const double *, int64_t, const double *,
+template __global__ void k_affine_normal<8, 4, 16, true>(int, const uint4 *, const double *, int64_t, const double *,
                                                       int64_t, double *, double, double *, double *, int32_t *);
-template __global__ void k_affine_normal<8, 16, false>(int, const uint4 *, const double *, int64_t, const double *,
+template __global__ void k_affine_normal<8, 4, 16, false>(int, const uint4 *, const double *, int64_t, const double *,
                                                        int64_t, double *, double, double *, double *, int32_t *);
 
 }  // namespace polyhip

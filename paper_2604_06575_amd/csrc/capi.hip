@@ -674,9 +674,9 @@ void ensure_lds_attrs()
                               (int)DV_LDS_MAX);
     (void)hipFuncSetAttribute((const void *)k_mul_buckets_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)MB_LDS_LIMIT);
-    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 16, true>,
+    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 4, 16, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N_LDS));
-    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 16, false>,
+    (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 4, 16, false>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N));
     (void)hipFuncSetAttribute((const void *)k_affine_stochastic, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)AS_LDS_BUDGET);
@@ -2263,9 +2263,9 @@ poly_status poly_affine_normal(const poly_csr *f, const double *X, int64_t N, do
                            affine_lds_bytes(n), s, n, (const uint4 *)enc, f->coefs, T, X, N, slots, reg, D, gnorm,
                            status);
     };
-    if (n <= AN_WAVE_N) launch(k_affine_normal<1, 8, true>, 1);
-    else if (n <= AN_MAX_N_LDS) launch(k_affine_normal<AN_WAVES, 16, true>, AN_WAVES);
-    else launch(k_affine_normal<AN_WAVES, 16, false>, AN_WAVES);
+    if (n <= AN_WAVE_N) launch(k_affine_normal<4, 1, 8, true>, 4);
+    else if (n <= AN_MAX_N_LDS) launch(k_affine_normal<AN_WAVES, 4, 16, true>, AN_WAVES);
+    else launch(k_affine_normal<AN_WAVES, 4, 16, false>, AN_WAVES);
     tl.done(s);
     LAUNCH_CHECK();
     return POLY_OK;

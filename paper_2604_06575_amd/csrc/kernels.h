@@ -237,9 +237,9 @@ __global__ void k_ws_rowptr(int64_t P, uint64_t span, const uint64_t *keys, int6
                             const int64_t *seg_count, const int64_t *out_off, int64_t nb, const uint64_t *st_ckey,
                             int64_t *row_ptr);
 
-// affine-normal direction (affine.hip): one workgroup per point.  One wave for
-// n <= AN_WAVE_N (a tangent block of at most 64 rows: one row per lane), else
-// AN_WAVES; the matrix in LDS for n <= AN_MAX_N_LDS, else in one of at most
+// affine-normal direction (affine.hip): one workgroup per point, of four waves
+// for n <= AN_WAVE_N (a tangent block of at most 64 rows: one row per lane of
+// one wave), else AN_WAVES; the matrix in LDS for n <= AN_MAX_N_LDS, else in one of at most
 // AN_MAX_SLOTS workspace slots, each kept by one workgroup.
 constexpr int AN_MAX_N = 255;       // every nvars the batches allow
 constexpr int AN_WAVE_N = 65;
@@ -265,7 +265,7 @@ __host__ __device__ constexpr size_t affine_lds_bytes(int n)
     return ((n <= AN_MAX_N_LDS ? (size_t)s.L * s.ld : (size_t)AN_BLOCK_DOUBLES) + 8 * (size_t)n + 1) * sizeof(double) +
            2 * (size_t)s.mp * sizeof(int);
 }
-template <int NW, int NB, bool LDSM>
+template <int NW, int PW, int NB, bool LDSM>
 __global__ void k_affine_normal(int n, const uint4 *__restrict__ enc, const double *__restrict__ coefs, int64_t T,
                                 const double *__restrict__ X, int64_t N, double *slots, double reg, double *D,
                                 double *gnorm, int32_t *status);
