@@ -136,6 +136,22 @@ def lib():
         f = getattr(L, name)
         f.argtypes = args
         f.restype = res
+    # entry points of this binding with C++ linkage (not part of the C ABI):
+    # products with bounds on the operands' total degrees
+    inner = {
+        "max_degrees": ("PK8poly_csrS2_PiPvmS4_", [pcsr, pcsr, ctypes.POINTER(i32), P, ctypes.c_size_t, P]),
+        "mul_bounded_workspace": ("PK8poly_csrS2_iiPmPl", [pcsr, pcsr, i32, i32, psz, ctypes.POINTER(i64)]),
+        "mul_bounded": ("PK8poly_csrS2_iiPS0_dPvmS4_", [pcsr, pcsr, i32, i32, pcsr, d, P, ctypes.c_size_t, P]),
+        "mtimes_bounded_workspace": ("PK8poly_csrS2_llliiPmPl",
+                                     [pcsr, pcsr, i64, i64, i64, i32, i32, psz, ctypes.POINTER(i64)]),
+        "mtimes_bounded": ("PK8poly_csrS2_llliiPS0_dPvmS4_",
+                           [pcsr, pcsr, i64, i64, i64, i32, i32, pcsr, d, P, ctypes.c_size_t, P]),
+    }
+    for name, (signature, args) in inner.items():
+        f = getattr(L, f"_ZN7polyhip{len(name)}{name}E{signature}")
+        f.argtypes = args
+        f.restype = i32
+        setattr(L, name, f)
     _lib = L
     _load_tuning(L)
     return L
@@ -409,19 +425,38 @@ def mul_workspace(a: Batch, b: Batch) -> tuple[int, int]:
     return int(ws_bytes.value), int(raw.value)
 
 
+def _product_degrees(ca: PolyCSR, cb: PolyCSR, n: int, raw: int, finish: bool, device) -> tuple[int, int]:
+    """Total degrees of both operands, read back from the device, for a call
+    that waits for its result anyway and whose product can be formed on a
+    dense range of monomials; (-1, -1) otherwise."""
+    if not finish or n > 16 or raw < 65536:
+        return -1, -1
+    deg = (ctypes.c_int32 * 2)()
+    ws = _workspace(256, device)
+    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb), deg, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+                                  _stream()), "max_degrees")
+    return int(deg[0]), int(deg[1])
+
+
 def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | None = None,
         out: Batch | None = None, finish: bool = True) -> Batch:
     """Entrywise simplify(a_p .* b_p)."""
     L = lib()
     ca, cb = a.csr(), b.csr()
     ws_bytes, raw = mul_workspace(a, b)
+    da, db = _product_degrees(ca, cb, a.n, raw, finish, a.coefs.device)
+    if da >= 0:
+        need, r = ctypes.c_size_t(), ctypes.c_int64()
+        _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(need),
+                                            ctypes.byref(r)), "poly_mul_workspace")
+        ws_bytes = int(need.value)
     if ws is None or ws.numel() < ws_bytes:
         ws = _workspace(ws_bytes, a.coefs.device)
     if out is None:
         out = _empty_out(a.n, a.npolys, raw, a.max_exp + b.max_exp, a.coefs.device)
     cout = out.csr()
-    _check(L.poly_mul(ctypes.byref(ca), ctypes.byref(cb), ctypes.byref(cout), float(tol),
-                      ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mul")
+    _check(L.mul_bounded(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(cout), float(tol),
+                              ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mul")
     if not finish:
         return out
     return _finish(out, ws, "poly_mul", trim)
@@ -440,13 +475,20 @@ def mtimes(a: Batch, b: Batch, I: int, K: int, J: int, tol: float = 0.0, trim: b
     """Matrix product of polynomial matrices: a is I x K, b is K x J, both
     with entries in row-major order; returns the I x J product."""
     L = lib()
+    ca, cb = a.csr(), b.csr()
     ws_bytes, raw = mtimes_workspace(a, b, I, K, J)
+    da, db = _product_degrees(ca, cb, a.n, raw, finish, a.coefs.device)
+    if da >= 0:
+        need, r = ctypes.c_size_t(), ctypes.c_int64()
+        _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db,
+                                               ctypes.byref(need), ctypes.byref(r)), "poly_mtimes_workspace")
+        ws_bytes = int(need.value)
     if ws is None or ws.numel() < ws_bytes:
         ws = _workspace(ws_bytes, a.coefs.device)
     if out is None:
         out = _empty_out(a.n, I * J, raw, a.max_exp + b.max_exp, a.coefs.device)
-    _check(L.poly_mtimes(ctypes.byref(a.csr()), ctypes.byref(b.csr()), I, K, J, ctypes.byref(out.csr()),
-                         float(tol), ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mtimes")
+    _check(L.mtimes_bounded(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(out.csr()),
+                                 float(tol), ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mtimes")
     if not finish:
         return out
     return _finish(out, ws, "poly_mtimes", trim)

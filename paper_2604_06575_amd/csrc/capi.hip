@@ -678,6 +678,11 @@ void ensure_lds_attrs()
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N_LDS));
     (void)hipFuncSetAttribute((const void *)k_affine_normal<AN_WAVES, 4, 16, false>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)affine_lds_bytes(AN_MAX_N));
+    for (const void *k : {(const void *)k_md_range<512, MD_ITEMS, 1>, (const void *)k_md_range<512, MD_ITEMS, 2>,
+                          (const void *)k_md_range<256, MD_ITEMS, 1>, (const void *)k_md_range<256, MD_ITEMS, 2>,
+                          (const void *)k_md_range<64, MD_ITEMS, 1>, (const void *)k_md_range<64, MD_ITEMS, 2>})
+        (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MD_LDS_MAX);
+    (void)hipFuncSetAttribute((const void *)k_md_cut, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     (void)hipFuncSetAttribute((const void *)k_affine_stochastic, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)AS_LDS_BUDGET);
     lds_attr_done = true;
@@ -1392,6 +1397,173 @@ static poly_status run_mul_rows(const poly_csr *a, const poly_csr *b, poly_csr *
     R.exps = re;
     R.coefs = rc;
     return run_simplify(&R, out, zero_tol, ws, m.sp, s);
+}
+
+}  // namespace
+
+namespace {
+
+// Products on a dense range of monomials (muldense.hip): `entries` output
+// entries of K products each (J > 0: a matrix product with J columns; J = 0:
+// entrywise, K = 1), operands of total degree at most da and db.
+struct MulDensePlan {
+    bool on = false, kb_lds = false;
+    int D = 0, threads = 0;
+    uint64_t radix = 0;
+    int64_t entries = 0, K = 1, J = 0, nr = 0, ranges = 0, max_partners = 0;
+    uint32_t cells = 0, cpr = 0;
+    size_t lds = 0;
+    size_t ka, wa, kb, wb, kb_s, wb_s, cb_s, table, pairs, bounds, cut, count, out_off, tmp, st_cell, st_coef, total;
+};
+
+// The route is taken where it can be (few variables, keys of 63 bits, cell
+// numbers of 31, an entry's rows in LDS) and where an output entry is dense
+// enough: every cell is cleared, scanned and unpacked whether or not a product
+// falls on it, which costs about an eighth of a raw product's own work.
+static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t I, int64_t K, int64_t J, int da, int db,
+                            int64_t raw)
+{
+    MulDensePlan m;
+    const int n = a->nvars;
+    if (da < 0 || db < 0 || da + db > 255 || n > MD_MAX_N || raw < 4096 || raw >= (int64_t(1) << 32)) return m;
+    m.D = da + db;
+    m.radix = (uint64_t)a->max_exp + (uint64_t)b->max_exp + 1;
+    unsigned __int128 span = 1, cells = 1;
+    for (int i = 0; i < n; ++i) {
+        span *= m.radix;
+        cells = cells * (unsigned)(m.D + i + 1) / (unsigned)(i + 1);   // C(D + i + 1, i + 1), exact
+        if (span > ((unsigned __int128)1 << 63) || cells >= ((unsigned __int128)1 << 31)) return m;
+    }
+    m.entries = J ? I * J : I;
+    m.K = K;
+    m.J = J;
+    if ((double)m.entries * (double)cells > 8.0 * (double)raw) return m;
+    m.max_partners = max_segment(b->row_ptr_host, b->npolys);
+    const size_t pairs = (size_t)((n + 1) / 2) * (m.D + 1) * (m.D + 1);
+    if (m.max_partners > 16384 || 4 * pairs > MD_TABLE_MAX) return m;
+    m.cells = (uint32_t)cells;
+    // Workgroup size and cells per range.  A range's chunk (4 raw products per
+    // thread) should be no longer than the range is wide.  Every range looks at
+    // all rows of its entry, so ranges are as narrow (and so as many, and their
+    // workgroups as small and free of barriers) as keeps that below the raw
+    // products' own number.
+    const int64_t total = m.entries * (int64_t)m.cells;
+    const int64_t left_rows = total_terms(a) * (J ? J : 1);
+    for (int threads : {64, 256, 512}) {
+        const int64_t widest = threads == 512 ? 4096 : threads * MD_ITEMS;
+        // about 2,048 one-wave workgroups' worth of ranges, none below a
+        // sixteenth of the widest
+        const int64_t want = ceil_div(total * (threads / 64), (int64_t)2048);
+        const int64_t cpr = std::min<int64_t>(std::max(widest / 16, std::min(widest, want)), (int64_t)m.cells);
+        m.threads = threads;
+        m.cpr = (uint32_t)cpr;
+        if (ceil_div(m.cells, cpr) * left_rows <= raw) break;
+    }
+    m.nr = ceil_div(m.cells, (int64_t)m.cpr);
+    m.ranges = m.entries * m.nr;
+    m.kb_lds = b->npolys == 1;   // at most 128 KB
+    m.lds = 12 * (size_t)m.cpr + 4 * pairs + 10 * (size_t)m.threads * MD_STEP_ROWS + 16;
+    if (m.lds > MD_LDS_MAX || m.ranges >= (int64_t(1) << 31) || m.ranges * (int64_t)m.cpr > (int64_t(1) << 30) ||
+        left_rows * (m.nr + 1) > (int64_t(1) << 31) || (J > 65535))
+        return m;
+    const int64_t Ta = total_terms(a), Tb = total_terms(b);
+    Layout L;
+    m.ka = L.take(8 * Ta);
+    m.wa = L.take(16 * Ta);
+    m.kb = L.take(8 * Tb);
+    m.wb = L.take(16 * Tb);
+    m.kb_s = L.take(8 * Tb);
+    m.wb_s = L.take(16 * Tb);
+    m.cb_s = L.take(8 * Tb);
+    m.table = L.take(4 * (size_t)n * (m.D + 2));
+    m.pairs = L.take(4 * pairs);
+    m.bounds = L.take(8 * (m.nr + 1));
+    m.cut = L.take(2 * (size_t)left_rows * (m.nr + 1));
+    m.count = L.take(8 * m.ranges);
+    m.out_off = L.take(8 * (m.ranges + 1));
+    m.tmp = L.take(8 * scan_tmp_count(m.ranges));
+    m.st_cell = L.take(4 * (size_t)m.ranges * m.cpr);
+    m.st_coef = L.take(8 * (size_t)m.ranges * m.cpr);
+    m.total = L.total();
+    m.on = true;
+    return m;
+}
+
+static poly_status run_mul_dense(const MulDensePlan &m, const poly_csr *a, const poly_csr *b, int da, int db, poly_csr *out,
+                          double zero_tol, void *ws, hipStream_t s)
+{
+    ensure_lds_attrs();
+    const int n = a->nvars;
+    const int64_t Ta = total_terms(a), Tb = total_terms(b);
+    MulDenseArgs A;
+    A.n = n;
+    A.D = m.D;
+    A.radix = m.radix;
+    A.cells = m.cells;
+    A.cpr = m.cpr;
+    A.nr = m.nr;
+    A.K = m.K;
+    A.J = m.J;
+    A.Ta = Ta;
+    A.cut = at<uint16_t>(ws, m.cut);
+    A.max_partners = m.max_partners;
+    A.kb_lds = m.kb_lds;
+    A.pairs = at<uint32_t>(ws, m.pairs);
+    A.bounds = at<uint64_t>(ws, m.bounds);
+    A.a_rp = a->row_ptr;
+    A.b_rp = b->row_ptr;
+    A.ka = at<uint64_t>(ws, m.ka);
+    A.wa = at<uint64_t>(ws, m.wa);
+    A.ca = a->coefs;
+    A.kb_s = at<uint64_t>(ws, m.kb_s);
+    A.wb_s = at<uint64_t>(ws, m.wb_s);
+    A.cb_s = at<double>(ws, m.cb_s);
+    A.table = at<uint32_t>(ws, m.table);
+    A.st_cell = at<uint32_t>(ws, m.st_cell);
+    A.st_coef = at<double>(ws, m.st_coef);
+    A.count = at<int64_t>(ws, m.count);
+    A.tol = zero_tol;
+    A.status = at<int32_t>(ws, 0);
+    uint64_t *kb = at<uint64_t>(ws, m.kb), *wb = at<uint64_t>(ws, m.wb);
+    hipLaunchKernelGGL(k_md_prep, dim3(grid1(Ta + Tb, 256)), dim3(256), 0, s, A, a->exps, Ta, a->max_exp, da, b->exps,
+                       Tb, b->max_exp, db, (uint64_t *)A.ka, (uint64_t *)A.wa, kb, wb, (uint32_t *)A.table,
+                       (uint32_t *)A.pairs);
+    const int64_t sort_blocks = ceil_div(Tb, (int64_t)16);
+    hipLaunchKernelGGL(k_md_sort, dim3((unsigned)(sort_blocks + ceil_div(m.nr + 1, (int64_t)256))), dim3(256), 0, s, A,
+                       b->row_ptr, b->npolys, Tb, (const uint64_t *)kb, (const uint64_t *)wb, b->coefs,
+                       (uint64_t *)A.kb_s, (uint64_t *)A.wb_s, (double *)A.cb_s, sort_blocks, (uint64_t *)A.bounds);
+    {
+        // stretches of bounds: about 1,024 blocks in all
+        const int64_t gx = ceil_div(Ta, (int64_t)32), gy = m.J ? m.J : 1, tiles = ceil_div(m.nr + 1, (int64_t)64);
+        const int64_t gz = std::min<int64_t>(tiles, std::max<int64_t>(1, 1024 / (gx * gy)));
+        const int64_t stretch = ceil_div(tiles, gz) * 64;
+        hipLaunchKernelGGL(k_md_cut, dim3((unsigned)gx, (unsigned)gy, (unsigned)ceil_div(m.nr + 1, stretch)), dim3(256),
+                           m.kb_lds ? 8 * (size_t)m.max_partners : 0, s, A, a->npolys, Ta, stretch,
+                           at<uint16_t>(ws, m.cut));
+    }
+    {
+        TimedLaunch tl(POLY_TIMING_MUL, s);
+        auto range = [&](auto threads) {
+            constexpr int NT = decltype(threads)::value;
+            if (n > 8)
+                hipLaunchKernelGGL((k_md_range<NT, MD_ITEMS, 2>), dim3((unsigned)m.ranges), dim3(NT), m.lds, s, A);
+            else
+                hipLaunchKernelGGL((k_md_range<NT, MD_ITEMS, 1>), dim3((unsigned)m.ranges), dim3(NT), m.lds, s, A);
+        };
+        if (m.threads == 64) range(std::integral_constant<int, 64>());
+        else if (m.threads == 256) range(std::integral_constant<int, 256>());
+        else range(std::integral_constant<int, 512>());
+        tl.done(s);
+    }
+    int64_t *out_off = at<int64_t>(ws, m.out_off);
+    launch_scan(A.count, m.ranges, out_off, at<int64_t>(ws, m.tmp), A.status, s);
+    const int64_t units = m.ranges * ceil_div((int64_t)m.cpr, (int64_t)256);
+    const unsigned ugrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(units, 4), (int64_t)device_cus() * 16));
+    hipLaunchKernelGGL(k_md_unpack, dim3(ugrid), dim3(256), 4 * (size_t)n * (m.D + 2) + (size_t)256 * n, s, A,
+                       (const int64_t *)out_off, m.ranges, m.entries, out->exps, out->coefs, out->capacity,
+                       out->row_ptr);
+    LAUNCH_CHECK();
+    return POLY_OK;
 }
 
 }  // namespace
@@ -2603,6 +2775,109 @@ poly_status poly_eval_backward2(const poly_csr *f, const double *X, int64_t N, c
 // the device wrote, and evaluation units skip what lies past it.
 
 }  // extern "C"
+
+// ------------------------------------------ entry points of the binding only
+//
+// C++ linkage, not part of the C ABI: products and simplify with bounds on the
+// operands' total degrees, which a caller that waits for its result can read
+// back first.
+
+namespace polyhip {
+
+// Largest total degree of a's and (b not null) b's terms, into degrees[0] and
+// degrees[1] on the host: launches, copies and waits for the stream, so it may
+// not be called under capture.  ws: at least kWsHeadBytes.
+poly_status max_degrees(const poly_csr *a, const poly_csr *b, int32_t *degrees, void *ws, size_t ws_bytes,
+                             void *stream)
+{
+    poly_status st = check_csr(a, true);
+    if (st != POLY_OK) return st;
+    if (b && (st = check_csr(b, true)) != POLY_OK) return st;
+    if (!degrees || (b && b->nvars != a->nvars)) return POLY_ERR_ARG;
+    if (!ws || ws_bytes < kWsHeadBytes) return POLY_ERR_WORKSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    uint32_t *deg = at<uint32_t>(ws, 0);
+    clear_u64(at<unsigned long long>(ws, 0), 1, s);
+    const int64_t Ta = total_terms(a), Tb = b ? total_terms(b) : 0;
+    if (Ta + Tb > 0)
+        hipLaunchKernelGGL(k_max_degree, dim3((unsigned)std::min<int64_t>(ceil_div(Ta + Tb, 256), 2048)), dim3(256), 0,
+                           s, a->exps, Ta, b ? b->exps : nullptr, Tb, (int)a->nvars, deg);
+    LAUNCH_CHECK();
+    uint32_t host[2];
+    if (hipMemcpyAsync(host, deg, sizeof host, hipMemcpyDeviceToHost, s) != hipSuccess) return POLY_ERR_HIP;
+    if (hipStreamSynchronize(s) != hipSuccess) return POLY_ERR_HIP;
+    degrees[0] = (int32_t)host[0];
+    degrees[1] = (int32_t)host[1];
+    return POLY_OK;
+}
+
+// poly_mul with bounds on the operands' total degrees (negative: not known,
+// the same as poly_mul).  The result is poly_mul's, bit for bit; where the
+// product is dense enough (plan_mul_dense) it is formed range by range on
+// chip.  A term above its bound is a device status POLY_ERR_EXPONENT.
+poly_status mul_bounded_workspace(const poly_csr *a, const poly_csr *b, int32_t deg_a, int32_t deg_b,
+                                       size_t *ws_bytes, int64_t *raw_terms)
+{
+    size_t bytes = 0;
+    int64_t raw = 0;
+    poly_status st = poly_mul_workspace(a, b, &bytes, &raw);
+    if (st != POLY_OK) return st;
+    const MulDensePlan d = plan_mul_dense(a, b, a->npolys, 1, 0, deg_a, deg_b, raw);
+    if (ws_bytes) *ws_bytes = d.on ? d.total : bytes;
+    if (raw_terms) *raw_terms = raw;
+    return POLY_OK;
+}
+
+poly_status mul_bounded(const poly_csr *a, const poly_csr *b, int32_t deg_a, int32_t deg_b, poly_csr *out,
+                             double zero_tol, void *ws, size_t ws_bytes, void *stream)
+{
+    int64_t raw = 0;
+    poly_status st = poly_mul_workspace(a, b, nullptr, &raw);
+    if (st != POLY_OK) return st;
+    const MulDensePlan d = plan_mul_dense(a, b, a->npolys, 1, 0, deg_a, deg_b, raw);
+    if (!d.on) return poly_mul(a, b, out, zero_tol, ws, ws_bytes, stream);
+    if ((st = check_csr(out, false)) != POLY_OK) return st;
+    if (out->nvars != a->nvars || out->npolys != a->npolys) return POLY_ERR_ARG;
+    if (!(zero_tol >= 0.0)) return POLY_ERR_ARG;
+    if (a->max_exp + b->max_exp > 255) return POLY_ERR_UNSUPPORTED;
+    if (!ws || ws_bytes < d.total) return POLY_ERR_WORKSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    clear_u64(at<unsigned long long>(ws, 0), 1, s);
+    return run_mul_dense(d, a, b, deg_a, deg_b, out, zero_tol, ws, s);
+}
+
+// poly_mtimes with bounds on the operands' total degrees, as mul_bounded.
+poly_status mtimes_bounded_workspace(const poly_csr *A, const poly_csr *B, int64_t I, int64_t K, int64_t J,
+                                          int32_t deg_a, int32_t deg_b, size_t *ws_bytes, int64_t *raw_terms)
+{
+    if (!ws_bytes || !raw_terms) return POLY_ERR_ARG;
+    poly_status st = poly_mtimes_workspace(A, B, I, K, J, ws_bytes, raw_terms);
+    if (st != POLY_OK || I <= 0 || K <= 0 || J <= 0) return st;
+    const MulDensePlan d = plan_mul_dense(A, B, I, K, J, deg_a, deg_b, *raw_terms);
+    if (d.on) *ws_bytes = d.total;
+    return POLY_OK;
+}
+
+poly_status mtimes_bounded(const poly_csr *A, const poly_csr *B, int64_t I, int64_t K, int64_t J, int32_t deg_a,
+                                int32_t deg_b, poly_csr *out, double zero_tol, void *ws, size_t ws_bytes, void *stream)
+{
+    size_t bytes = 0;
+    int64_t raw = 0;
+    poly_status st = poly_mtimes_workspace(A, B, I, K, J, &bytes, &raw);
+    if (st != POLY_OK) return st;
+    MulDensePlan d;
+    if (I > 0 && K > 0 && J > 0) d = plan_mul_dense(A, B, I, K, J, deg_a, deg_b, raw);
+    if (!d.on) return poly_mtimes(A, B, I, K, J, out, zero_tol, ws, ws_bytes, stream);
+    if ((st = check_csr(out, false)) != POLY_OK) return st;
+    if (out->nvars != A->nvars || out->npolys != I * J || out->max_exp < A->max_exp + B->max_exp) return POLY_ERR_ARG;
+    if (!(zero_tol >= 0.0)) return POLY_ERR_ARG;
+    if (!ws || ws_bytes < d.total) return POLY_ERR_WORKSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    clear_u64(at<unsigned long long>(ws, 0), 1, s);
+    return run_mul_dense(d, A, B, deg_a, deg_b, out, zero_tol, ws, s);
+}
+
+}  // namespace polyhip
 
 struct poly_plan {
     hipGraph_t graph = nullptr;

@@ -120,6 +120,50 @@ __global__ void k_mul_sorted_coefs(const int64_t *rp, const uint32_t *perm, cons
 __global__ void k_mul_rowptr(const int64_t *out_off, const int64_t *pb_start, int64_t P, int64_t *out_rp,
                              int64_t nbuckets);
 
+// products on a dense range of monomials (muldense.hip)
+constexpr int MD_MAX_N = 16;            // pair words: two of four 16-bit pairs
+constexpr int MD_ITEMS = 4;             // raw products per thread and chunk
+constexpr int MD_STEP_ROWS = 4;         // rows per thread and step
+constexpr size_t MD_TABLE_MAX = 32 * 1024;   // LDS of the pair tables
+constexpr size_t MD_LDS_MAX = 156 * 1024;
+struct MulDenseArgs {
+    int n, D;                   // variables, degree bound of the product
+    uint64_t radix;             // of the keys
+    uint32_t cells;             // C(n + D, n)
+    uint32_t cpr;               // cells per range
+    int64_t nr;                 // ranges per output entry
+    int64_t K, J;               // mtimes: inner and column counts; entrywise: 1, 0
+    int64_t Ta;                 // left terms
+    int64_t max_partners;       // longest right polynomial
+    int kb_lds;                 // k_md_cut keeps its keys in LDS (one right polynomial)
+    const int64_t *a_rp, *b_rp;
+    const uint64_t *ka, *wa;    // left terms in storage order: keys, pair words [2]
+    const double *ca;
+    const uint64_t *kb_s, *wb_s;   // right terms in key order
+    const double *cb_s;
+    const uint32_t *table;      // [n][D + 2]
+    const uint32_t *pairs;      // [(n + 1) / 2][(D + 1)^2]
+    const uint64_t *bounds;     // [nr + 1] first key of each range of an entry
+    const uint16_t *cut;        // partners below each bound, per entry [nr + 1][rows]
+    uint32_t *st_cell;          // [ranges][cpr] kept cells, their sums and their count
+    double *st_coef;
+    int64_t *count;
+    double tol;
+    int32_t *status;
+};
+__global__ void k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb, int n, uint32_t *deg);
+__global__ void k_md_prep(MulDenseArgs A, const uint8_t *ea, int64_t Ta, int amax, int adeg, const uint8_t *eb,
+                          int64_t Tb, int bmax, int bdeg, uint64_t *ka, uint64_t *wa, uint64_t *kb, uint64_t *wb,
+                          uint32_t *table, uint32_t *pairs);
+__global__ void k_md_sort(MulDenseArgs A, const int64_t *rp, int64_t P, int64_t T, const uint64_t *k,
+                          const uint64_t *w, const double *c, uint64_t *ks, uint64_t *ws, double *cs,
+                          int64_t sort_blocks, uint64_t *bounds);
+__global__ void k_md_cut(MulDenseArgs A, int64_t P, int64_t Ta, int64_t stretch, uint16_t *cut);
+template <int NT, int IT, int NWORD>
+__global__ void k_md_range(MulDenseArgs A);
+__global__ void k_md_unpack(MulDenseArgs A, const int64_t *out_off, int64_t ranges, int64_t entries,
+                            uint8_t *out_exps, double *out_coefs, int64_t capacity, int64_t *row_ptr);
+
 // Host-side measurement hook (poly_timing_*): records HIP events on the
 // launch stream around a kernel when timing is enabled.
 struct TimedLaunch {
