@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -139,7 +140,8 @@ def lib():
     # entry points of this binding with C++ linkage (not part of the C ABI):
     # products with bounds on the operands' total degrees
     inner = {
-        "max_degrees": ("PK8poly_csrS2_PiPvmS4_", [pcsr, pcsr, ctypes.POINTER(i32), P, ctypes.c_size_t, P]),
+        "max_degrees": ("PK8poly_csrS2_PvPlS3_", [pcsr, pcsr, P, P, P]),
+        "read_back": ("PKvPKllPlPv", [P, P, i64, P, P]),
         "mul_bounded_workspace": ("PK8poly_csrS2_iiPmPl", [pcsr, pcsr, i32, i32, psz, ctypes.POINTER(i64)]),
         "mul_bounded": ("PK8poly_csrS2_iiPS0_dPvmS4_", [pcsr, pcsr, i32, i32, pcsr, d, P, ctypes.c_size_t, P]),
         "mtimes_bounded_workspace": ("PK8poly_csrS2_llliiPmPl",
@@ -306,11 +308,35 @@ def _empty_out(n: int, P: int, cap: int, max_exp: int, device) -> Batch:
                  torch.empty(max(cap, 1), dtype=torch.float64, device=device))
 
 
+def _result(n: int, P: int, cap: int, max_exp: int, device) -> Batch:
+    """As _empty_out, for a call that writes the whole row pointer."""
+    return Batch(n, max_exp, torch.empty(P + 1, dtype=torch.int64, device=device), np.zeros(P + 1, np.int64),
+                 torch.empty((max(cap, 1), n), dtype=torch.uint8, device=device),
+                 torch.empty(max(cap, 1), dtype=torch.float64, device=device))
+
+
+_host = threading.local()
+_HOST_WORDS = 8192
+
+
+def _host_words(count: int) -> np.ndarray:
+    """`count` int64 words of pinned host memory that kernels write and this
+    thread reads once it has waited for them: one buffer per thread, given
+    back with it, or one of its own for a longer row pointer."""
+    if count > _HOST_WORDS:
+        return torch.empty(count, dtype=torch.int64, pin_memory=True).numpy()
+    words = getattr(_host, "words", None)
+    if words is None:
+        words = _host.words = torch.empty(_HOST_WORDS, dtype=torch.int64, pin_memory=True).numpy()
+    return words
+
+
 def _finish(out: Batch, ws: torch.Tensor, where: str, trim: bool) -> Batch:
-    """Read back the device row pointer (one sync) and the device status."""
-    st = lib().poly_read_status(ctypes.c_void_p(ws.data_ptr()), _stream())
-    _check(st, where)
-    out.row_ptr_host = out.row_ptr.cpu().numpy()
+    """Read back the device row pointer and the device status (one wait)."""
+    count = out.row_ptr.numel()
+    words = _host_words(count + 1)
+    _check(lib().read_back(ws.data_ptr(), out.row_ptr.data_ptr(), count, words.ctypes.data, _stream()), where)
+    out.row_ptr_host = words[1:count + 1].copy()
     if trim:
         T = out.nterms
         out.exps = out.exps[:T]
@@ -334,11 +360,12 @@ def simplify(b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | N
     capture); the output row pointer stays on the device."""
     L = lib()
     cin = b.csr()
-    need = simplify_workspace(b)
-    if ws is None or ws.numel() < need:
-        ws = _workspace(need, b.coefs.device)
+    need = ctypes.c_size_t()
+    _check(L.poly_simplify_workspace(ctypes.byref(cin), ctypes.byref(need)), "poly_simplify_workspace")
+    if ws is None or ws.numel() < need.value:
+        ws = _workspace(need.value, b.coefs.device)
     if out is None:
-        out = _empty_out(b.n, b.npolys, b.nterms, b.max_exp, b.coefs.device)
+        out = _result(b.n, b.npolys, b.nterms, b.max_exp, b.coefs.device)
     cout = out.csr()
     _check(L.poly_simplify(ctypes.byref(cin), ctypes.byref(cout), float(tol), ctypes.c_void_p(ws.data_ptr()),
                            ws.numel(), _stream()), "poly_simplify")
@@ -425,17 +452,17 @@ def mul_workspace(a: Batch, b: Batch) -> tuple[int, int]:
     return int(ws_bytes.value), int(raw.value)
 
 
-def _product_degrees(ca: PolyCSR, cb: PolyCSR, n: int, raw: int, finish: bool, device) -> tuple[int, int]:
+def _product_degrees(ca: PolyCSR, cb: PolyCSR, raw: int, finish: bool, scratch: torch.Tensor) -> tuple[int, int]:
     """Total degrees of both operands, read back from the device, for a call
     that waits for its result anyway and whose product can be formed on a
-    dense range of monomials; (-1, -1) otherwise."""
-    if not finish or n > 16 or raw < 65536:
+    dense range of monomials; (-1, -1) otherwise.  scratch: two words or more
+    on the device, free until the call's kernels run."""
+    if not finish or ca.nvars > 16 or raw < 4096:
         return -1, -1
-    deg = (ctypes.c_int32 * 2)()
-    ws = _workspace(256, device)
-    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb), deg, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
-                                  _stream()), "max_degrees")
-    return int(deg[0]), int(deg[1])
+    words = _host_words(2)
+    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb), scratch.data_ptr(), words.ctypes.data, _stream()),
+           "max_degrees")
+    return int(words[0]), int(words[1])
 
 
 def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | None = None,
@@ -443,20 +470,21 @@ def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tenso
     """Entrywise simplify(a_p .* b_p)."""
     L = lib()
     ca, cb = a.csr(), b.csr()
-    ws_bytes, raw = mul_workspace(a, b)
-    da, db = _product_degrees(ca, cb, a.n, raw, finish, a.coefs.device)
-    if da >= 0:
-        need, r = ctypes.c_size_t(), ctypes.c_int64()
-        _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(need),
-                                            ctypes.byref(r)), "poly_mul_workspace")
-        ws_bytes = int(need.value)
-    if ws is None or ws.numel() < ws_bytes:
-        ws = _workspace(ws_bytes, a.coefs.device)
+    dev = a.coefs.device
+    ws_bytes, raw = ctypes.c_size_t(), ctypes.c_int64()
+    _check(L.poly_mul_workspace(ctypes.byref(ca), ctypes.byref(cb), ctypes.byref(ws_bytes), ctypes.byref(raw)),
+           "poly_mul_workspace")
     if out is None:
-        out = _empty_out(a.n, a.npolys, raw, a.max_exp + b.max_exp, a.coefs.device)
+        out = _result(a.n, a.npolys, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
+    da, db = _product_degrees(ca, cb, raw.value, finish, out.row_ptr)
+    if da >= 0:
+        _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(ws_bytes),
+                                       ctypes.byref(raw)), "poly_mul_workspace")
+    if ws is None or ws.numel() < ws_bytes.value:
+        ws = _workspace(ws_bytes.value, dev)
     _check(L.mul_bounded(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(cout), float(tol),
-                              ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mul")
+                         ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mul")
     if not finish:
         return out
     return _finish(out, ws, "poly_mul", trim)
@@ -476,19 +504,21 @@ def mtimes(a: Batch, b: Batch, I: int, K: int, J: int, tol: float = 0.0, trim: b
     with entries in row-major order; returns the I x J product."""
     L = lib()
     ca, cb = a.csr(), b.csr()
-    ws_bytes, raw = mtimes_workspace(a, b, I, K, J)
-    da, db = _product_degrees(ca, cb, a.n, raw, finish, a.coefs.device)
-    if da >= 0:
-        need, r = ctypes.c_size_t(), ctypes.c_int64()
-        _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db,
-                                               ctypes.byref(need), ctypes.byref(r)), "poly_mtimes_workspace")
-        ws_bytes = int(need.value)
-    if ws is None or ws.numel() < ws_bytes:
-        ws = _workspace(ws_bytes, a.coefs.device)
+    dev = a.coefs.device
+    ws_bytes, raw = ctypes.c_size_t(), ctypes.c_int64()
+    _check(L.poly_mtimes_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, ctypes.byref(ws_bytes),
+                                   ctypes.byref(raw)), "poly_mtimes_workspace")
     if out is None:
-        out = _empty_out(a.n, I * J, raw, a.max_exp + b.max_exp, a.coefs.device)
-    _check(L.mtimes_bounded(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(out.csr()),
-                                 float(tol), ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mtimes")
+        out = _result(a.n, I * J, raw.value, a.max_exp + b.max_exp, dev)
+    cout = out.csr()
+    da, db = _product_degrees(ca, cb, raw.value, finish, out.row_ptr)
+    if da >= 0:
+        _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(ws_bytes),
+                                          ctypes.byref(raw)), "poly_mtimes_workspace")
+    if ws is None or ws.numel() < ws_bytes.value:
+        ws = _workspace(ws_bytes.value, dev)
+    _check(L.mtimes_bounded(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(cout), float(tol),
+                            ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mtimes")
     if not finish:
         return out
     return _finish(out, ws, "poly_mtimes", trim)

@@ -2784,31 +2784,39 @@ poly_status poly_eval_backward2(const poly_csr *f, const double *X, int64_t N, c
 
 namespace polyhip {
 
-// Largest total degree of a's and (b not null) b's terms, into degrees[0] and
-// degrees[1] on the host: launches, copies and waits for the stream, so it may
-// not be called under capture.  ws: at least kWsHeadBytes.
-poly_status max_degrees(const poly_csr *a, const poly_csr *b, int32_t *degrees, void *ws, size_t ws_bytes,
-                             void *stream)
+// Largest total degree of a's and (b not null) b's terms, into host[0] and
+// host[1]: launches and waits for the stream, so it may not be called under
+// capture.  scratch: 16 bytes of device memory; host: memory that the device
+// can write.
+poly_status max_degrees(const poly_csr *a, const poly_csr *b, void *scratch, int64_t *host, void *stream)
 {
     poly_status st = check_csr(a, true);
     if (st != POLY_OK) return st;
     if (b && (st = check_csr(b, true)) != POLY_OK) return st;
-    if (!degrees || (b && b->nvars != a->nvars)) return POLY_ERR_ARG;
-    if (!ws || ws_bytes < kWsHeadBytes) return POLY_ERR_WORKSPACE;
+    if (!scratch || !host || (b && b->nvars != a->nvars)) return POLY_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    uint32_t *deg = at<uint32_t>(ws, 0);
-    clear_u64(at<unsigned long long>(ws, 0), 1, s);
     const int64_t Ta = total_terms(a), Tb = b ? total_terms(b) : 0;
-    if (Ta + Tb > 0)
-        hipLaunchKernelGGL(k_max_degree, dim3((unsigned)std::min<int64_t>(ceil_div(Ta + Tb, 256), 2048)), dim3(256), 0,
-                           s, a->exps, Ta, b ? b->exps : nullptr, Tb, (int)a->nvars, deg);
+    // one block takes eight terms per thread in about the time of a launch
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ceil_div(Ta + Tb, 8192), 512));
+    if (blocks > 1) clear_u64((unsigned long long *)scratch, 2, s);
+    hipLaunchKernelGGL(k_max_degree, dim3((unsigned)blocks), dim3(1024), 0, s, a->exps, Ta, b ? b->exps : nullptr, Tb,
+                       (int)a->nvars, (uint32_t *)scratch, host);
     LAUNCH_CHECK();
-    uint32_t host[2];
-    if (hipMemcpyAsync(host, deg, sizeof host, hipMemcpyDeviceToHost, s) != hipSuccess) return POLY_ERR_HIP;
+    return hipStreamSynchronize(s) == hipSuccess ? POLY_OK : POLY_ERR_HIP;
+}
+
+// The device status of a finished call (poly_read_status) and its row pointer
+// of `count` entries, into host[1 .. count] (memory that the device can
+// write), with one wait for the stream.
+poly_status read_back(const void *ws, const int64_t *row_ptr, int64_t count, int64_t *host, void *stream)
+{
+    if (!ws || !row_ptr || !host || count < 0) return POLY_ERR_ARG;
+    hipStream_t s = (hipStream_t)stream;
+    hipLaunchKernelGGL(k_read_back, dim3(grid1(std::max<int64_t>(count, 1), 256)), dim3(256), 0, s,
+                       (const int32_t *)ws, row_ptr, count, host);
+    LAUNCH_CHECK();
     if (hipStreamSynchronize(s) != hipSuccess) return POLY_ERR_HIP;
-    degrees[0] = (int32_t)host[0];
-    degrees[1] = (int32_t)host[1];
-    return POLY_OK;
+    return (poly_status)(int32_t)host[0];
 }
 
 // poly_mul with bounds on the operands' total degrees (negative: not known,

@@ -151,7 +151,9 @@ struct MulDenseArgs {
     double tol;
     int32_t *status;
 };
-__global__ void k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb, int n, uint32_t *deg);
+__global__ void k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb, int n, uint32_t *deg,
+                             int64_t *host);
+__global__ void k_read_back(const int32_t *status, const int64_t *row_ptr, int64_t count, int64_t *host);
 __global__ void k_md_prep(MulDenseArgs A, const uint8_t *ea, int64_t Ta, int amax, int adeg, const uint8_t *eb,
                           int64_t Tb, int bmax, int bdeg, uint64_t *ka, uint64_t *wa, uint64_t *kb, uint64_t *wb,
                           uint32_t *table, uint32_t *pairs);

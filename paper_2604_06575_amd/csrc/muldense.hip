@@ -29,9 +29,9 @@
 // Bound by instruction issue and LDS latency, not by memory: the raw product
 // stays on chip.  5,000 x 5,000 terms in
 // 10 variables (25 million raw products, 5.3 million cells): k_md_range 331 us
-// (75 G raw products/s), k_md_cut 71, the whole call 0.64 ms with read-backs;
+// (75 G raw products/s), k_md_cut 71, the whole call 0.58 ms with read-backs;
 // the radix sort of the raw product's 41-bit keys took 1.36 ms.  600 pairs of
-// 6 to 300 terms in 8 variables: 77 + 31 us, the call 0.35 against 0.98 ms.
+// 6 to 300 terms in 8 variables: 77 + 31 us, the call 0.26 against 0.98 ms.
 // Ordering each chunk by an LDS counting sort instead of claims: 592 us.
 #include "kernels.h"
 
@@ -53,13 +53,16 @@ __device__ inline uint32_t monomials_below(int m, int d)
 
 }  // namespace
 
-// Largest total degree of the rows of two batches, into deg[0] and deg[1]
-// (zero before the launch).
-__global__ void __launch_bounds__(256) k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb,
-                                                    int n, uint32_t *deg)
+// Largest total degree of the rows of two batches, into host[0] and host[1]
+// (host memory that the device can write).  One block writes them itself;
+// several meet in deg[0..2] (zero before the launch: two maxima and a count of
+// finished blocks), and the last one writes them.
+__global__ void __launch_bounds__(1024) k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb,
+                                                     int n, uint32_t *deg, int64_t *host)
 {
+    __shared__ uint32_t s_m[2][16];
     uint32_t m[2] = {0, 0};
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < Ta + Tb; t += (int64_t)gridDim.x * 256) {
+    for (int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x; t < Ta + Tb; t += (int64_t)gridDim.x * 1024) {
         const bool second = t >= Ta;
         const uint8_t *row = second ? eb + (t - Ta) * n : ea + t * n;
         uint32_t d = 0;
@@ -83,9 +86,34 @@ __global__ void __launch_bounds__(256) k_max_degree(const uint8_t *ea, int64_t T
             const uint32_t y = (uint32_t)__shfl_xor((int)v, o, kWave);
             v = y > v ? y : v;
         }
-        if (lane_id() == 0 && v > __hip_atomic_load(deg + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(deg + k, v);
+        if (lane_id() == 0) s_m[k][threadIdx.x >> 6] = v;
     }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint32_t v[2] = {0, 0};
+    for (int k = 0; k < 2; ++k)
+        for (int w = 0; w < 16; ++w) v[k] = s_m[k][w] > v[k] ? s_m[k][w] : v[k];
+    if (gridDim.x > 1) {
+        atomicMax(deg, v[0]);
+        atomicMax(deg + 1, v[1]);
+        __threadfence();
+        if (atomicAdd(deg + 2, 1u) + 1 != gridDim.x) return;
+        __threadfence();
+        v[0] = __hip_atomic_load(deg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[1] = __hip_atomic_load(deg + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    host[0] = v[0];
+    host[1] = v[1];
+}
+
+// The status word and a row pointer for the host: one launch that writes to
+// host memory instead of two copies, each with its own wait.
+__global__ void __launch_bounds__(256) k_read_back(const int32_t *status, const int64_t *row_ptr, int64_t count,
+                                                   int64_t *host)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) host[0] = *status;
+    if (i < count) host[1 + i] = row_ptr[i];
 }
 
 // Keys and pair words of both operands' terms, and the rank tables:
