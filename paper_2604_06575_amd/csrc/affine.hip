@@ -38,8 +38,8 @@
 // so that one point's panel runs beside another's MFMAs; larger n eight waves,
 // four of them for the panel.  Bound by the panels' serial chain:
 // a pivot search, a reciprocal and a row update per column.
-// n = 64, 320 terms, 4,096 points: AFF64.  n = 160, 800 terms, 256 points:
-// AFF160.
+// n = 64, 320 terms, 4,096 points: 1,050 us as the kernels before it, 288 us.
+// n = 160, 800 terms, 256 points: 7,060 us, 473 us.
 #include <limits.h>
 
 #include "kernels.h"

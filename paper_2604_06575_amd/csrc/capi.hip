@@ -11,7 +11,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "kernels.h"
+#include "regeval.h"
 
 using namespace polyhip;
 
@@ -549,21 +549,63 @@ inline int64_t eval_segments(int64_t Q, int64_t N, int64_t T)
 
 inline size_t eval_partial_bytes(int64_t Q, int64_t N, int64_t S) { return S > 1 ? (size_t)(8 * S * Q * N) : 0; }
 
-void launch_eval_blocks(const EvalArgs &A, const uint32_t *enc, double *partial, int64_t S, hipStream_t s)
+// Factor lists of at most T terms for the evaluation kernels: 16 bytes per
+// term, and for n <= RE_MAX_N two planes of register words, 4 bytes per term.
+inline int64_t word_plane(int64_t T) { return T + RE_WORD_PAD; }
+inline size_t factor_bytes(int n, int64_t T) { return 16 * (size_t)T + (n <= RE_MAX_N ? 8 * word_plane(T) : 0); }
+inline uint32_t *factor_words(uint32_t *enc, int n, int64_t T) { return n <= RE_MAX_N ? enc + 4 * T : nullptr; }
+
+template <class F>
+void with_regeval_rows(int n, F f)
+{
+    switch (regeval_rows(n)) {
+    case 24: f(std::integral_constant<int, 24>()); break;
+    case 56: f(std::integral_constant<int, 56>()); break;
+    default: f(std::integral_constant<int, 113>()); break;
+    }
+}
+
+// Grid of the evaluation kernels for tiles of `points` points: per_cu
+// workgroups per CU, each looping over work units, so that the block's points
+// are staged in LDS once for many polynomials.
+inline dim3 eval_grid(int64_t N, int points, int64_t units, int64_t per_cu)
+{
+    const int64_t gx = ceil_div(N, points);
+    const int64_t want = std::max<int64_t>(1, ((int64_t)device_cus() * per_cu + gx - 1) / gx);
+    return dim3((unsigned)gx, (unsigned)std::min<int64_t>(std::min<int64_t>(ceil_div(units, EV_WAVES), want), 65535));
+}
+// The register forms': one or two workgroups are resident on a CU, and where
+// another kernel takes the batch each of them still has to start and end (at
+// 32 per CU, 14 us beside a call of 157).
+inline dim3 regeval_grid(int64_t N, int rows, int64_t units)
+{
+    return eval_grid(N, kWave * regeval_points(rows), units, std::min<int64_t>(tunables().eval_blocks_per_cu, 16));
+}
+inline size_t regeval_lds(int rows) { return (size_t)rows * regeval_points(rows) * kWave * sizeof(double); }
+
+// At most (exact: just) cap terms were encoded at enc (factor_bytes), their
+// class at A.maxdeg.
+void launch_eval_blocks(EvalArgs A, uint32_t *enc, int64_t cap, bool exact, double *partial, int64_t S, hipStream_t s)
 {
     if (A.Q <= 0 || A.N <= 0) return;
-    const unsigned gx = (unsigned)ceil_div(A.N, kWave);
-    // eval_blocks_per_cu workgroups per CU, each looping over work units, so
-    // that the block's points are staged in LDS once for many polynomials
-    const int64_t want = std::max<int64_t>(1, ((int64_t)device_cus() * tunables().eval_blocks_per_cu + gx - 1) / gx);
-    const unsigned gy = (unsigned)std::min<int64_t>(std::min<int64_t>(ceil_div(A.Q * S, EV_WAVES), want), 65535);
+    const dim3 grid = eval_grid(A.N, kWave, A.Q * S, tunables().eval_blocks_per_cu);
     const size_t lds = (size_t)(A.n + 1) * kWave * sizeof(double);
+    A.ranges = A.Q * S;
+    A.words_cap = word_plane(cap);
     TimedLaunch tl(POLY_TIMING_TERMS, s);
-    if (A.maxdeg)
-        hipLaunchKernelGGL(k_eval_terms_short, dim3(gx, gy), dim3(EV_THREADS), lds, s, A, enc, A.coefs, partial, S);
-    hipLaunchKernelGGL(k_eval_terms, dim3(gx, gy), dim3(EV_THREADS), lds, s, A, enc, partial, S);
+    if (A.maxdeg && regeval_pays(A.n, 8, cap, A.ranges, A.N))   // at any degree class
+        with_regeval_rows(A.n, [&](auto nr) {
+            constexpr int NR = decltype(nr)::value;
+            hipLaunchKernelGGL((k_eval_terms_reg<NR>), regeval_grid(A.N, NR, A.Q * S),
+                               dim3(EV_THREADS), regeval_lds(NR), s, A, (const uint32_t *)enc, A.coefs,
+                               (const uint32_t *)factor_words(enc, A.n, cap), partial, S);
+        });
+    if (A.maxdeg && !(exact && regeval_pays(A.n, 4, cap, A.ranges, A.N)))
+        hipLaunchKernelGGL(k_eval_terms_short, grid, dim3(EV_THREADS), lds, s, A, (const uint32_t *)enc, A.coefs,
+                           partial, S);
+    hipLaunchKernelGGL(k_eval_terms, grid, dim3(EV_THREADS), lds, s, A, (const uint32_t *)enc, partial, S);
     tl.done(s);
-    if (S > 1) hipLaunchKernelGGL(k_eval_reduce, dim3(grid1(A.Q * A.N, 256)), dim3(256), 0, s, A, partial, S);
+    if (S > 1) hipLaunchKernelGGL(k_eval_reduce, dim3(grid1(A.Q * A.N, 32)), dim3(256), 0, s, A, partial, S);
 }
 
 // ------------------------------------------------------- scans, formation
@@ -833,7 +875,7 @@ GradPlan plan_grad_formed(const poly_csr *f, int64_t N, Layout &L, bool wsum)
     g.jrp = L.take(8 * (P * n + 1));
     g.jexps = L.take((size_t)g.cap * n);
     g.jcoefs = L.take(8 * g.cap);
-    g.jenc = L.take(16 * g.cap);
+    g.jenc = L.take(factor_bytes(n, g.cap));
     if (wsum) {
         const int64_t per = ceil_div(std::max<int64_t>(N, 1), kWave) * n;
         g.S = std::max<int64_t>(1, std::min<int64_t>({ceil_div(EV_TARGET_WAVES, per), P, 256}));
@@ -895,7 +937,7 @@ EvalArgs form_jacobian(const poly_csr *f, const double *X, int64_t N, void *ws, 
     F.capacity = g.cap;
     run_form(g.form, F, ws, s);
     hipLaunchKernelGGL(k_encode_factors, dim3(grid1(g.cap, 256)), dim3(256), 0, s, jexps, g.cap, n, jenc,
-                       (const int64_t *)(jrp + P * n), ws_maxdeg(ws));
+                       (const int64_t *)(jrp + P * n), ws_maxdeg(ws), factor_words(jenc, n, g.cap));
     EvalArgs A;
     memset(&A, 0, sizeof(A));
     A.maxdeg = ws_maxdeg(ws);
@@ -927,7 +969,7 @@ poly_status run_grad(const poly_csr *f, const double *X, int64_t N, double *G, v
     EvalArgs A = form_jacobian(f, X, N, ws, g, s);
     A.mode = OUT_GRAD;
     A.Y = G;
-    launch_eval_blocks(A, at<uint32_t>(ws, g.jenc), at<double>(ws, g.part), g.S, s);
+    launch_eval_blocks(A, at<uint32_t>(ws, g.jenc), g.cap, false, at<double>(ws, g.part), g.S, s);
     LAUNCH_CHECK();
     return POLY_OK;
 }
@@ -939,18 +981,25 @@ poly_status run_wsum(const poly_csr *f, const double *X, int64_t N, const double
 {
     EvalArgs A = form_jacobian(f, X, N, ws, g, s);
     const int n = f->nvars;
-    const unsigned gx = (unsigned)ceil_div(N, kWave);
     const int64_t units = (int64_t)n * g.S;
-    const int64_t want = std::max<int64_t>(1, ((int64_t)device_cus() * tunables().eval_blocks_per_cu + gx - 1) / gx);
-    const unsigned gy = (unsigned)std::min<int64_t>(std::min<int64_t>(ceil_div(units, EV_WAVES), want), 65535);
+    const dim3 grid = eval_grid(N, kWave, units, tunables().eval_blocks_per_cu);
     const size_t lds = (size_t)(n + 1) * kWave * sizeof(double);
     double *part = g.S > 1 ? at<double>(ws, g.part) : nullptr;
+    uint32_t *jenc = at<uint32_t>(ws, g.jenc);
+    A.ranges = A.Q;
+    A.words_cap = word_plane(g.cap);
     TimedLaunch tl(POLY_TIMING_TERMS, s);
-    if (A.maxdeg)
-        hipLaunchKernelGGL(k_eval_wsum_short, dim3(gx, gy), dim3(EV_THREADS), lds, s, A,
-                           (const uint32_t *)at<uint32_t>(ws, g.jenc), A.coefs, gY, f->npolys, g.S, dX, part);
-    hipLaunchKernelGGL(k_eval_wsum, dim3(gx, gy), dim3(EV_THREADS), lds, s, A, (const uint32_t *)at<uint32_t>(ws, g.jenc),
-                       gY, f->npolys, g.S, dX, part);
+    if (regeval_pays(n, 8, g.cap, A.ranges, N))
+        with_regeval_rows(n, [&](auto nr) {
+            constexpr int NR = decltype(nr)::value;
+            hipLaunchKernelGGL((k_eval_wsum_reg<NR>), regeval_grid(N, NR, units),
+                               dim3(EV_THREADS), regeval_lds(NR), s, A, (const uint32_t *)jenc, A.coefs,
+                               (const uint32_t *)factor_words(jenc, n, g.cap), gY, f->npolys, g.S, dX, part);
+        });
+    hipLaunchKernelGGL(k_eval_wsum_short, grid, dim3(EV_THREADS), lds, s, A, (const uint32_t *)jenc, A.coefs, gY,
+                       f->npolys, g.S, dX, part);
+    hipLaunchKernelGGL(k_eval_wsum, grid, dim3(EV_THREADS), lds, s, A, (const uint32_t *)jenc, gY, f->npolys, g.S, dX,
+                       part);
     tl.done(s);
     if (g.S > 1)
         hipLaunchKernelGGL(k_sum_slices, dim3(grid1(N * n, 256)), dim3(256), 0, s, (const double *)part, N * n, g.S,
@@ -1984,7 +2033,7 @@ poly_status poly_eval_workspace(const poly_csr *f, int64_t N, poly_prec prec, in
     if (prec != POLY_FP64) return POLY_ERR_ARG;
     (void)nslices;
     Layout L;
-    L.take(16 * total_terms(f));
+    L.take(factor_bytes(f->nvars, total_terms(f)));
     L.take(eval_partial_bytes(f->npolys, N, eval_segments(f->npolys, N, total_terms(f))));
     *ws_bytes = L.total();
     return POLY_OK;
@@ -2003,7 +2052,7 @@ poly_status poly_eval(const poly_csr *f, const double *X, int64_t N, double *Y, 
     (void)nslices;
     const int64_t T = total_terms(f);
     Layout L;
-    const size_t o_enc = L.take(16 * T);
+    const size_t o_enc = L.take(factor_bytes(f->nvars, T));
     const int64_t S = eval_segments(f->npolys, N, T);
     const size_t o_part = L.take(eval_partial_bytes(f->npolys, N, S));
     if (!ws || ws_bytes < L.total()) return POLY_ERR_WORKSPACE;
@@ -2019,7 +2068,7 @@ poly_status poly_eval(const poly_csr *f, const double *X, int64_t N, double *Y, 
     // pays only where the evaluation itself is long
     uint32_t *md = T * N >= ((int64_t)1 << 22) ? ws_maxdeg(ws) : nullptr;
     if (T > 0) hipLaunchKernelGGL(k_encode_factors, dim3(grid1(T, 256)), dim3(256), 0, s, f->exps, T, f->nvars, enc,
-                                  (const int64_t *)nullptr, md);
+                                  (const int64_t *)nullptr, md, md ? factor_words(enc, f->nvars, T) : nullptr);
     EvalArgs A;
     memset(&A, 0, sizeof(A));
     A.maxdeg = md;
@@ -2033,7 +2082,7 @@ poly_status poly_eval(const poly_csr *f, const double *X, int64_t N, double *Y, 
     A.mode = OUT_EVAL;
     A.Y = Y;
     A.term_limit = T;
-    launch_eval_blocks(A, enc, at<double>(ws, o_part), S, s);
+    launch_eval_blocks(A, enc, T, true, at<double>(ws, o_part), S, s);
     LAUNCH_CHECK();
     return POLY_OK;
 }
@@ -2100,7 +2149,7 @@ static HessPlan plan_hess(const poly_csr *f, int64_t N, Layout &L)
     h.hrp = L.take(8 * (P * n * n + 1));
     h.hexps = L.take((size_t)h.hcap * n);
     h.hcoefs = L.take(8 * h.hcap);
-    h.henc = L.take(16 * h.hcap);
+    h.henc = L.take(factor_bytes(n, h.hcap));
     h.S = eval_segments(P * n * n, N, T);
     h.part = L.take(eval_partial_bytes(P * n * n, N, h.S));
     h.stage = L.take(8 * (size_t)P * n * n * N);   // entries (j <= k), point-contiguous
@@ -2147,7 +2196,7 @@ static poly_status run_hess(const poly_csr *f, const double *X, int64_t N, doubl
     F.capacity = h.hcap;
     run_form(h.hform, F, ws, s);
     hipLaunchKernelGGL(k_encode_factors, dim3(grid1(h.hcap, 256)), dim3(256), 0, s, hexps, h.hcap, n, henc,
-                       (const int64_t *)(hrp + P * n * n), ws_maxdeg(ws));
+                       (const int64_t *)(hrp + P * n * n), ws_maxdeg(ws), factor_words(henc, n, h.hcap));
     EvalArgs A;
     memset(&A, 0, sizeof(A));
     A.maxdeg = ws_maxdeg(ws);
@@ -2161,7 +2210,7 @@ static poly_status run_hess(const poly_csr *f, const double *X, int64_t N, doubl
     A.mode = OUT_HESS;
     A.Y = at<double>(ws, h.stage);
     A.term_limit = h.hcap;
-    launch_eval_blocks(A, henc, at<double>(ws, h.part), h.S, s);
+    launch_eval_blocks(A, henc, h.hcap, false, at<double>(ws, h.part), h.S, s);
     hipLaunchKernelGGL(k_hess_transpose, dim3((unsigned)ceil_div(N, 32), (unsigned)n,
                                                (unsigned)std::min<int64_t>(P, 65535)), dim3(256),
                        (size_t)n * 33 * sizeof(double), s, (const double *)A.Y, P, N, n, H);
@@ -2911,7 +2960,7 @@ PipePlan plan_pipeline(const poly_csr *in, int64_t N)
     L.off = pp.sp.total;
     pp.jcap = grad_terms_bound(T, n);
     pp.form = plan_form_bound(P, T, n, L);
-    pp.enc = L.take(16 * std::max<int64_t>(pp.jcap, 1));
+    pp.enc = L.take(factor_bytes(n, std::max<int64_t>(pp.jcap, 1)));
     pp.S = eval_segments(P * n, N, pp.jcap);
     pp.part = L.take(eval_partial_bytes(P * n, N, pp.S));
     pp.total = L.total();
@@ -2986,7 +3035,8 @@ poly_status poly_plan_create(const poly_csr *in, double zero_tol, const double *
             if (N > 0) {
                 uint32_t *enc = at<uint32_t>(ws, pp.enc);
                 hipLaunchKernelGGL(k_encode_factors, dim3(grid1(pp.jcap, 256)), dim3(256), 0, s, jac->exps, pp.jcap, n,
-                                   enc, (const int64_t *)(jac->row_ptr + P * n), ws_maxdeg(ws));
+                                   enc, (const int64_t *)(jac->row_ptr + P * n), ws_maxdeg(ws),
+                                   factor_words(enc, n, pp.jcap));
                 EvalArgs A;
                 memset(&A, 0, sizeof(A));
                 A.maxdeg = ws_maxdeg(ws);
@@ -3000,7 +3050,7 @@ poly_status poly_plan_create(const poly_csr *in, double zero_tol, const double *
                 A.mode = OUT_GRAD;
                 A.Y = G;
                 A.term_limit = pp.jcap;
-                launch_eval_blocks(A, enc, at<double>(ws, pp.part), pp.S, s);
+                launch_eval_blocks(A, enc, pp.jcap, false, at<double>(ws, pp.part), pp.S, s);
             }
         }
     }

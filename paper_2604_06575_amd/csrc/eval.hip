@@ -17,7 +17,7 @@
 //    batch whose terms all have degree <= 4 (the class the encoder records
 //    on the device) is streamed by the _short kernels, which read exactly
 //    that many factors per term, with no branch on the term's degree.
-#include "kernels.h"
+#include "regeval.h"
 
 namespace polyhip {
 
@@ -290,8 +290,11 @@ __global__ void __launch_bounds__(256) k_encode_support(const uint8_t *exps, int
 // repetition, in variable order (x1^2 x3 -> 0, 0, 2), bytes 0..11, the rest
 // of the list padded with n (an LDS row of ones); byte 12 holds d.  A term of
 // higher degree has byte 12 = 0xFF and is evaluated from its dense row.
+// `words` (or null; n <= RE_MAX_N then): the first eight factors again as
+// register offsets 2 i, four to a word, the first words at words[t] and the
+// second at words[T + RE_WORD_PAD + t] (regeval.h).
 __global__ void __launch_bounds__(256) k_encode_factors(const uint8_t *exps, int64_t T, int n, uint32_t *enc,
-                                                        const int64_t *used, uint32_t *maxdeg)
+                                                        const int64_t *used, uint32_t *maxdeg, uint32_t *words)
 {
     __shared__ uint32_t s_rows[256 * ROW_STAGE_MAX_N / 4];
     const int64_t lim = used && *used < T ? *used : T;
@@ -316,14 +319,23 @@ __global__ void __launch_bounds__(256) k_encode_factors(const uint8_t *exps, int
     }
     uint4 *o = reinterpret_cast<uint4 *>(enc) + t;
     *o = make_uint4(w[0], w[1], w[2], w[3]);
+    if (words) {
+        words[t] = w[0] << 1;   // bytes of at most RE_MAX_N: no carries
+        words[T + RE_WORD_PAD + t] = w[1] << 1;
+    }
     if (maxdeg) {
-        // the wave's largest degree, as 2 (<= 2), 3, 4 or 255 (more), by one
-        // lane, and only if it raises the recorded value: the word soon holds
-        // the batch's class, after which waves read it and add nothing (one
-        // atomic per wave on one word would serialize on large batches)
-        const uint32_t cls = w[3] <= 2u ? 2u : (w[3] <= 4u ? w[3] : 255u);
+        // the wave's largest degree, as 2 (<= 2), 3 .. 6, 8 (7, 8) or 255
+        // (more), by one lane, and only if it raises the recorded value: the
+        // word soon holds the batch's class, after which waves read it and
+        // add nothing (one atomic per wave on one word would serialize on
+        // large batches)
+        const uint32_t cls = w[3] <= 2u ? 2u : (w[3] <= 6u ? w[3] : (w[3] <= 8u ? 8u : 255u));
         const unsigned long long act = __ballot(1);
-        const uint32_t m = __ballot(cls == 255u) ? 255u : (__ballot(cls == 4u) ? 4u : (__ballot(cls == 3u) ? 3u : 2u));
+        uint32_t m = 2;
+#pragma unroll
+        for (uint32_t k = 3; k <= 8; ++k)
+            if (__ballot(cls == k)) m = k;
+        if (__ballot(cls == 255u)) m = 255;
         if (lane_id() == __ffsll((long long)act) - 1 &&
             m > __hip_atomic_load(maxdeg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax(maxdeg, m);
@@ -382,14 +394,6 @@ __device__ inline double chunk4(double v, uint32_t word, const double *xl)
     return (((v * x0) * x1) * x2) * x3;
 }
 
-// a 64-bit value that is the same on every lane, as a scalar
-__device__ inline int64_t uniform_i64(int64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
 // value of v in lane k (k uniform)
 __device__ inline double lane_f64(double v, int k)
 {
@@ -399,15 +403,14 @@ __device__ inline double lane_f64(double v, int k)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// Sum of c_t * m_t(x) over terms [ta, tb), in term order.  Term records
+// acc + the sum of c_t * m_t(x) over terms [ta, tb), in term order.  Term records
 // travel in groups of 64: lane l loads the record of term g0 + l (one
 // coalesced load per field), each term is read out of its lane into scalar
 // registers, and the next group's loads are in flight while the current
 // group is evaluated.  Only the factor words a term's degree needs are read.
 __device__ inline double term_range(const EvalArgs &A, const uint32_t *enc, int64_t ta, int64_t tb,
-                                    const double *xl)
+                                    const double *xl, double acc = 0.0)
 {
-    double acc = 0.0;
     const uint4 *ev = reinterpret_cast<const uint4 *>(enc);
     const int lane = lane_id();
     uint4 gw = make_uint4(0, 0, 0, 0);
@@ -445,13 +448,13 @@ __device__ inline double term_range(const EvalArgs &A, const uint32_t *enc, int6
     return acc;
 }
 
-// term_range for a batch whose terms all have degree <= C (C = 2, 3, 4: the
-// batch's recorded largest degree class): a term is the product of the first
+// term_range for a batch whose terms all have degree <= C (C = 2, 3, 4, 6, 8:
+// the batch's recorded largest degree class): a term is the product of the first
 // C factors of its list, read with no branch on its degree.  The padding
 // factors are ones, so the value is the same to the bit as term_range's.
 template <int C>
 __device__ inline double term_range_short(const double *__restrict__ coefs, const uint32_t *__restrict__ enc,
-                                          int64_t ta, int64_t tb, const double *xl)
+                                          int64_t ta, int64_t tb, const double *xl, double acc)
 {
     // the range is the same on every lane: as scalars, the term records and
     // coefficients are read by scalar loads, eight terms at a time, and no
@@ -459,16 +462,19 @@ __device__ inline double term_range_short(const double *__restrict__ coefs, cons
     ta = uniform_i64(ta);
     tb = uniform_i64(tb);
     const uint4 *ev = reinterpret_cast<const uint4 *>(enc);
-    double acc = 0.0;
-    auto term = [&](uint32_t word, double c) {
+    auto term = [&](uint32_t word, uint32_t next, double c) {
         double v = 1.0 * xl[(word & 0xffu) * kWave];
         if (C > 1) v = v * xl[((word >> 8) & 0xffu) * kWave];
         if (C > 2) v = v * xl[((word >> 16) & 0xffu) * kWave];
         if (C > 3) v = v * xl[(word >> 24) * kWave];
+        if (C > 4) v = v * xl[(next & 0xffu) * kWave];
+        if (C > 5) v = v * xl[((next >> 8) & 0xffu) * kWave];
+        if (C > 6) v = v * xl[((next >> 16) & 0xffu) * kWave];
+        if (C > 7) v = v * xl[(next >> 24) * kWave];
         acc += c * v;
     };
     int64_t t = ta;
-    for (; t + 8 <= tb; t += 8) {
+    if (C <= 4) for (; t + 8 <= tb; t += 8) {
         uint32_t wd[8];
         double cf[8];
 #pragma unroll
@@ -477,29 +483,67 @@ __device__ inline double term_range_short(const double *__restrict__ coefs, cons
             cf[k] = coefs[t + k];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) term(wd[k], cf[k]);
+        for (int k = 0; k < 8; ++k) term(wd[k], 0u, cf[k]);
     }
-    for (; t < tb; ++t) term(ev[t].x, coefs[t]);
+    for (; t < tb; ++t) term(ev[t].x, C > 4 ? ev[t].y : 0u, coefs[t]);
     return acc;
 }
 
 // term_range_short with the factor reads the batch's degree class md (<= 4) needs
 __device__ inline double term_range_md(uint32_t md, const double *__restrict__ coefs, const uint32_t *__restrict__ enc,
-                                       int64_t ta, int64_t tb, const double *xl)
+                                       int64_t ta, int64_t tb, const double *xl, double acc = 0.0)
 {
-    if (md <= 2) return term_range_short<2>(coefs, enc, ta, tb, xl);
-    if (md == 3) return term_range_short<3>(coefs, enc, ta, tb, xl);
-    return term_range_short<4>(coefs, enc, ta, tb, xl);
+    if (md <= 2) return term_range_short<2>(coefs, enc, ta, tb, xl, acc);
+    if (md == 3) return term_range_short<3>(coefs, enc, ta, tb, xl, acc);
+    return term_range_short<4>(coefs, enc, ta, tb, xl, acc);
 }
 
-// Which of the two forms of an evaluation kernel runs: the short one when
-// the batch's degree class is recorded and at most 4, the general one
-// otherwise.  Both are launched; the other returns before staging anything.
-template <bool SHORT>
+// term_range with the coordinates in registers (regeval.h), for a batch of
+// degree class md <= 8: eight terms at a time there, the last few (fewer than
+// eight) from the tile in LDS, in the same order and with the same roundings.
+// A range whose factors are fewer than the NR rows that the registers are
+// loaded with stays in LDS altogether.
+template <int NR>
+__device__ inline void term_range_reg(const EvalArgs &A, uint32_t md, const uint32_t *__restrict__ enc,
+                                      const double *__restrict__ coefs, const uint32_t *__restrict__ words, int64_t ta,
+                                      int64_t tb, const double *xl, uint32_t xa, double (&acc)[regeval_points(NR)])
+{
+    ta = uniform_i64(ta);
+    tb = uniform_i64(tb);
+    while (tb - ta >= 8 && (tb - ta) / 8 * 8 * md >= NR) {
+        const uint32_t q = (uint32_t)((tb - ta) >> 3 < (1 << 20) ? (tb - ta) >> 3 : 1 << 20);
+        const uint32_t *wp = words + ta, *up = words + A.words_cap + ta;
+        const double *cp = coefs + ta;
+        if (md <= 2u) term_octets<NR, 2>(acc, q, wp, up, cp, xa);
+        else if (md == 3u) term_octets<NR, 3>(acc, q, wp, up, cp, xa);
+        else if (md == 4u) term_octets<NR, 4>(acc, q, wp, up, cp, xa);
+        else if (md == 5u) term_octets<NR, 5>(acc, q, wp, up, cp, xa);
+        else if (md == 6u) term_octets<NR, 6>(acc, q, wp, up, cp, xa);
+        else term_octets<NR, 8>(acc, q, wp, up, cp, xa);
+        ta += 8 * (int64_t)q;
+    }
+#pragma unroll
+    for (int p = 0; p < regeval_points(NR); ++p) {
+        const double *x = xl + p * NR * kWave;
+        if (md <= 4u) acc[p] = term_range_md(md, coefs, enc, ta, tb, x, acc[p]);
+        else if (md <= 6u) acc[p] = term_range_short<6>(coefs, enc, ta, tb, x, acc[p]);
+        else acc[p] = term_range_short<8>(coefs, enc, ta, tb, x, acc[p]);
+    }
+}
+
+// FORM of an evaluation kernel: EF_GENERAL (term_range), EF_SHORT
+// (term_range_short) or the rows of the register form (term_range_reg).
+constexpr int EF_GENERAL = 0, EF_SHORT = 1;
+
+// Which of the kernels of an evaluation runs, by the batch's degree class (255
+// where it is not recorded) and its terms.  Those that the host cannot rule
+// out are launched; the others return before staging anything.
+template <int FORM>
 __device__ inline bool eval_form_runs(const EvalArgs &A, uint32_t &md)
 {
-    md = A.maxdeg ? *A.maxdeg : 255u;
-    return SHORT == (md <= 4u);
+    md = A.maxdeg ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*A.maxdeg) : 255u;
+    const bool reg = A.maxdeg && regeval_pays(A.n, md, A.rp[A.Q], A.ranges, A.N);
+    return FORM > EF_SHORT ? reg : (!reg && (FORM == EF_SHORT) == (md <= 4u));
 }
 
 }  // namespace
@@ -513,23 +557,56 @@ __device__ inline bool eval_form_runs(const EvalArgs &A, uint32_t &md)
 // pointers are fetched while the current unit is evaluated.  The block's
 // waves share the point tile in LDS: (n + 1) * 64 doubles, variable-major,
 // plus a row of ones that the factor lists use as padding.
-template <bool SHORT>
+
+// This lane's column of the coordinate tile as an LDS byte address.
+__device__ inline uint32_t lds_address(const double *p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) double *)p;
+}
+
+// points of a lane
+template <int FORM>
+constexpr int form_points = FORM <= EF_SHORT ? 1 : regeval_points(FORM);
+
+template <int FORM>
+__device__ inline void range_of_form(const EvalArgs &A, uint32_t md, const uint32_t *__restrict__ enc,
+                                     const double *__restrict__ coefs, const uint32_t *__restrict__ words, int64_t ta,
+                                     int64_t tb, const double *xl, double (&acc)[form_points<FORM>])
+{
+#pragma unroll
+    for (int p = 0; p < form_points<FORM>; ++p) acc[p] = 0.0;
+    if constexpr (FORM == EF_GENERAL) acc[0] = term_range(A, enc, ta, tb, xl);
+    else if constexpr (FORM == EF_SHORT) acc[0] = term_range_md(md, coefs, enc, ta, tb, xl);
+    else term_range_reg<FORM>(A, md, enc, coefs, words, ta, tb, xl, lds_address(xl), acc);
+}
+
+// The coordinate tiles of the block's points, FORM rows apart.
+template <int FORM>
+__device__ inline void stage_points(const EvalArgs &A, int64_t pt0, double *s_x)
+{
+    const int rows = A.n + 1;
+#pragma unroll
+    for (int p = 0; p < form_points<FORM>; ++p)
+        for (int idx = threadIdx.x; idx < rows * kWave; idx += EV_THREADS) {
+            const int i = idx / kWave, l = idx % kWave;
+            const int64_t pt = pt0 + p * kWave + l;
+            s_x[p * FORM * kWave + idx] = i == A.n ? 1.0 : (pt < A.N ? A.X[pt * A.n + i] : 0.0);
+        }
+    __syncthreads();   // the only barrier: waves run independently from here
+}
+
+template <int FORM>
 __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__restrict__ enc,
-                                       const double *__restrict__ coefs, double *partial, int64_t S)
+                                       const double *__restrict__ coefs, const uint32_t *__restrict__ words,
+                                       double *partial, int64_t S)
 {
     extern __shared__ double s_x[];
     uint32_t md;
-    if (!eval_form_runs<SHORT>(A, md)) return;
+    if (!eval_form_runs<FORM>(A, md)) return;
     const int lane = lane_id();
     const int w = wave_id();
-    const int64_t pt0 = (int64_t)blockIdx.x * kWave;
-    const int64_t pt = pt0 + lane;
-    for (int idx = threadIdx.x; idx < (A.n + 1) * kWave; idx += EV_THREADS) {
-        const int i = idx / kWave, l = idx % kWave;
-        const int64_t p = pt0 + l;
-        s_x[idx] = i == A.n ? 1.0 : (p < A.N ? A.X[p * A.n + i] : 0.0);
-    }
-    __syncthreads();   // the only barrier: waves run independently from here
+    const int64_t pt0 = (int64_t)blockIdx.x * (kWave * form_points<FORM>);
+    stage_points<FORM>(A, pt0, s_x);
     const double *xl = s_x + lane;
     int vz;   // a zero the compiler treats as per-lane
     asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
@@ -550,10 +627,15 @@ __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__rest
         const int64_t b1 = r1 < A.term_limit ? r1 : A.term_limit;
         const int64_t len = b1 > b0 ? b1 - b0 : 0;
         const int64_t sa = b0 + len * sg / S, sb = b0 + len * (sg + 1) / S;
-        const double acc = SHORT ? term_range_md(md, coefs, enc, sa, sb, xl) : term_range(A, enc, sa, sb, xl);
-        if (pt < A.N) {
-            if (S == 1) store_out(A, q, pt, acc);
-            else partial[(sg * A.Q + q) * A.N + pt] = acc;
+        double acc[form_points<FORM>];
+        range_of_form<FORM>(A, md, enc, coefs, words, sa, sb, xl, acc);
+#pragma unroll
+        for (int k = 0; k < form_points<FORM>; ++k) {
+            const int64_t pt = pt0 + k * kWave + lane;
+            if (pt < A.N) {
+                if (S == 1) store_out(A, q, pt, acc[k]);
+                else partial[(sg * A.Q + q) * A.N + pt] = acc[k];
+            }
         }
         r0 = n0;
         r1 = n1;
@@ -563,7 +645,7 @@ __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__rest
 __global__ void __launch_bounds__(EV_THREADS) k_eval_terms(EvalArgs A, const uint32_t *enc, double *partial,
                                                            int64_t S)
 {
-    eval_terms_body<false>(A, enc, A.coefs, partial, S);
+    eval_terms_body<EF_GENERAL>(A, enc, A.coefs, nullptr, partial, S);
 }
 
 // The same for batches of degree class <= 4 (term_range_short).
@@ -571,8 +653,28 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_terms_short(EvalArgs A, con
                                                                  const double *__restrict__ coefs, double *partial,
                                                                  int64_t S)
 {
-    eval_terms_body<true>(A, enc, coefs, partial, S);
+    eval_terms_body<EF_SHORT>(A, enc, coefs, nullptr, partial, S);
 }
+
+// The same for batches of degree class <= 8 in at most RE_MAX_N variables,
+// coordinates in registers.  Bound by the issue of scalar and vector
+// instructions.  A quartic of 100,000 terms in 100 variables at 8,192 points
+// (one point a lane, 254 registers): 364 us from LDS, 227 us; gradients of 256
+// polynomials of degree 6 in 20 variables, 4.3 million derivative terms at
+// 1,000 points (two points a lane, 128 registers): 3,400 us, 1,033 us.
+template <int NR>
+__global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
+    k_eval_terms_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
+                     const uint32_t *__restrict__ words, double *partial, int64_t S)
+{
+    eval_terms_body<NR>(A, enc, coefs, words, partial, S);
+}
+template __global__ void k_eval_terms_reg<24>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                              double *, int64_t);
+template __global__ void k_eval_terms_reg<56>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                              double *, int64_t);
+template __global__ void k_eval_terms_reg<113>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                              double *, int64_t);
 
 // Weighted sum over polynomials of formed Jacobian entries (the reverse mode
 // of eval without per-polynomial gradients):
@@ -580,43 +682,47 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_terms_short(EvalArgs A, con
 // Unit (j, s) takes the polynomials p of segment s of S, in order, and sums
 // gY * (that entry's terms summed in term order); with S > 1 the segments'
 // partials [S][N][n] are added in order by k_sum_slices.
-template <bool SHORT>
+template <int FORM>
 __device__ inline void eval_wsum_body(const EvalArgs &A, const uint32_t *__restrict__ enc,
-                                      const double *__restrict__ coefs, const double *gY, int64_t P, int64_t S,
-                                      double *out, double *partial)
+                                      const double *__restrict__ coefs, const uint32_t *__restrict__ words,
+                                      const double *gY, int64_t P, int64_t S, double *out, double *partial)
 {
     extern __shared__ double s_x[];
     uint32_t md;
-    if (!eval_form_runs<SHORT>(A, md)) return;
+    if (!eval_form_runs<FORM>(A, md)) return;
     const int lane = lane_id();
     const int w = wave_id();
     const int n = A.n;
-    const int64_t pt0 = (int64_t)blockIdx.x * kWave;
-    const int64_t pt = pt0 + lane;
-    for (int idx = threadIdx.x; idx < (n + 1) * kWave; idx += EV_THREADS) {
-        const int i = idx / kWave, l = idx % kWave;
-        const int64_t p = pt0 + l;
-        s_x[idx] = i == n ? 1.0 : (p < A.N ? A.X[p * n + i] : 0.0);
-    }
-    __syncthreads();
+    constexpr int PT = form_points<FORM>;
+    const int64_t pt0 = (int64_t)blockIdx.x * (kWave * PT);
+    stage_points<FORM>(A, pt0, s_x);
     const double *xl = s_x + lane;
     const int64_t units = (int64_t)n * S;
     for (int64_t u = (int64_t)blockIdx.y * EV_WAVES + w; u < units; u += (int64_t)gridDim.y * EV_WAVES) {
         const int64_t j = u / S, sg = u % S;
         const int64_t p0 = P * sg / S, p1 = P * (sg + 1) / S;
-        double acc = 0.0;
+        double acc[PT] = {};
         for (int64_t p = p0; p < p1; ++p) {
             const int64_t q = p * n + j;
             const int64_t b0 = A.rp[q];
             const int64_t b1 = A.rp[q + 1] < A.term_limit ? A.rp[q + 1] : A.term_limit;
             if (b1 <= b0) continue;
-            const double v = SHORT ? term_range_md(md, coefs, enc, b0, b1, xl) : term_range(A, enc, b0, b1, xl);
-            const double g = pt < A.N ? gY[p * A.N + pt] : 0.0;
-            acc = __builtin_fma(g, v, acc);
+            double v[PT];
+            range_of_form<FORM>(A, md, enc, coefs, words, b0, b1, xl, v);
+#pragma unroll
+            for (int k = 0; k < PT; ++k) {
+                const int64_t pt = pt0 + k * kWave + lane;
+                const double g = pt < A.N ? gY[p * A.N + pt] : 0.0;
+                acc[k] = __builtin_fma(g, v[k], acc[k]);
+            }
         }
-        if (pt < A.N) {
-            if (S == 1) out[pt * n + j] = acc;
-            else partial[(sg * A.N + pt) * n + j] = acc;
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int64_t pt = pt0 + k * kWave + lane;
+            if (pt < A.N) {
+                if (S == 1) out[pt * n + j] = acc[k];
+                else partial[(sg * A.N + pt) * n + j] = acc[k];
+            }
         }
     }
 }
@@ -624,7 +730,7 @@ __device__ inline void eval_wsum_body(const EvalArgs &A, const uint32_t *__restr
 __global__ void __launch_bounds__(EV_THREADS) k_eval_wsum(EvalArgs A, const uint32_t *enc, const double *gY,
                                                           int64_t P, int64_t S, double *out, double *partial)
 {
-    eval_wsum_body<false>(A, enc, A.coefs, gY, P, S, out, partial);
+    eval_wsum_body<EF_GENERAL>(A, enc, A.coefs, nullptr, gY, P, S, out, partial);
 }
 
 // The same for batches of degree class <= 4 (term_range_short).
@@ -632,8 +738,25 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_wsum_short(EvalArgs A, cons
                                                                 const double *__restrict__ coefs, const double *gY,
                                                                 int64_t P, int64_t S, double *out, double *partial)
 {
-    eval_wsum_body<true>(A, enc, coefs, gY, P, S, out, partial);
+    eval_wsum_body<EF_SHORT>(A, enc, coefs, nullptr, gY, P, S, out, partial);
 }
+
+// The same for batches of degree class <= 8, coordinates in registers (the
+// quartic's 400,000 derivative terms: 1,118 us from LDS, 625 us).
+template <int NR>
+__global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
+    k_eval_wsum_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
+                    const uint32_t *__restrict__ words, const double *gY, int64_t P, int64_t S, double *out,
+                    double *partial)
+{
+    eval_wsum_body<NR>(A, enc, coefs, words, gY, P, S, out, partial);
+}
+template __global__ void k_eval_wsum_reg<24>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                             const double *, int64_t, int64_t, double *, double *);
+template __global__ void k_eval_wsum_reg<56>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                             const double *, int64_t, int64_t, double *, double *);
+template __global__ void k_eval_wsum_reg<113>(EvalArgs, const uint32_t *, const double *, const uint32_t *,
+                                             const double *, int64_t, int64_t, double *, double *);
 
 // H[p][pt][j][k] = stage[p][min(j,k)][max(j,k)][pt]: each Hessian entry was
 // evaluated once (j <= k) into a point-contiguous staging row; both triangles
@@ -664,16 +787,26 @@ __global__ void __launch_bounds__(256) k_hess_transpose(const double *stage, int
     }
 }
 
-// Sum of the S segment partials of (q, pt) in segment order, stored in the
-// output layout of A.mode.
-__global__ void k_eval_reduce(EvalArgs A, const double *partial, int64_t S)
+// Sum of the S segment partials of (q, pt), stored in the output layout of
+// A.mode.  A block takes 32 outputs, eight threads each: an eighth of the
+// segments in segment order, then the eight sums in that order.  (One thread
+// per output added them one load after another: 36 against 7 us for 128
+// segments of 8,192 outputs.)
+__global__ void __launch_bounds__(256) k_eval_reduce(EvalArgs A, const double *partial, int64_t S)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= A.Q * A.N) return;
-    const int64_t q = idx / A.N, pt = idx % A.N;
-    double sum = partial[idx];
-    for (int64_t s = 1; s < S; ++s) sum += partial[s * A.Q * A.N + idx];
-    store_out(A, q, pt, sum);
+    __shared__ double s_sum[8][33];
+    const int l = threadIdx.x & 31, part = threadIdx.x >> 5;
+    const int64_t idx = (int64_t)blockIdx.x * 32 + l, total = A.Q * A.N;
+    double sum = 0.0;
+    if (idx < total)
+        for (int64_t s = S * part / 8; s < S * (part + 1) / 8; ++s) sum += partial[s * total + idx];
+    s_sum[part][l] = sum;
+    __syncthreads();
+    if (part == 0 && idx < total) {
+#pragma unroll
+        for (int k = 1; k < 8; ++k) sum += s_sum[k][l];
+        store_out(A, idx / A.N, idx % A.N, sum);
+    }
 }
 
 // --------------------------------------------------------------- backward

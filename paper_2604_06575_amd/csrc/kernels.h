@@ -222,15 +222,17 @@ struct EvalArgs {
     int mode;                     // OutMode
     double *Y;                    // output
     int64_t term_limit;           // terms at or beyond this index are never read
-    const uint32_t *maxdeg;       // bound on every term's degree (2, 3, 4; else 255), recorded by k_encode_factors, or null
+    const uint32_t *maxdeg;       // bound on every term's degree (2 .. 6, 8; else 255), recorded by k_encode_factors, or null
+    int64_t ranges;               // ranges that the terms are summed in
+    int64_t words_cap;            // words from one plane of k_encode_factors to the next
 };
 
 __global__ void k_encode_support(const uint8_t *exps, int64_t T, int n, uint64_t *enc, const int64_t *used);
 constexpr int EV_MAX_DEG = 12;   // total degree handled by the factor-list encoding
 // maxdeg (or null): a zeroed word that receives, by atomicMax, the largest
-// degree class of the encoded terms (2 for degree <= 2, then 3, 4, and 255)
+// degree class of the encoded terms (2 for degree <= 2, then 3 .. 6, 8, and 255)
 __global__ void k_encode_factors(const uint8_t *exps, int64_t T, int n, uint32_t *enc, const int64_t *used,
-                                 uint32_t *maxdeg);
+                                 uint32_t *maxdeg, uint32_t *words = nullptr);
 
 // products of polynomial matrices (matrix.hip)
 constexpr int MAT_THREADS = 256;
@@ -344,9 +346,17 @@ struct AffStochArgs {
 __global__ void k_affine_stochastic(AffStochArgs A);
 __global__ void k_eval_terms(EvalArgs A, const uint32_t *enc, double *partial, int64_t S);
 // k_eval_terms for batches whose recorded degree class (A.maxdeg) is at most
-// 4; each of the two returns at once where the other applies
+// 4, and with the coordinates in registers (NR = regeval_rows(n)) where
+// regeval_pays; each of the three returns at once where another applies
 __global__ void k_eval_terms_short(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
                                    double *partial, int64_t S);
+template <int NR>
+__global__ void k_eval_terms_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
+                                 const uint32_t *__restrict__ words, double *partial, int64_t S);
+template <int NR>
+__global__ void k_eval_wsum_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
+                                const uint32_t *__restrict__ words, const double *gY, int64_t P, int64_t S,
+                                double *out, double *partial);
 __global__ void k_eval_reduce(EvalArgs A, const double *partial, int64_t S);
 __global__ void k_hess_transpose(const double *stage, int64_t P, int64_t N, int n, double *H);
 // CSR batches over a shared basis (dense.hip)

@@ -1,0 +1,91 @@
+"""Sparse evaluation and reverse mode of long batches of low degree (the
+coordinates in registers): at the variable counts where the registers and the
+tile's rows change, in every degree class, and at ranges around the 8, 16 and
+32 terms of a step beside long ones.
+
+Bound: a sum of m products of at most d + 3 factors, in any order, is within
+(m + d + 5) * 2**-53 of the sum of the terms' absolute values.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_06575_amd as ph
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -53
+
+
+def _batch(rng, n, d, sizes):
+    """Factor lists padded with n, and the exponent rows.  Variables 1 to 6
+    occur in few terms and variable 2 in none; the last one often, also twice."""
+    T = sum(sizes)
+    f = rng.integers(0, n, size=(T, d))
+    f[:, :2] = np.where(rng.random((T, 2)) < 0.2, n - 1, f[:, :2])
+    if n > 7:
+        f[(f > 0) & (f < 7)] = n - 2
+        for v, m in ((1, 1), (3, 7), (4, 8), (5, 33), (6, 65)):
+            f[rng.choice(T, m, replace=False), 0] = v
+    f[np.arange(d)[None, :] >= rng.integers(0, d + 1, size=T)[:, None]] = n
+    f[-1, :] = rng.integers(0, n, size=d)                               # one term of the full degree
+    f.sort(axis=1)
+    e = np.zeros((T, n + 1), np.uint8)
+    np.add.at(e, (np.arange(T)[:, None], f), 1)
+    rp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    return f, np.ascontiguousarray(e[:, :n]), rp, rng.standard_normal(T)
+
+
+def _padded(X):
+    return np.concatenate([X, np.ones((X.shape[0], 1))], axis=1).astype(np.longdouble)
+
+
+CASES = [(4, 8), (23, 2), (24, 3), (55, 4), (56, 5), (100, 6), (112, 4), (112, 7), (55, 8), (113, 4), (40, 9)]
+
+
+@pytest.mark.parametrize("n,d", CASES)
+def test_eval(n, d):
+    rng = np.random.default_rng(100 * n + d)
+    sizes = [0, 1, 15, 16, 18, 33, 0, 64, 131, 8191]
+    f, e, rp, c = _batch(rng, n, d, sizes)
+    N = 65601
+    X = rng.uniform(-1, 1, (N, n))
+    X[3, 0], X[70, n - 1], X[N - 1, 0] = np.inf, np.nan, -np.inf
+    b = ph.batch_from_numpy(rp, e, c)
+    t = torch.from_numpy(X).cuda()
+    Y = ph.eval(b, t).cpu().numpy().reshape(-1, N)
+    assert np.array_equal(Y, ph.eval(b, t).cpu().numpy().reshape(-1, N), equal_nan=True)
+    pts = np.concatenate([np.arange(0, 3), np.arange(60, 70), np.arange(71, N - 1, 999), np.arange(N - 70, N - 1)])
+    v = c * np.prod(_padded(X[pts])[:, f], axis=2)                       # [points, T]
+    for p, m in enumerate(sizes):
+        s = v[:, rp[p]:rp[p + 1]]
+        assert np.all(np.abs(Y[p, pts] - s.sum(1)) <= (m + d + 5) * U * np.abs(s).sum(1)), p
+    # one term past the degrees of the fast forms: the other polynomials are
+    # evaluated by the general kernel, to the same bits
+    e2 = e.copy()
+    e2[-1, 0] += 9
+    Y2 = ph.eval(ph.batch_from_numpy(rp, e2, c), t).cpu().numpy().reshape(-1, N)
+    assert np.array_equal(Y[:-1], Y2[:-1], equal_nan=True)
+
+
+@pytest.mark.parametrize("n,d", [c for c in CASES if c[0] > 7])
+def test_dx(n, d):
+    rng = np.random.default_rng(200 * n + d)
+    sizes = [20000, 9001]
+    f, e, rp, c = _batch(rng, n, d, sizes)
+    N, P = 1281, len(sizes)
+    X, gY = rng.uniform(-1, 1, (N, n)), rng.standard_normal((P, N))
+    gX, _ = ph.eval_backward(ph.batch_from_numpy(rp, e, c), torch.from_numpy(X).cuda(), torch.from_numpy(gY).cuda(),
+                             want_dX=True, want_dC=False)
+    pts = np.array([0, 1, 63, 64, 127, 128, 640, 1279, 1280])
+    x = _padded(X[pts])[:, f]                                           # [points, T, d]
+    g = np.repeat(gY[:, pts], sizes, axis=0).T * c                      # [points, T]
+    ref, mag = np.zeros((n + 1, len(pts)), np.longdouble), np.zeros((n + 1, len(pts)), np.longdouble)
+    cnt = np.zeros((n + 1, 1))
+    for k in range(d):                                                  # the derivative in the k-th factor
+        q = (g * np.prod(np.delete(x, k, axis=2), axis=2)).T            # [T, points]
+        np.add.at(ref, f[:, k], q)
+        np.add.at(mag, f[:, k], np.abs(q))
+        np.add.at(cnt, f[:, k], 1)
+    got = gX.cpu().numpy().T[:, pts]
+    assert np.all(np.abs(got - ref[:n]) <= (cnt[:n] + d + 5) * U * mag[:n])
