@@ -142,6 +142,8 @@ def lib():
     inner = {
         "max_degrees": ("PK8poly_csrS2_PvPlS3_", [pcsr, pcsr, P, P, P]),
         "read_back": ("PKvPKllPlPv", [P, P, i64, P, P]),
+        "simplify_bounded_workspace": ("PK8poly_csriPm", [pcsr, i32, psz]),
+        "simplify_bounded": ("PK8poly_csriPS0_dPvmS4_", [pcsr, i32, pcsr, d, P, ctypes.c_size_t, P]),
         "mul_bounded_workspace": ("PK8poly_csrS2_iiPmPl", [pcsr, pcsr, i32, i32, psz, ctypes.POINTER(i64)]),
         "mul_bounded": ("PK8poly_csrS2_iiPS0_dPvmS4_", [pcsr, pcsr, i32, i32, pcsr, d, P, ctypes.c_size_t, P]),
         "mtimes_bounded_workspace": ("PK8poly_csrS2_llliiPmPl",
@@ -360,15 +362,18 @@ def simplify(b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | N
     capture); the output row pointer stays on the device."""
     L = lib()
     cin = b.csr()
-    need = ctypes.c_size_t()
-    _check(L.poly_simplify_workspace(ctypes.byref(cin), ctypes.byref(need)), "poly_simplify_workspace")
-    if ws is None or ws.numel() < need.value:
-        ws = _workspace(need.value, b.coefs.device)
     if out is None:
         out = _result(b.n, b.npolys, b.nterms, b.max_exp, b.coefs.device)
     cout = out.csr()
-    _check(L.poly_simplify(ctypes.byref(cin), ctypes.byref(cout), float(tol), ctypes.c_void_p(ws.data_ptr()),
-                           ws.numel(), _stream()), "poly_simplify")
+    # the terms' degree, for a call that waits for its result anyway: 2,048 terms
+    # in 20 variables 92 against 110 us, 1,024 terms 89 us either way
+    deg = _degrees(cin, b.coefs.device)[0] if finish and b.nterms >= 2048 else -1
+    need = ctypes.c_size_t()
+    _check(L.simplify_bounded_workspace(ctypes.byref(cin), deg, ctypes.byref(need)), "poly_simplify_workspace")
+    if ws is None or ws.numel() < need.value:
+        ws = _workspace(need.value, b.coefs.device)
+    _check(L.simplify_bounded(ctypes.byref(cin), deg, ctypes.byref(cout), float(tol), ctypes.c_void_p(ws.data_ptr()),
+                              ws.numel(), _stream()), "poly_simplify")
     if not finish:
         return out
     return _finish(out, ws, "poly_simplify", trim)
@@ -452,17 +457,22 @@ def mul_workspace(a: Batch, b: Batch) -> tuple[int, int]:
     return int(ws_bytes.value), int(raw.value)
 
 
-def _product_degrees(ca: PolyCSR, cb: PolyCSR, raw: int, finish: bool, scratch: torch.Tensor) -> tuple[int, int]:
+def _degrees(ca: PolyCSR, device, cb: PolyCSR | None = None) -> tuple[int, int]:
+    """Total degrees of one or two batches, read back from the device."""
+    words = _host_words(2)
+    scratch = _workspace(16, device)
+    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb) if cb is not None else None, scratch.data_ptr(),
+                             words.ctypes.data, _stream()), "max_degrees")
+    return int(words[0]), int(words[1])
+
+
+def _product_degrees(ca: PolyCSR, cb: PolyCSR, raw: int, finish: bool, device) -> tuple[int, int]:
     """Total degrees of both operands, read back from the device, for a call
     that waits for its result anyway and whose product can be formed on a
-    dense range of monomials; (-1, -1) otherwise.  scratch: two words or more
-    on the device, free until the call's kernels run."""
+    dense range of monomials; (-1, -1) otherwise."""
     if not finish or ca.nvars > 16 or raw < 4096:
         return -1, -1
-    words = _host_words(2)
-    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb), scratch.data_ptr(), words.ctypes.data, _stream()),
-           "max_degrees")
-    return int(words[0]), int(words[1])
+    return _degrees(ca, device, cb)
 
 
 def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | None = None,
@@ -477,7 +487,7 @@ def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tenso
     if out is None:
         out = _result(a.n, a.npolys, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
-    da, db = _product_degrees(ca, cb, raw.value, finish, out.row_ptr)
+    da, db = _product_degrees(ca, cb, raw.value, finish, dev)
     if da >= 0:
         _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(ws_bytes),
                                        ctypes.byref(raw)), "poly_mul_workspace")
@@ -511,7 +521,7 @@ def mtimes(a: Batch, b: Batch, I: int, K: int, J: int, tol: float = 0.0, trim: b
     if out is None:
         out = _result(a.n, I * J, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
-    da, db = _product_degrees(ca, cb, raw.value, finish, out.row_ptr)
+    da, db = _product_degrees(ca, cb, raw.value, finish, dev)
     if da >= 0:
         _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(ws_bytes),
                                           ctypes.byref(raw)), "poly_mtimes_workspace")

@@ -703,6 +703,9 @@ void ensure_lds_attrs()
     (void)hipFuncSetAttribute((const void *)k_eval_terms, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 8192);
     (void)hipFuncSetAttribute((const void *)k_eval_terms_short, hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024 - 8192);
+    for (const void *f : {(const void *)k_sr_merge<1024, 20, 7>, (const void *)k_sr_merge<1024, 20, 9>,
+                          (const void *)k_sr_merge<512, 16, 7>, (const void *)k_sr_merge<512, 16, 9>})
+        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
     (void)hipFuncSetAttribute((const void *)k_backward_dc, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     (void)hipFuncSetAttribute((const void *)k_backward2_dc, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     (void)hipFuncSetAttribute((const void *)k_hess_transpose, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
@@ -2866,6 +2869,136 @@ poly_status read_back(const void *ws, const int64_t *row_ptr, int64_t count, int
     LAUNCH_CHECK();
     if (hipStreamSynchronize(s) != hipSuccess) return POLY_ERR_HIP;
     return (poly_status)(int32_t)host[0];
+}
+
+// simplify by monomial ranks: sizes and layout, on == false where it does not
+// apply.
+struct SegRankPlan {
+    bool on = false;
+    uint32_t cells = 0;
+    int rank_bits = 0;
+    int64_t count[4] = {0, 0, 0, 0};   // polynomials of at least 8,192, 1,024, 256 and 0 terms
+    size_t pairs = 0;                  // table entries
+    size_t table, pair, order, seg_count, st_rank, st_coef, total;
+};
+
+static SegRankPlan plan_segrank(const poly_csr *in, int deg)
+{
+    SegRankPlan m;
+    const int n = in->nvars;
+    const int64_t T = total_terms(in), P = in->npolys;
+    if (deg < 0 || deg > 255 || n < 1 || n > SR_MAX_N || T < 1 || P >= (int64_t(1) << 31)) return m;
+    for (int64_t p = 0; p < P; ++p) {
+        const int64_t t = in->row_ptr_host[p + 1] - in->row_ptr_host[p];
+        if (t > SR_MAX_TERMS) return m;
+        ++m.count[(t < 8192) + (t < 1024) + (t < 256)];
+    }
+    unsigned __int128 cells = 1;
+    for (int i = 0; i < n; ++i) {
+        cells = cells * (unsigned)(deg + i + 1) / (unsigned)(i + 1);   // C(deg + i + 1, i + 1), exact
+        if (cells >= ((unsigned __int128)1 << 31)) return m;
+    }
+    m.pairs = (size_t)((n + 1) / 2) * (deg + 1) * (deg + 1);
+    if (4 * m.pairs > SR_TABLE_MAX) return m;
+    m.cells = (uint32_t)cells;
+    m.rank_bits = m.cells > 1 ? bit_width_u32(m.cells - 1) : 0;
+    Layout L;
+    m.table = L.take(4 * (size_t)n * (deg + 2));
+    m.pair = L.take(4 * m.pairs);
+    m.order = L.take(8 * P);
+    m.seg_count = L.take(8 * P);
+    m.st_rank = L.take(4 * T);
+    m.st_coef = L.take(8 * T);
+    m.total = L.total();
+    m.on = true;
+    return m;
+}
+
+static poly_status run_segrank(const SegRankPlan &m, const poly_csr *in, int deg, poly_csr *out, double zero_tol,
+                               void *ws, hipStream_t s)
+{
+    const int n = in->nvars;
+    const int64_t P = in->npolys;
+    MulDenseArgs M;   // the rank tables' kernel, no terms
+    memset(&M, 0, sizeof(M));
+    M.n = n;
+    M.D = deg;
+    M.status = at<int32_t>(ws, 0);
+    hipLaunchKernelGGL(k_md_prep, dim3(4), dim3(256), 0, s, M, in->exps, (int64_t)0, 0, 0, in->exps, (int64_t)0, 0, 0,
+                       (uint64_t *)nullptr, (uint64_t *)nullptr, (uint64_t *)nullptr, (uint64_t *)nullptr,
+                       at<uint32_t>(ws, m.table), at<uint32_t>(ws, m.pair));
+    SegRankArgs A;
+    A.n = n;
+    A.D = deg;
+    A.max_exp = in->max_exp;
+    A.cells = m.cells;
+    A.rank_bits = m.rank_bits;
+    A.rp = in->row_ptr;
+    A.exps = in->exps;
+    A.coefs = in->coefs;
+    A.order = at<int64_t>(ws, m.order);
+    A.pairs = at<uint32_t>(ws, m.pair);
+    A.table = at<uint32_t>(ws, m.table);
+    A.st_rank = at<uint32_t>(ws, m.st_rank);
+    A.st_coef = at<double>(ws, m.st_coef);
+    A.seg_count = at<int64_t>(ws, m.seg_count);
+    A.tol = zero_tol;
+    A.status = M.status;
+    hipLaunchKernelGGL(k_order_by_size, dim3(1), dim3(1024), 0, s, in->row_ptr, P, at<int64_t>(ws, m.order));
+    // passes of nine bits, or of seven where that takes no more of them
+    const bool seven = (m.rank_bits + 6) / 7 == (m.rank_bits + 8) / 9;
+    int64_t first = 0;
+    auto merge = [&](auto threads, auto items, int64_t count) {
+        constexpr int TH = decltype(threads)::value, IT = decltype(items)::value;
+        const size_t lds = (size_t)TH / kWave * 1024 + 6 * (size_t)TH * IT + 4 * m.pairs;
+        if (count > 0 && seven)
+            hipLaunchKernelGGL((k_sr_merge<TH, IT, 7>), dim3((unsigned)count), dim3(TH), lds, s, A, first);
+        else if (count > 0)
+            hipLaunchKernelGGL((k_sr_merge<TH, IT, 9>), dim3((unsigned)count), dim3(TH), lds, s, A, first);
+        first += count;
+    };
+    merge(std::integral_constant<int, 1024>(), std::integral_constant<int, 20>(), m.count[0]);
+    merge(std::integral_constant<int, 512>(), std::integral_constant<int, 16>(), m.count[1]);
+    merge(std::integral_constant<int, 256>(), std::integral_constant<int, 4>(), m.count[2]);
+    merge(std::integral_constant<int, 64>(), std::integral_constant<int, 4>(), m.count[3]);
+    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, (const int64_t *)A.seg_count, P, out->row_ptr);
+    const size_t lds = 4 * (size_t)n * (deg + 2) + 256 * (size_t)n;
+    const int64_t grid = std::min<int64_t>(ceil_div(total_terms(in), 256), (int64_t)device_cus() * 32);
+    hipLaunchKernelGGL(k_sr_unpack, dim3((unsigned)grid), dim3(256), lds, s, A, P, (const int64_t *)out->row_ptr,
+                       out->exps, out->coefs, out->capacity);
+    LAUNCH_CHECK();
+    return POLY_OK;
+}
+
+// poly_simplify with a bound on the terms' total degree (negative: not known,
+// the same as poly_simplify).  The result is poly_simplify's, bit for bit.  A
+// term above the bound is a device status POLY_ERR_EXPONENT.
+poly_status simplify_bounded_workspace(const poly_csr *in, int32_t deg, size_t *ws_bytes)
+{
+    poly_status st = check_csr(in, true);
+    if (st != POLY_OK) return st;
+    if (!ws_bytes) return POLY_ERR_ARG;
+    const SegRankPlan m = plan_segrank(in, deg);
+    if (!m.on) return poly_simplify_workspace(in, ws_bytes);
+    *ws_bytes = m.total;
+    return POLY_OK;
+}
+
+poly_status simplify_bounded(const poly_csr *in, int32_t deg, poly_csr *out, double zero_tol, void *ws,
+                             size_t ws_bytes, void *stream)
+{
+    poly_status st = check_csr(in, true);
+    if (st != POLY_OK) return st;
+    const SegRankPlan m = plan_segrank(in, deg);
+    if (!m.on) return poly_simplify(in, out, zero_tol, ws, ws_bytes, stream);
+    if ((st = check_csr(out, false)) != POLY_OK) return st;
+    if (out->nvars != in->nvars || out->npolys != in->npolys) return POLY_ERR_ARG;
+    if (!(zero_tol >= 0.0)) return POLY_ERR_ARG;
+    if (!ws || ws_bytes < m.total) return POLY_ERR_WORKSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    ensure_lds_attrs();
+    clear_u64(at<unsigned long long>(ws, 0), 1, s);
+    return run_segrank(m, in, deg, out, zero_tol, ws, s);
 }
 
 // poly_mul with bounds on the operands' total degrees (negative: not known,

@@ -151,6 +151,34 @@ struct MulDenseArgs {
     double tol;
     int32_t *status;
 };
+
+// simplify by monomial ranks (segrank.hip)
+struct SegRankArgs {
+    int n, D, max_exp;          // variables, degree and exponent bounds of the terms
+    uint32_t cells;             // C(n + D, n)
+    int rank_bits;              // of cells - 1
+    const int64_t *rp;
+    const uint8_t *exps;
+    const double *coefs;
+    const int64_t *order;       // polynomials by decreasing size
+    const uint32_t *table;      // as in MulDenseArgs
+    const uint32_t *pairs;
+    uint32_t *st_rank;          // kept runs, from their polynomial's first term on
+    double *st_coef;
+    int64_t *seg_count;
+    double tol;
+    int32_t *status;
+};
+constexpr int SR_MAX_N = 128;               // rows of 64 terms for each wave in LDS
+constexpr int64_t SR_MAX_TERMS = 20480;     // of a polynomial: six bytes each in LDS
+constexpr size_t SR_TABLE_MAX = 16384;      // bytes of the pair table
+// one workgroup per polynomial order[first + blockIdx.x] of at most THREADS * ITEMS terms
+// (passes of DB bits)
+template <int THREADS, int ITEMS, int DB>
+__global__ void k_sr_merge(SegRankArgs A, int64_t first);
+__global__ void k_sr_unpack(SegRankArgs A, int64_t P, const int64_t *__restrict__ row_ptr, uint8_t *out_exps, double *out_coefs,
+                            int64_t capacity);
+// product on a dense range (muldense.hip)
 __global__ void k_max_degree(const uint8_t *ea, int64_t Ta, const uint8_t *eb, int64_t Tb, int n, uint32_t *deg,
                              int64_t *host);
 __global__ void k_read_back(const int32_t *status, const int64_t *row_ptr, int64_t count, int64_t *host);

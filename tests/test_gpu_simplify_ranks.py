@@ -1,0 +1,58 @@
+"""simplify of large batches of low degree (sorted by monomial rank in LDS), bit
+for bit against the general path, which finish=False takes, and the oracle: at
+the polynomial sizes where the workgroup changes, with runs longer than a round,
+one monomial only, rows that are no whole words, and just past the sizes,
+degrees and variables that the rank path takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2604_06575_amd as ph
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [0, 1, 2, 64, 65, 255, 256, 257, 1023, 0, 1024, 1025, 8191, 8192, 8193, 20479, 20480, 3]
+
+
+def _batch(rng, n, d, sizes):
+    T = sum(sizes)
+    f = rng.integers(0, n + 1, size=(T, d))
+    e = np.zeros((T, n + 1), np.uint8)
+    np.add.at(e, (np.arange(T)[:, None], f), 1)
+    c = rng.integers(-3, 4, T) * rng.choice([1.0, 0.1, 1e16, -0.0], T)
+    return np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64), np.ascontiguousarray(e[:, :n]), c
+
+
+@pytest.mark.parametrize("n,d,sizes", [
+    (20, 6, EDGES), (7, 3, EDGES), (2, 3, EDGES), (3, 0, EDGES), (1, 40, EDGES), (9, 12, EDGES), (128, 3, EDGES),
+    (20, 6, [20481] + EDGES), (129, 2, EDGES), (24, 9, EDGES), (5, 60, EDGES), (20, 6, [30] * 3000),
+])
+def test_simplify_ranks(n, d, sizes):
+    rng = np.random.default_rng(1000 * n + d + len(sizes))
+    rp, e, c = _batch(rng, n, d, sizes)
+    b = ph.batch_from_numpy(rp, e, c)
+    for tol in (0.0, 0.25):
+        got = ph.simplify(b, tol)
+        g = ph.simplify(b, tol, finish=False)
+        torch.cuda.synchronize()
+        assert torch.equal(got.row_ptr, g.row_ptr)
+        T = got.nterms
+        assert torch.equal(got.exps, g.exps[:T])
+        assert torch.equal(got.coefs.view(torch.int64), g.coefs[:T].view(torch.int64))
+    if n in (2, 7):
+        orp, oe, oc = oracle.simplify_batch(rp, e, c, 0.25, n=n)
+        grp, ge, gc = ph.batch_to_numpy(got)
+        assert np.array_equal(grp, orp) and np.array_equal(ge, oe)
+        assert np.array_equal(gc.view(np.uint64), np.asarray(oc).view(np.uint64))
+
+
+def test_capacity_and_exponent_status():
+    rng = np.random.default_rng(5)
+    rp, e, c = _batch(rng, 6, 4, [40000 // 2] * 4)
+    b = ph.batch_from_numpy(rp, e, np.abs(c) + 1)
+    small = ph.batch_from_numpy(np.zeros(5, np.int64), np.zeros((7, 6), np.uint8), np.zeros(7), n=6, max_exp=4)
+    with pytest.raises(ph.PolyError):
+        ph.simplify(b, out=small)
+    with pytest.raises(ph.PolyError):
+        ph.simplify(ph.batch_from_numpy(rp, e, c, n=6, max_exp=3))
