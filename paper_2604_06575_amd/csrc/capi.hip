@@ -706,6 +706,9 @@ void ensure_lds_attrs()
     for (const void *f : {(const void *)k_sr_merge<1024, 20, 7>, (const void *)k_sr_merge<1024, 20, 9>,
                           (const void *)k_sr_merge<512, 16, 7>, (const void *)k_sr_merge<512, 16, 9>})
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+    for (const void *f : {(const void *)k_backward_dc_reg<24>, (const void *)k_backward_dc_reg<56>,
+                          (const void *)k_backward_dc_reg<113>})
+        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 8192);
     (void)hipFuncSetAttribute((const void *)k_backward_dc, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     (void)hipFuncSetAttribute((const void *)k_backward2_dc, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     (void)hipFuncSetAttribute((const void *)k_hess_transpose, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
@@ -2580,7 +2583,7 @@ struct BackwardPlan {
     GradPlan g;             // dX from the formed Jacobian
     size_t senc = 0, part = 0;   // dC
     int cp = 0;
-    int64_t nchunks = 0;
+    int64_t nchunks = 0, tiles = 0;   // point chunks of the dC kernels
 };
 
 static BackwardPlan plan_backward(const poly_csr *f, int64_t N, Layout &L)
@@ -2595,10 +2598,11 @@ static BackwardPlan plan_backward(const poly_csr *f, int64_t N, Layout &L)
     } else {
         b.g = plan_grad_formed(f, N, L, true);
     }
-    b.senc = L.take(16 * T);   // factor lists of the dC kernel
+    b.senc = L.take(factor_bytes(n, T));   // factor lists of the dC kernel
     b.cp = std::max(1, std::min(BWC_POINTS, 8192 / (n + 1)));
     b.nchunks = ceil_div(N, b.cp);
-    b.part = L.take(8 * T * b.nchunks);
+    b.tiles = n <= RE_MAX_N ? ceil_div(N, kWave * regeval_points(regeval_rows(n))) : 0;
+    b.part = L.take(8 * T * std::max(b.nchunks, b.tiles));
     return b;
 }
 
@@ -2627,23 +2631,47 @@ static Backward2Plan plan_backward2(const poly_csr *f, int64_t N, Layout &L)
 }
 
 // dC[t] = sum_pt gY[p(t)][pt] m_t(x_pt) over point chunks, then in chunk order
-static void launch_dc(const poly_csr *f, const double *X, int64_t N, const double *gY, double *dC, uint64_t *senc,
-               double *part, int cp, int64_t nchunks, hipStream_t s)
+static void launch_dc(const poly_csr *f, const double *X, int64_t N, const double *gY, double *dC, void *ws,
+                      const BackwardPlan &b, hipStream_t s)
 {
-    const int n = f->nvars;
-    const int64_t P = f->npolys, T = total_terms(f);
+    const int n = f->nvars, cp = b.cp;
+    const int64_t P = f->npolys, T = total_terms(f), nchunks = b.nchunks;
+    uint32_t *senc = at<uint32_t>(ws, b.senc);
+    double *part = at<double>(ws, b.part);
     if (T <= 0) return;
     if (N == 0) {
         clear_u64((unsigned long long *)dC, T, s);
         return;
     }
-    hipLaunchKernelGGL(k_encode_factors, dim3(grid1(T, 256)), dim3(256), 0, s, f->exps, T, n, (uint32_t *)senc,
-                       (const int64_t *)nullptr, (uint32_t *)nullptr);
+    // segments of at least 512 terms, about four for each resident wave
+    const int64_t S = std::max<int64_t>(1, std::min(ceil_div((int64_t)8192, std::max<int64_t>(P * b.tiles, 1)), T / (P * 512)));
+    EvalArgs A;
+    memset(&A, 0, sizeof(A));
+    A.rp = f->row_ptr;
+    A.n = n;
+    A.X = X;
+    A.N = N;
+    A.Q = P;
+    A.term_limit = T;
+    A.ranges = P * S;
+    A.words_cap = word_plane(T);
+    const bool reg = regeval_pays(n, 8, T, A.ranges, N);   // at any degree class
+    if (reg) A.maxdeg = at<uint32_t>(ws, 8);
+    hipLaunchKernelGGL(k_encode_factors, dim3(grid1(T, 256)), dim3(256), 0, s, f->exps, T, n, senc,
+                       (const int64_t *)nullptr, reg ? at<uint32_t>(ws, 8) : nullptr,
+                       reg ? factor_words(senc, n, T) : nullptr);
+    if (reg)
+        with_regeval_rows(n, [&](auto nr) {
+            constexpr int NR = decltype(nr)::value;
+            hipLaunchKernelGGL((k_backward_dc_reg<NR>), regeval_grid(N, NR, P * S), dim3(EV_THREADS),
+                               regeval_lds(NR) + EV_WAVES * RD_BUF * sizeof(double), s, A, (const uint32_t *)senc,
+                               (const uint32_t *)factor_words(senc, n, T), gY, T, S, part);
+        });
     const size_t lds = (size_t)cp * (n + 1) * sizeof(double);
     hipLaunchKernelGGL(k_backward_dc, dim3(grid1(T, BWC_TERMS * BWC_THREADS), (unsigned)nchunks), dim3(BWC_THREADS),
-                       lds, s, f->row_ptr, P, f->exps, n, T, X, N, gY, part, nchunks, (const uint4 *)senc, cp);
+                       lds, s, f->row_ptr, P, f->exps, n, T, X, N, gY, part, nchunks, (const uint4 *)senc, cp, A);
     hipLaunchKernelGGL(k_backward_dc_reduce, dim3(grid1(T, 256)), dim3(256), 0, s, (const double *)part, T, nchunks,
-                       dC);
+                       dC, A, b.tiles);
 }
 
 }  // namespace
@@ -2712,7 +2740,7 @@ poly_status poly_eval_backward(const poly_csr *f, const double *X, int64_t N, co
     if (!ws || ws_bytes < L.total()) return POLY_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     ensure_lds_attrs();
-    clear_u64(at<unsigned long long>(ws, 0), 1, s);
+    clear_u64(at<unsigned long long>(ws, 0), 2, s);   // status, degree classes of the formed and of the given terms
     if (P == 0) {
         LAUNCH_CHECK();
         return POLY_OK;
@@ -2731,7 +2759,7 @@ poly_status poly_eval_backward(const poly_csr *f, const double *X, int64_t N, co
             if (st != POLY_OK) return st;
         }
     }
-    if (dC) launch_dc(f, X, N, gY, dC, at<uint64_t>(ws, b.senc), at<double>(ws, b.part), b.cp, b.nchunks, s);
+    if (dC) launch_dc(f, X, N, gY, dC, ws, b, s);
     LAUNCH_CHECK();
     return POLY_OK;
 }
@@ -2809,8 +2837,10 @@ poly_status poly_eval_backward2(const poly_csr *f, const double *X, int64_t N, c
             const size_t lds = 2 * (size_t)b.cp * n * sizeof(double);
             hipLaunchKernelGGL(k_backward2_dc, dim3(grid1(T, BWC_THREADS), (unsigned)b.nchunks), dim3(BWC_THREADS),
                                lds, s, f->row_ptr, P, f->exps, n, T, X, u, N, gY, part, (const uint64_t *)senc, b.cp);
+            EvalArgs none;
+            memset(&none, 0, sizeof(none));
             hipLaunchKernelGGL(k_backward_dc_reduce, dim3(grid1(T, 256)), dim3(256), 0, s, (const double *)part, T,
-                               b.nchunks, ggC);
+                               b.nchunks, ggC, none, (int64_t)0);
         }
     }
     LAUNCH_CHECK();

@@ -811,6 +811,73 @@ __global__ void __launch_bounds__(256) k_eval_reduce(EvalArgs A, const double *p
 
 // --------------------------------------------------------------- backward
 
+// Partial dC over a tile of points with the coordinates in registers
+// (regeval.h): lanes are points, a wave takes segments of a polynomial's terms
+// and leaves one sum per term and tile in partial[tile][T].  Bound by the
+// issue of vector instructions.  A quartic of 100,000 terms in 100 variables,
+// 8,192 points: 332 us; lanes as terms, which gather coordinates from LDS with
+// bank conflicts, 830.  Dynamic LDS: the tile, then RD_BUF doubles per wave.
+template <int NR>
+__global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
+    k_backward_dc_reg(EvalArgs A, const uint32_t *__restrict__ enc, const uint32_t *__restrict__ words,
+                      const double *gY, int64_t T, int64_t S, double *partial)
+{
+    constexpr int PT = regeval_points(NR);
+    extern __shared__ double s_x[];
+    uint32_t md;
+    if (!eval_form_runs<NR>(A, md)) return;
+    const int lane = lane_id(), w = wave_id();
+    const int64_t pt0 = (int64_t)blockIdx.x * (kWave * PT);
+    stage_points<NR>(A, pt0, s_x);
+    const double *xl = s_x + lane;
+    const uint32_t xa = lds_address(xl);
+    const uint32_t buf = lds_address(s_x + NR * PT * kWave + w * RD_BUF);
+    double *out = partial + (int64_t)blockIdx.x * T;
+    const int64_t units = A.Q * S;
+    for (int64_t u = (int64_t)blockIdx.y * EV_WAVES + w; u < units; u += (int64_t)gridDim.y * EV_WAVES) {
+        const int64_t p = u / S, sg = u % S;
+        const int64_t r0 = A.rp[p], r1 = A.rp[p + 1] < A.term_limit ? A.rp[p + 1] : A.term_limit;
+        const int64_t len = r1 > r0 ? r1 - r0 : 0, step = (len + 64 * S - 1) / (64 * S) * 64;
+        int64_t ta = uniform_i64(r0 + step * sg);
+        const int64_t tb = uniform_i64(r0 + (step * (sg + 1) < len ? step * (sg + 1) : len));
+        if (ta >= tb) continue;
+        double g[PT];
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int64_t pt = pt0 + k * kWave + lane;
+            g[k] = pt < A.N ? gY[p * A.N + pt] : 0.0;
+        }
+        while (tb - ta >= 8) {
+            const uint32_t q = (uint32_t)((tb - ta) >> 3 < (1 << 20) ? (tb - ta) >> 3 : 1 << 20);
+            const uint32_t *wp = words + ta, *up = words + A.words_cap + ta;
+            if (md <= 2u) dc_octets<NR, 2>(out + ta, q, wp, up, xa, g, buf);
+            else if (md == 3u) dc_octets<NR, 3>(out + ta, q, wp, up, xa, g, buf);
+            else if (md == 4u) dc_octets<NR, 4>(out + ta, q, wp, up, xa, g, buf);
+            else if (md == 5u) dc_octets<NR, 5>(out + ta, q, wp, up, xa, g, buf);
+            else if (md == 6u) dc_octets<NR, 6>(out + ta, q, wp, up, xa, g, buf);
+            else dc_octets<NR, 8>(out + ta, q, wp, up, xa, g, buf);
+            ta += 8 * (int64_t)q;
+        }
+        for (; ta < tb; ++ta) {   // the last few, from the tile
+            const uint4 e = reinterpret_cast<const uint4 *>(enc)[ta];
+            double v = 0.0;
+#pragma unroll
+            for (int k = 0; k < PT; ++k) {
+                const double *x = xl + k * NR * kWave;
+                v += g[k] * chunk4(md > 4u ? chunk4(1.0, e.x, x) : 1.0, md > 4u ? e.y : e.x, x);
+            }
+            v = wave_sum(v);
+            if (lane == 0) out[ta] = v;
+        }
+    }
+}
+template __global__ void k_backward_dc_reg<24>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
+                                               int64_t, double *);
+template __global__ void k_backward_dc_reg<56>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
+                                               int64_t, double *);
+template __global__ void k_backward_dc_reg<113>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
+                                                int64_t, double *);
+
 // Partial dC over one chunk of points: lanes are terms.  Each lane holds its
 // term's factor list (k_encode_factors: up to EV_MAX_DEG variable indices,
 // padded with n, the index of the one that ends every point's coordinates in
@@ -819,13 +886,16 @@ __global__ void __launch_bounds__(256) k_eval_reduce(EvalArgs A, const double *p
 // words, degrees beyond EV_MAX_DEG the exponent row.  A thread takes
 // BWC_TERMS terms (BWC_THREADS apart) against one staging of the chunk.
 // grid: x = term blocks of BWC_TERMS * BWC_THREADS, y = point chunks.
+// Returns at once where k_backward_dc_reg runs (A; its sizes).
 // Dynamic LDS: cp * (n + 1) doubles, point-major.
 __global__ void __launch_bounds__(BWC_THREADS) k_backward_dc(const int64_t *rp, int64_t P, const uint8_t *exps,
                                                              int n, int64_t T, const double *X, int64_t N,
                                                              const double *gY, double *partial, int64_t nchunks,
-                                                             const uint4 *fenc, int cp)
+                                                             const uint4 *fenc, int cp, EvalArgs A)
 {
     extern __shared__ double s_xc[];
+    uint32_t md;
+    if (eval_form_runs<24>(A, md)) return;
     const int64_t c = blockIdx.y;
     const int64_t pt0 = c * cp;
     const int np = (int)((N - pt0) < cp ? (N - pt0) : cp);
@@ -879,8 +949,12 @@ __global__ void __launch_bounds__(BWC_THREADS) k_backward_dc(const int64_t *rp, 
     }
 }
 
-__global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC)
+// reg_tiles: the chunks where k_backward_dc_reg ran
+__global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC, EvalArgs A,
+                                     int64_t reg_tiles)
 {
+    uint32_t md;
+    if (eval_form_runs<24>(A, md)) nchunks = reg_tiles;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
     double s = partial[t];

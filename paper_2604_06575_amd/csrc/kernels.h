@@ -433,7 +433,11 @@ constexpr int BWC_POINTS = 512;   // points per chunk
 constexpr int BWC_TERMS = 4;      // terms per thread
 __global__ void k_backward_dc(const int64_t *rp, int64_t P, const uint8_t *exps, int n, int64_t T, const double *X,
                               int64_t N, const double *gY, double *partial, int64_t nchunks,
-                              const uint4 *fenc, int cp);
-__global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC);
+                              const uint4 *fenc, int cp, EvalArgs A);
+template <int NR>
+__global__ void k_backward_dc_reg(EvalArgs A, const uint32_t *__restrict__ enc, const uint32_t *__restrict__ words,
+                                  const double *gY, int64_t T, int64_t S, double *partial);
+__global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC, EvalArgs A,
+                                     int64_t reg_tiles);
 
 }  // namespace polyhip

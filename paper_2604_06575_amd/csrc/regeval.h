@@ -251,4 +251,122 @@ __device__ inline void term_octets(double (&acc)[regeval_points(NR)], uint32_t q
     }
 }
 
+// ---- one sum over points per term (dC), 64 terms at a time
+//
+// The products of four terms are weighted by the lane's point and added over
+// the wave down to 16 partial sums each, the four terms' in one register: two
+// exchanges of half waves (v_permlane32_swap) and one of rows of 16
+// (v_permlane16_swap), three additions.  The partial sums go to the wave's LDS
+// buffer, 17 doubles per term so that the reads meet no bank twice; after 64
+// terms each lane adds those of its own.  v[22:29] hold the products, v[30:31]
+// the first half of four terms at two points per lane.
+#define RD_SWAP(w, a, b) "v_permlane" w "_swap_b32 v" #a ", v" #b "\n"
+#define RD_OUT "ds_write_b64 %[wa], v[22:23] offset:544*re_q\n.set re_q, re_q+1\n"
+// v[22:23] = its own and v[24:25]'s sums over half waves
+#define RD_HALF "s_nop 1\n" RD_SWAP("32", 22, 24) RD_SWAP("32", 23, 25) "v_add_f64 v[22:23], v[22:23], v[24:25]\n"
+#define RD_LAST1                                                                                       \
+    "s_set_gpr_idx_off\nv_mul_f64 %[t0], %[t0], %[g0]\nv_mul_f64 %[t1], %[t1], %[g0]\n"                  \
+    "v_mul_f64 %[t2], %[t2], %[g0]\nv_mul_f64 %[t3], %[t3], %[g0]\n" RD_HALF                            \
+    RD_SWAP("32", 26, 28) RD_SWAP("32", 27, 29) "v_add_f64 v[26:27], v[26:27], v[28:29]\ns_nop 1\n"      \
+    RD_SWAP("16", 22, 26) RD_SWAP("16", 23, 27) "v_add_f64 v[22:23], v[22:23], v[26:27]\n" RD_OUT        \
+    ".set re_w, re_w+4\n.set re_u, re_u+4\n"
+#define RD_WEIGH2                                                                                      \
+    "s_set_gpr_idx_off\nv_mul_f64 %[t0], %[t0], %[g0]\nv_mul_f64 %[t2], %[t2], %[g0]\n"                  \
+    "v_fma_f64 v[22:23], v[24:25], %[g1], v[22:23]\nv_fma_f64 v[24:25], v[28:29], %[g1], v[26:27]\n" RD_HALF \
+    ".set re_w, re_w+2\n.set re_u, re_u+2\n"
+#define RD_FOUR1(C, X, Y) RE_LIST##C(1, X, Y) RD_LAST1
+#define RD_FOUR2(C, X, Y)                                                                              \
+    RE_LIST##C(2, X, Y) RD_WEIGH2 "v_mov_b32 v30, v22\nv_mov_b32 v31, v23\n" RE_LIST##C(2, X, Y) RD_WEIGH2 \
+    "s_nop 1\n" RD_SWAP("16", 30, 22) RD_SWAP("16", 31, 23) "v_add_f64 v[22:23], v[30:31], v[22:23]\n" RD_OUT
+#define RD_OCTET(C, P, X, Y) \
+    "s_sub_u32 %[q], %[q], 1\ns_cbranch_scc1 9f\n.rept 2\n" RD_FOUR##P(C, X, Y) ".endr\n"
+#define RD_SET_SHORT(C, P, X, Y, r, next)                                                              \
+    "s_waitcnt lgkmcnt(0)\ns_cmp_le_u32 %[q], 4\ns_cbranch_scc1 2f\n"                                    \
+    "s_add_u32 %[wo], %[wo], 128\ns_add_u32 %[wo2], %[wo2], 128\n" RE_LOAD_SHORT(next)                  \
+    "2:\n.set re_w, " #r "\n" RD_OCTET(C, P, X, Y) RD_OCTET(C, P, X, Y) RD_OCTET(C, P, X, Y) RD_OCTET(C, P, X, Y)
+#define RD_SET_LONG(C, P, X, Y, r, next)                                                               \
+    "s_waitcnt lgkmcnt(0)\ns_cmp_le_u32 %[q], 2\ns_cbranch_scc1 2f\n"                                    \
+    "s_add_u32 %[wo], %[wo], 64\n" RE_LOAD_LONG(next)                                                  \
+    "2:\n.set re_w, " #r "\n.set re_u, " #r "+16\n" RD_OCTET(C, P, X, Y) RD_OCTET(C, P, X, Y)
+#define RD_BATCH_SHORT(C, P, X, Y) RD_SET_SHORT(C, P, X, Y, 36, 68) RD_SET_SHORT(C, P, X, Y, 68, 36)
+#define RD_BATCH_LONG(C, P, X, Y)                                                                      \
+    RD_SET_LONG(C, P, X, Y, 36, 68) RD_SET_LONG(C, P, X, Y, 68, 36) RD_SET_LONG(C, P, X, Y, 36, 68)      \
+        RD_SET_LONG(C, P, X, Y, 68, 36)
+// the lane's 16 partial sums, in order, and the store of those within the range
+#define RD_READ(o)                                                                                     \
+    "ds_read_b64 v[22:23], %[ra] offset:" #o "\nds_read_b64 v[24:25], %[ra] offset:" #o "+8\n"           \
+    "ds_read_b64 v[26:27], %[ra] offset:" #o "+16\nds_read_b64 v[28:29], %[ra] offset:" #o "+24\n"       \
+    "s_waitcnt lgkmcnt(0)\n"
+#define RD_SUM \
+    "v_add_f64 %[acc], %[acc], v[22:23]\nv_add_f64 %[acc], %[acc], v[24:25]\nv_add_f64 %[acc], %[acc], v[26:27]\n" \
+    "v_add_f64 %[acc], %[acc], v[28:29]\n"
+#define RD_FLUSH                                                                                       \
+    "s_waitcnt lgkmcnt(0)\n" RD_READ(0)                             \
+    "v_add_f64 %[acc], v[22:23], v[24:25]\nv_add_f64 %[acc], %[acc], v[26:27]\n"                         \
+    "v_add_f64 %[acc], %[acc], v[28:29]\n" RD_READ(32) RD_SUM RD_READ(64) RD_SUM RD_READ(96) RD_SUM      \
+    "v_cmp_gt_u32 vcc, %[vend], %[vo]\ns_and_saveexec_b64 %[ex], vcc\n"                                  \
+    "global_store_dwordx2 %[vo], %[acc], %[op]\ns_mov_b64 exec, %[ex]\nv_add_u32 %[vo], 0x200, %[vo]\n"
+#define RD_G1 [g0] "v"(g[0])
+#define RD_G2 [g0] "v"(g[0]), [g1] "v"(g[1])
+#define RD_ASM(NR, P, base, X, Y, C, L, ...)                                                                \
+    asm volatile("s_mov_b32 %[m], m0\n" RE_LOAD_##L(36)                                                     \
+                 ".set re_i, 0\n.rept " #NR "*" #P "\n"                                                      \
+                 "ds_read_b64 v[" #base "+2*re_i:" #base "+1+2*re_i], %[xa] offset:512*re_i\n"               \
+                 ".set re_i, re_i+1\n.endr\n.set re_u, 0\n"                                                  \
+                 "1:\n.set re_q, 0\n" RD_BATCH_##L(C, P, X, Y) RD_FLUSH "s_branch 1b\n"                       \
+                 "9:\n" RD_FLUSH "s_waitcnt vmcnt(0) lgkmcnt(0)\ns_mov_b32 m0, %[m]\n"                        \
+                 : [t0] "=&{v[22:23]}"(t0), [t1] "=&{v[24:25]}"(t1), [t2] "=&{v[26:27]}"(t2),                \
+                   [t3] "=&{v[28:29]}"(t3), [acc] "=&v"(acc), [vo] "+v"(vo), [q] "+s"(q), [wo] "+s"(wo),     \
+                   [wo2] "+s"(wo2), [m] "=&s"(m0), [ex] "=&s"(ex)                                            \
+                 : [wp] "s"(wp), [up] "s"(up), [op] "s"(op), [xa] "v"(xa), [wa] "v"(wa), [ra] "v"(ra),       \
+                   [vend] "v"(vend), RD_G##P                                                                 \
+                 : "memory", "scc", "vcc", RE_SGPRS, __VA_ARGS__)
+
+// Doubles of a wave's buffer: 64 terms of 16 partial sums and a spare.
+constexpr int RD_BUF = 64 * 17;
+
+// out[t] = the sum over the wave's points p of g[p] * term t at p, for 8 q
+// terms (1 <= q < 2^23), coefficients left out.  buf: LDS byte address of the
+// wave's buffer.  The rest as in term_octets.
+template <int NR, int C>
+__device__ inline void dc_octets(double *out, uint32_t q, const uint32_t *wp, const uint32_t *up, uint32_t xa,
+                                 const double (&g)[regeval_points(NR)], uint32_t buf)
+{
+    wp = reinterpret_cast<const uint32_t *>(uniform_i64(reinterpret_cast<int64_t>(wp)));
+    up = reinterpret_cast<const uint32_t *>(uniform_i64(reinterpret_cast<int64_t>(up)));
+    double *op = reinterpret_cast<double *>(uniform_i64(reinterpret_cast<int64_t>(out)));
+    q = (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
+    double t0, t1, t2, t3, acc;
+    const uint32_t lane = (uint32_t)lane_id(), vend = 64u * q;
+    const uint32_t wa = buf + (lane >> 4) * 136u + (lane & 15u) * 8u, ra = buf + lane * 136u;
+    // the exchanges leave terms 0, 2, 1, 3 in the rows of 16
+    uint32_t vo = 8u * ((lane & ~3u) + ((lane & 1u) << 1) + ((lane >> 1) & 1u));
+    uint32_t wo = 0, wo2 = 64, m0;
+    uint64_t ex;
+    if constexpr (NR == 24) {
+        if constexpr (C == 2) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 2, SHORT, "v30", "v31", RE_VGPRS24);
+        if constexpr (C == 3) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 3, SHORT, "v30", "v31", RE_VGPRS24);
+        if constexpr (C == 4) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 4, SHORT, "v30", "v31", RE_VGPRS24);
+        if constexpr (C == 5) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 5, LONG, "v30", "v31", RE_VGPRS24);
+        if constexpr (C == 6) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 6, LONG, "v30", "v31", RE_VGPRS24);
+        if constexpr (C == 8) RD_ASM(24, 2, 32, "v[32:33]", "v[80:81]", 8, LONG, "v30", "v31", RE_VGPRS24);
+    }
+    if constexpr (NR == 56) {
+        if constexpr (C == 2) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 2, SHORT, "v30", "v31", RE_VGPRS56);
+        if constexpr (C == 3) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 3, SHORT, "v30", "v31", RE_VGPRS56);
+        if constexpr (C == 4) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 4, SHORT, "v30", "v31", RE_VGPRS56);
+        if constexpr (C == 5) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 5, LONG, "v30", "v31", RE_VGPRS56);
+        if constexpr (C == 6) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 6, LONG, "v30", "v31", RE_VGPRS56);
+        if constexpr (C == 8) RD_ASM(56, 2, 32, "v[32:33]", "v[144:145]", 8, LONG, "v30", "v31", RE_VGPRS56);
+    }
+    if constexpr (NR == 113) {
+        if constexpr (C == 2) RD_ASM(113, 1, 30, "v[30:31]", "", 2, SHORT, RE_VGPRS113);
+        if constexpr (C == 3) RD_ASM(113, 1, 30, "v[30:31]", "", 3, SHORT, RE_VGPRS113);
+        if constexpr (C == 4) RD_ASM(113, 1, 30, "v[30:31]", "", 4, SHORT, RE_VGPRS113);
+        if constexpr (C == 5) RD_ASM(113, 1, 30, "v[30:31]", "", 5, LONG, RE_VGPRS113);
+        if constexpr (C == 6) RD_ASM(113, 1, 30, "v[30:31]", "", 6, LONG, RE_VGPRS113);
+        if constexpr (C == 8) RD_ASM(113, 1, 30, "v[30:31]", "", 8, LONG, RE_VGPRS113);
+    }
+}
+
 }  // namespace polyhip

@@ -89,3 +89,22 @@ def test_dx(n, d):
         np.add.at(cnt, f[:, k], 1)
     got = gX.cpu().numpy().T[:, pts]
     assert np.all(np.abs(got - ref[:n]) <= (cnt[:n] + d + 5) * U * mag[:n])
+
+
+@pytest.mark.parametrize("n,d", CASES)
+def test_dc(n, d):
+    rng = np.random.default_rng(300 * n + d)
+    sizes = [0, 3, 20001, 64, 135, 9007]
+    f, e, rp, c = _batch(rng, n, d, sizes)
+    N, P = 2561, len(sizes)
+    X, gY = rng.uniform(-1, 1, (N, n)), rng.standard_normal((P, N))
+    b, x, g = ph.batch_from_numpy(rp, e, c), torch.from_numpy(X).cuda(), torch.from_numpy(gY).cuda()
+    _, dC = ph.eval_backward(b, x, g, want_dX=False, want_dC=True)
+    gX, dC2 = ph.eval_backward(b, x, g)
+    assert torch.equal(dC, dC2)
+    t = np.unique(np.concatenate([np.arange(300), rp[:-1], rp[1:-1] - 1, np.arange(rp[3] - 70, rp[3] + 70),
+                                  np.arange(rp[-1] - 130, rp[-1]), rng.integers(0, rp[-1], 300)]))
+    v = np.prod(_padded(X)[:, f[t]], axis=2)                             # [N, terms]
+    v = v * gY[np.searchsorted(rp, t, side="right") - 1].T
+    got = dC.cpu().numpy()[t]
+    assert np.all(np.abs(got - v.sum(0)) <= (N + d + 5) * U * np.abs(v).sum(0))
