@@ -260,6 +260,32 @@ __device__ inline const uint8_t *encode_row(const uint8_t *exps, int64_t lim, in
     return t < lim ? exps + t * n : nullptr;
 }
 
+// put(i, e) for the exponents e > 0 of a row, in variable order.  Eight at a
+// time: most are zero, and a loop over all of them waits for one LDS read
+// after another (100 variables, 100,000 terms of degree 4: 29 us against 17).
+template <class Put>
+__device__ inline void for_exponents(const uint8_t *row, int n, Put put)
+{
+    const bool words = ((n | (int)(uintptr_t)row) & 3) == 0;
+    for (int i0 = 0; i0 < n; i0 += 8) {
+        uint64_t x = 0;
+        if (words) {
+            const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row + i0);
+            x = r4[0];
+            if (i0 + 4 < n) x |= (uint64_t)r4[1] << 32;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + k < n) x |= (uint64_t)row[i0 + k] << (8 * k);
+        }
+        while (x) {
+            const int b = (__ffsll((long long)x) - 1) & ~7;
+            put(i0 + (b >> 3), (uint32_t)(x >> b) & 0xffu);
+            x &= ~(0xffull << b);
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) k_encode_support(const uint8_t *exps, int64_t T, int n, uint64_t *enc,
                                                         const int64_t *used)
 {
@@ -271,12 +297,12 @@ __global__ void __launch_bounds__(256) k_encode_support(const uint8_t *exps, int
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t w[2] = {0, 0};
     int s = 0;
-    for (int i = 0; i < n; ++i) {
-        const uint32_t e = row[i];
-        if (e == 0) continue;
-        if (s < 8) w[s >> 2] |= (uint64_t)(((e << 8) | (uint32_t)i) & 0xffffu) << (16 * (s & 3));
+    for_exponents(row, n, [&](int i, uint32_t e) {
+        const uint64_t x = (uint64_t)(((e << 8) | (uint32_t)i) & 0xffffu) << (16 * (s & 3));
+        if (s < 4) w[0] |= x;
+        else if (s < 8) w[1] |= x;
         ++s;
-    }
+    });
     if (s > 8) {
         w[0] = 0xffffull;
         w[1] = 0;
@@ -302,20 +328,28 @@ __global__ void __launch_bounds__(256) k_encode_factors(const uint8_t *exps, int
     const uint8_t *row = encode_row(exps, lim, n, s_rows);
     if (!row) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t w[4] = {0, 0, 0, 0};
-    int d = 0;
-    for (int i = 0; i < n && d <= EV_MAX_DEG; ++i) {
-        for (uint32_t e = row[i]; e > 0 && d <= EV_MAX_DEG; --e) {
-            if (d < EV_MAX_DEG) w[d >> 2] |= (uint32_t)i << (8 * (d & 3));
-            ++d;
+    uint64_t lo = 0;   // factors 0 to 7
+    uint32_t hi = 0;   // and 8 to 11
+    uint32_t d = 0;
+    for_exponents(row, n, [&](int i, uint32_t e) {
+        for (; e > 0 && d <= (uint32_t)EV_MAX_DEG; --e, ++d) {
+            if (d < 8) lo |= (uint64_t)i << (8 * d);
+            else if (d < (uint32_t)EV_MAX_DEG) hi |= (uint32_t)i << (8 * (d - 8));
         }
-    }
-    if (d > EV_MAX_DEG) {
+    });
+    uint32_t w[4];
+    if (d > (uint32_t)EV_MAX_DEG) {
         w[0] = w[1] = w[2] = 0;
         w[3] = 0xFFu;
     } else {
-        for (int k = d; k < EV_MAX_DEG; ++k) w[k >> 2] |= (uint32_t)n << (8 * (k & 3));
-        w[3] = (uint32_t)d;
+        const uint64_t pad = (uint64_t)n * 0x0101010101010101ull;
+        if (d < 8) lo |= pad & (~0ull << (8 * d));
+        const uint32_t k = d > 8 ? d - 8 : 0;
+        if (k < 4) hi |= (uint32_t)pad & (~0u << (8 * k));
+        w[0] = (uint32_t)lo;
+        w[1] = (uint32_t)(lo >> 32);
+        w[2] = hi;
+        w[3] = d;
     }
     uint4 *o = reinterpret_cast<uint4 *>(enc) + t;
     *o = make_uint4(w[0], w[1], w[2], w[3]);

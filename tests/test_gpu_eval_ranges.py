@@ -40,7 +40,8 @@ def _padded(X):
     return np.concatenate([X, np.ones((X.shape[0], 1))], axis=1).astype(np.longdouble)
 
 
-CASES = [(4, 8), (23, 2), (24, 3), (55, 4), (56, 5), (100, 6), (112, 4), (112, 7), (55, 8), (113, 4), (40, 9)]
+CASES = [(4, 8), (23, 2), (24, 3), (55, 4), (56, 5), (100, 6), (112, 4), (112, 7), (55, 8), (113, 4), (40, 9), (129, 3),
+         (200, 4)]
 
 
 @pytest.mark.parametrize("n,d", CASES)
