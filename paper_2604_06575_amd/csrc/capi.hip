@@ -574,12 +574,37 @@ inline dim3 eval_grid(int64_t N, int points, int64_t units, int64_t per_cu)
     const int64_t want = std::max<int64_t>(1, ((int64_t)device_cus() * per_cu + gx - 1) / gx);
     return dim3((unsigned)gx, (unsigned)std::min<int64_t>(std::min<int64_t>(ceil_div(units, EV_WAVES), want), 65535));
 }
-// The register forms': one or two workgroups are resident on a CU, and where
-// another kernel takes the batch each of them still has to start and end (at
-// 32 per CU, 14 us beside a call of 157).
-inline dim3 regeval_grid(int64_t N, int rows, int64_t units)
+// The register forms'.  At most 16 workgroups per CU: where another kernel
+// takes the batch each of them still has to start and end (at 32, 14 us beside
+// a call of 157; at 8, polynomials of unequal length were evaluated in 1,090
+// instead of 1,030 us).  One polynomial's units are of equal length: two
+// workgroups (one past 23 variables) are resident on a CU, the launch goes in
+// rounds, each as long as the staging of a tile and the ranges of one wave,
+// and as many workgroups are taken as fill one round, or two and so on,
+// whichever comes out shortest.  Clocks as measured: staging 16,000, a term 25
+// for each of a SIMD's waves.  (One quartic of 100,000 terms in 100 variables,
+// 8,192 points: 235 and 640 us for the values and the point gradients with a
+// workgroup for every eight units, 217 and 587.)
+inline dim3 regeval_grid(int64_t N, int rows, int64_t units, int64_t terms, bool equal)
 {
-    return eval_grid(N, kWave * regeval_points(rows), units, std::min<int64_t>(tunables().eval_blocks_per_cu, 16));
+    const int resident = rows == 24 ? 2 : 1;
+    const int64_t gx = ceil_div(N, kWave * regeval_points(rows)), slots = (int64_t)device_cus() * resident;
+    const int64_t most = std::min<int64_t>(ceil_div(units, EV_WAVES), 65535);
+    const double range = 2.0 * resident * 25.0 * (double)terms / (double)std::max<int64_t>(units, 1) + 3000.0;
+    const int64_t per_cu = std::min<int64_t>(tunables().eval_blocks_per_cu, 16);
+    int64_t gy = std::max<int64_t>(1, std::min(most, ceil_div(device_cus() * per_cu, gx)));
+    if (!equal) return dim3((unsigned)gx, (unsigned)gy);
+    int64_t chosen = gy;
+    double best = 0.0;
+    for (int64_t rounds = 16 / resident; rounds >= 1; --rounds) {
+        const int64_t g = std::max<int64_t>(1, std::min(gy, rounds * slots / gx));
+        const double cost = (double)ceil_div(gx * g, slots) * (16000.0 + (double)ceil_div(units, g * EV_WAVES) * range);
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            chosen = g;
+        }
+    }
+    return dim3((unsigned)gx, (unsigned)chosen);
 }
 inline size_t regeval_lds(int rows) { return (size_t)rows * regeval_points(rows) * kWave * sizeof(double); }
 
@@ -596,7 +621,7 @@ void launch_eval_blocks(EvalArgs A, uint32_t *enc, int64_t cap, bool exact, doub
     if (A.maxdeg && regeval_pays(A.n, 8, cap, A.ranges, A.N))   // at any degree class
         with_regeval_rows(A.n, [&](auto nr) {
             constexpr int NR = decltype(nr)::value;
-            hipLaunchKernelGGL((k_eval_terms_reg<NR>), regeval_grid(A.N, NR, A.Q * S),
+            hipLaunchKernelGGL((k_eval_terms_reg<NR>), regeval_grid(A.N, NR, A.Q * S, exact ? cap : cap / 2, A.Q == 1),
                                dim3(EV_THREADS), regeval_lds(NR), s, A, (const uint32_t *)enc, A.coefs,
                                (const uint32_t *)factor_words(enc, A.n, cap), partial, S);
         });
@@ -998,7 +1023,7 @@ poly_status run_wsum(const poly_csr *f, const double *X, int64_t N, const double
     if (regeval_pays(n, 8, g.cap, A.ranges, N))
         with_regeval_rows(n, [&](auto nr) {
             constexpr int NR = decltype(nr)::value;
-            hipLaunchKernelGGL((k_eval_wsum_reg<NR>), regeval_grid(N, NR, units),
+            hipLaunchKernelGGL((k_eval_wsum_reg<NR>), regeval_grid(N, NR, units, g.cap / 2, f->npolys == 1),
                                dim3(EV_THREADS), regeval_lds(NR), s, A, (const uint32_t *)jenc, A.coefs,
                                (const uint32_t *)factor_words(jenc, n, g.cap), gY, f->npolys, g.S, dX, part);
         });
@@ -2663,7 +2688,7 @@ static void launch_dc(const poly_csr *f, const double *X, int64_t N, const doubl
     if (reg)
         with_regeval_rows(n, [&](auto nr) {
             constexpr int NR = decltype(nr)::value;
-            hipLaunchKernelGGL((k_backward_dc_reg<NR>), regeval_grid(N, NR, P * S), dim3(EV_THREADS),
+            hipLaunchKernelGGL((k_backward_dc_reg<NR>), regeval_grid(N, NR, P * S, T, P == 1), dim3(EV_THREADS),
                                regeval_lds(NR) + EV_WAVES * RD_BUF * sizeof(double), s, A, (const uint32_t *)senc,
                                (const uint32_t *)factor_words(senc, n, T), gY, T, S, part);
         });
