@@ -640,27 +640,33 @@ __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__rest
     const int lane = lane_id();
     const int w = wave_id();
     const int64_t pt0 = (int64_t)blockIdx.x * (kWave * form_points<FORM>);
-    stage_points<FORM>(A, pt0, s_x);
-    const double *xl = s_x + lane;
     int vz;   // a zero the compiler treats as per-lane
     asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
     const int64_t units = A.Q * S;
     const int64_t ustride = (int64_t)gridDim.y * EV_WAVES;
     int64_t u = (int64_t)blockIdx.y * EV_WAVES + w;
-    if (u >= units) return;
-    int64_t r0 = A.rp[u / S + vz], r1 = A.rp[u / S + 1 + vz];
+    // polynomial of a unit; the first one's offsets are loaded behind the staging
+    const bool small = units < ((int64_t)1 << 31);
+    auto poly = [&](int64_t x) { return S == 1 ? x : (small ? (int64_t)((uint32_t)x / (uint32_t)S) : x / S); };
+    int64_t r0 = 0, r1 = 0;
+    if (u < units) {
+        r0 = A.rp[poly(u) + vz];
+        r1 = A.rp[poly(u) + 1 + vz];
+    }
+    stage_points<FORM>(A, pt0, s_x);
+    const double *xl = s_x + lane;
     for (; u < units; u += ustride) {
         const int64_t un = u + ustride;
         int64_t n0 = 0, n1 = 0;
         if (un < units) {
-            n0 = A.rp[un / S + vz];
-            n1 = A.rp[un / S + 1 + vz];
+            n0 = A.rp[poly(un) + vz];
+            n1 = A.rp[poly(un) + 1 + vz];
         }
-        const int64_t q = u / S, sg = u % S;
+        const int64_t q = poly(u), sg = u - q * S;
         const int64_t b0 = r0;
         const int64_t b1 = r1 < A.term_limit ? r1 : A.term_limit;
         const int64_t len = b1 > b0 ? b1 - b0 : 0;
-        const int64_t sa = b0 + len * sg / S, sb = b0 + len * (sg + 1) / S;
+        const int64_t sa = S == 1 ? b0 : b0 + len * sg / S, sb = S == 1 ? b0 + len : b0 + len * (sg + 1) / S;
         double acc[form_points<FORM>];
         range_of_form<FORM>(A, md, enc, coefs, words, sa, sb, xl, acc);
 #pragma unroll
