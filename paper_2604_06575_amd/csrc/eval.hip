@@ -266,23 +266,27 @@ __device__ inline const uint8_t *encode_row(const uint8_t *exps, int64_t lim, in
 template <class Put>
 __device__ inline void for_exponents(const uint8_t *row, int n, Put put)
 {
-    const bool words = ((n | (int)(uintptr_t)row) & 3) == 0;
-    for (int i0 = 0; i0 < n; i0 += 8) {
-        uint64_t x = 0;
-        if (words) {
-            const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row + i0);
-            x = r4[0];
-            if (i0 + 4 < n) x |= (uint64_t)r4[1] << 32;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (i0 + k < n) x |= (uint64_t)row[i0 + k] << (8 * k);
-        }
+    auto four = [&](uint32_t x, int i) {
         while (x) {
-            const int b = (__ffsll((long long)x) - 1) & ~7;
-            put(i0 + (b >> 3), (uint32_t)(x >> b) & 0xffu);
-            x &= ~(0xffull << b);
+            const int b = (__ffs((int)x) - 1) & 24;
+            put(i + (b >> 3), (x >> b) & 0xffu);
+            x &= ~(0xffu << b);
         }
+    };
+    if (((n | (int)(uintptr_t)row) & 3) == 0) {
+        for (int i0 = 0; i0 < n; i0 += 8) {
+            const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row + i0);
+            const uint32_t x = r4[0], y = i0 + 4 < n ? r4[1] : 0;
+            four(x, i0);
+            four(y, i0 + 4);
+        }
+    } else {
+        int i0 = 0;
+        for (; i0 + 4 <= n; i0 += 4)
+            four((uint32_t)row[i0] | (uint32_t)row[i0 + 1] << 8 | (uint32_t)row[i0 + 2] << 16 | (uint32_t)row[i0 + 3] << 24,
+                 i0);
+        for (; i0 < n; ++i0)
+            if (row[i0]) put(i0, row[i0]);
     }
 }
 
@@ -328,27 +332,26 @@ __global__ void __launch_bounds__(256) k_encode_factors(const uint8_t *exps, int
     const uint8_t *row = encode_row(exps, lim, n, s_rows);
     if (!row) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint64_t lo = 0;   // factors 0 to 7
-    uint32_t hi = 0;   // and 8 to 11
+    uint32_t w[4] = {0, 0, 0, 0};
     uint32_t d = 0;
     for_exponents(row, n, [&](int i, uint32_t e) {
         for (; e > 0 && d <= (uint32_t)EV_MAX_DEG; --e, ++d) {
-            if (d < 8) lo |= (uint64_t)i << (8 * d);
-            else if (d < (uint32_t)EV_MAX_DEG) hi |= (uint32_t)i << (8 * (d - 8));
+            const uint32_t x = (uint32_t)i << (8 * (d & 3));
+            w[0] |= d < 4 ? x : 0u;
+            w[1] |= (d >> 2) == 1 ? x : 0u;
+            w[2] |= (d >> 2) == 2 ? x : 0u;
         }
     });
-    uint32_t w[4];
     if (d > (uint32_t)EV_MAX_DEG) {
         w[0] = w[1] = w[2] = 0;
         w[3] = 0xFFu;
     } else {
-        const uint64_t pad = (uint64_t)n * 0x0101010101010101ull;
-        if (d < 8) lo |= pad & (~0ull << (8 * d));
-        const uint32_t k = d > 8 ? d - 8 : 0;
-        if (k < 4) hi |= (uint32_t)pad & (~0u << (8 * k));
-        w[0] = (uint32_t)lo;
-        w[1] = (uint32_t)(lo >> 32);
-        w[2] = hi;
+        const uint32_t pad = (uint32_t)n * 0x01010101u;
+#pragma unroll
+        for (uint32_t k = 0; k < 3; ++k) {
+            const uint32_t have = d > 4 * k ? d - 4 * k : 0;   // factors in this word, if below four
+            if (have < 4) w[k] |= pad & (~0u << (8 * have));
+        }
         w[3] = d;
     }
     uint4 *o = reinterpret_cast<uint4 *>(enc) + t;
@@ -645,24 +648,25 @@ __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__rest
     const int64_t units = A.Q * S;
     const int64_t ustride = (int64_t)gridDim.y * EV_WAVES;
     int64_t u = (int64_t)blockIdx.y * EV_WAVES + w;
-    // polynomial of a unit; the first one's offsets are loaded behind the staging
-    const bool small = units < ((int64_t)1 << 31);
-    auto poly = [&](int64_t x) { return S == 1 ? x : (small ? (int64_t)((uint32_t)x / (uint32_t)S) : x / S); };
+    // unit u is segment sg of polynomial q, the next one dq polynomials and ds
+    // segments on; the first one's offsets are loaded behind the staging
+    int64_t q = u / S, sg = u - q * S;
+    const int64_t dq = ustride / S, ds = ustride - dq * S;
     int64_t r0 = 0, r1 = 0;
     if (u < units) {
-        r0 = A.rp[poly(u) + vz];
-        r1 = A.rp[poly(u) + 1 + vz];
+        r0 = A.rp[q + vz];
+        r1 = A.rp[q + 1 + vz];
     }
     stage_points<FORM>(A, pt0, s_x);
     const double *xl = s_x + lane;
     for (; u < units; u += ustride) {
-        const int64_t un = u + ustride;
+        const bool carry = sg + ds >= S;
+        const int64_t qn = q + dq + (carry ? 1 : 0), sn = sg + ds - (carry ? S : 0);
         int64_t n0 = 0, n1 = 0;
-        if (un < units) {
-            n0 = A.rp[poly(un) + vz];
-            n1 = A.rp[poly(un) + 1 + vz];
+        if (u + ustride < units) {
+            n0 = A.rp[qn + vz];
+            n1 = A.rp[qn + 1 + vz];
         }
-        const int64_t q = poly(u), sg = u - q * S;
         const int64_t b0 = r0;
         const int64_t b1 = r1 < A.term_limit ? r1 : A.term_limit;
         const int64_t len = b1 > b0 ? b1 - b0 : 0;
@@ -679,6 +683,8 @@ __device__ inline void eval_terms_body(const EvalArgs &A, const uint32_t *__rest
         }
         r0 = n0;
         r1 = n1;
+        q = qn;
+        sg = sn;
     }
 }
 
