@@ -50,13 +50,68 @@ __device__ inline int64_t item_poly(const int64_t *item_start, int64_t P, int64_
     return lo;
 }
 
-// multiplier of term row `row` of source polynomial p in group g (0 = the
-// term vanishes); the formed row is `row` with exponent g decremented
-__device__ inline int group_mult(const FormArgs &A, const uint8_t *row, int64_t p, int64_t g)
+// Up to eight of the variables from `from` on that have an exponent in a row,
+// one byte each, count in cnt; `from` moves behind the last one, to n or more
+// at the row's end.
+__device__ inline uint64_t next_vars(const uint8_t *row, int n, int &from, int &cnt)
 {
-    if (A.mode == 0) return row[g];
-    const int jj = (int)(p % A.n);
-    return g >= jj ? ((int)row[jj] + 1) * (int)row[g] : 0;
+    const bool words = ((n | (int)(uintptr_t)row) & 3) == 0;
+    uint64_t vars = 0;
+    cnt = 0;
+    for (int i0 = from & ~3; i0 < n && cnt < 8;) {
+        uint32_t x = 0;
+        if (words) {
+            x = *reinterpret_cast<const uint32_t *>(row + i0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + k < n) x |= (uint32_t)row[i0 + k] << (8 * k);
+        }
+        if (from > i0) x &= from - i0 < 4 ? ~0u << (8 * (from - i0)) : 0u;
+        while (x && cnt < 8) {
+            const int b = (__ffs((int)x) - 1) & 24;
+            from = i0 + (b >> 3);
+            vars |= (uint64_t)from << (8 * cnt);
+            ++from;
+            ++cnt;
+            x &= ~(0xffu << b);
+        }
+        if (!x) {
+            i0 += 4;
+            from = i0;
+        }
+    }
+    return vars;
+}
+
+// put(i, e) for the exponents e > 0 of a row, in variable order.  Eight at a
+// time: most are zero, and a loop over all of them waits for one LDS read
+// after another (100 variables, 100,000 terms of degree 4: 29 us against 17).
+template <class Put>
+__device__ inline void for_exponents(const uint8_t *row, int n, Put put)
+{
+    auto four = [&](uint32_t x, int i) {
+        while (x) {
+            const int b = (__ffs((int)x) - 1) & 24;
+            put(i + (b >> 3), (x >> b) & 0xffu);
+            x &= ~(0xffu << b);
+        }
+    };
+    if (((n | (int)(uintptr_t)row) & 3) == 0) {
+        for (int i0 = 0; i0 < n; i0 += 8) {
+            const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row + i0);
+            const uint32_t x = r4[0], y = i0 + 4 < n ? r4[1] : 0;
+            four(x, i0);
+            four(y, i0 + 4);
+        }
+    } else {
+        int i0 = 0;
+        for (; i0 + 4 <= n; i0 += 4)
+            four((uint32_t)row[i0] | (uint32_t)row[i0 + 1] << 8 | (uint32_t)row[i0 + 2] << 16 | (uint32_t)row[i0 + 3] << 24,
+                 i0);
+        for (; i0 < n; ++i0)
+            if (row[i0]) put(i0, row[i0]);
+    }
 }
 
 }  // namespace
@@ -101,6 +156,7 @@ __global__ void __launch_bounds__(JAC_THREADS) k_form_count(FormArgs A)
     const int64_t t0 = chunk * A.chunk;
     const int64_t t1 = t0 + A.chunk < T ? t0 + A.chunk : T;
     __shared__ uint32_t s_rows[JAC_THREADS * ROW_STAGE_MAX_N / 4];
+    const int first = A.mode ? (int)(p % A.n) : 0;   // a Hessian entry is formed for j <= k
     const int w = threadIdx.x >> 6;
     const bool staged = A.n <= ROW_STAGE_MAX_N;
     for (int i = threadIdx.x; i < (JAC_THREADS / kWave) * DF_MAX_GROUPS; i += JAC_THREADS) (&s_wc[0][0])[i] = 0;
@@ -115,11 +171,10 @@ __global__ void __launch_bounds__(JAC_THREADS) k_form_count(FormArgs A)
         }
         const uint8_t *row = staged ? reinterpret_cast<const uint8_t *>(s_rows) + threadIdx.x * A.n
                                     : A.exps + (base + t) * A.n;
-        for (int64_t g = 0; g < A.ngroups; ++g) {
-            const int m = t < t1 ? group_mult(A, row, p, g) : 0;
-            const unsigned long long bal = __ballot(m > 0);
-            if (lane_id() == 0) s_wc[w][g] += __popcll(bal);
-        }
+        if (t < t1)
+            for_exponents(row, A.n, [&](int g, uint32_t) {
+                if (g >= first) atomicAdd(&s_wc[w][g], 1);
+            });
     }
     __syncthreads();
     const int64_t cb = A.item_start[p] * A.ngroups;
@@ -145,10 +200,17 @@ __global__ void k_form_rowptr(FormArgs A, const int64_t *off)
     A.out_rp[idx] = off[A.item_start[p] * G + g * nch];
 }
 
+// The survivors of a group keep the source order.  A wave marks its lanes in
+// one mask per group, so a survivor's place is a count of bits, and takes the
+// lanes' first variables together, then their second ones, and so on: as many
+// steps as a term has variables (a ballot per group: 79 us for 100,000 terms
+// in 100 variables, 40).
 __global__ void __launch_bounds__(JAC_THREADS) k_form_write(FormArgs A, const int64_t *off)
 {
-    __shared__ int s_wc[JAC_THREADS / kWave][DF_MAX_GROUPS];
-    __shared__ uint8_t s_map[JAC_THREADS / kWave][kWave];   // survivor rank -> lane, per wave
+    constexpr int W = JAC_THREADS / kWave;
+    __shared__ unsigned long long s_mask[W][DF_MAX_GROUPS];
+    __shared__ int64_t s_out[W][kWave];       // a step's survivors: output slot,
+    __shared__ uint32_t s_from[W][kWave];     // lane and variable
     __shared__ int64_t s_run[DF_MAX_GROUPS];
     __shared__ uint32_t s_rows[JAC_THREADS * ROW_STAGE_MAX_N / 4];
     const int64_t item = blockIdx.x;
@@ -160,83 +222,88 @@ __global__ void __launch_bounds__(JAC_THREADS) k_form_write(FormArgs A, const in
     const int64_t T = A.rp[p + 1] - base;
     const int64_t t0 = chunk * A.chunk;
     const int64_t t1 = t0 + A.chunk < T ? t0 + A.chunk : T;
-    const int w = threadIdx.x >> 6;
+    const int w = wave_id();
     const int lane = lane_id();
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t cb = A.item_start[p] * A.ngroups;
     const int n = A.n;
+    const int first = A.mode ? (int)(p % n) : 0;
     const bool staged = n <= ROW_STAGE_MAX_N;
     const bool words = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(A.exps) | reinterpret_cast<uintptr_t>(A.out_exps)) & 3) == 0;
     for (int64_t g = threadIdx.x; g < A.ngroups; g += JAC_THREADS) s_run[g] = off[cb + g * nch + chunk];
-    __syncthreads();
     for (int64_t c0 = t0; c0 < t1; c0 += JAC_THREADS) {
         const int64_t t = c0 + threadIdx.x;
         const bool valid = t < t1;
         const int cnt = (int)(t1 - c0 < JAC_THREADS ? t1 - c0 : JAC_THREADS);
+        for (int g = lane; g < n; g += kWave) s_mask[w][g] = 0;
         if (staged) stage_rows(A.exps, base + c0, cnt, n, s_rows);
         const uint8_t *rows = staged ? reinterpret_cast<const uint8_t *>(s_rows) : A.exps + (base + c0) * n;
-        if (staged) __syncthreads();
+        __syncthreads();
         const uint8_t *row = rows + threadIdx.x * n;
-        for (int64_t g = 0; g < A.ngroups; ++g) {
-            const int m = valid ? group_mult(A, row, p, g) : 0;
-            const unsigned long long bal = __ballot(m > 0);
-            if (lane == 0) s_wc[w][g] = __popcll(bal);
-        }
+        if (valid)
+            for_exponents(row, n, [&](int g, uint32_t) {
+                if (g >= first) atomicOr(&s_mask[w][g], 1ull << lane);
+            });
         __syncthreads();
         const double c = valid ? A.coefs[base + t] : 0.0;
-        for (int64_t g = 0; g < A.ngroups; ++g) {
-            const int j = (int)g;
-            const int m = valid ? group_mult(A, row, p, g) : 0;
-            const unsigned long long bal = __ballot(m > 0);
-            if (bal == 0) continue;
-            // the wave's survivors take consecutive output slots from o0
-            int64_t o0 = s_run[g];
-            for (int q = 0; q < w; ++q) o0 += s_wc[q][g];
-            const int rank = __popcll(bal & lt);
-            const int nsurv = __popcll(bal);
-            if (m > 0) {
-                const int64_t o = o0 + rank;
-                if (o < A.capacity) A.out_coefs[o] = A.keep_coefs ? c : c * (double)m;
-                else set_status(A.status, A.overflow_code);
-                s_map[w][rank] = (uint8_t)lane;
-            }
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // their rows (exponent j decremented: it is >= 1 in a survivor) as
-            // one contiguous output run, lane by lane, rows past the capacity
-            // dropped
-            const int64_t keep = o0 >= A.capacity ? 0 : (A.capacity - o0 < nsurv ? A.capacity - o0 : nsurv);
-            if (words) {
-                const uint32_t nw = (uint32_t)n >> 2;
-                uint32_t *d32 = reinterpret_cast<uint32_t *>(A.out_exps + o0 * n);
-                for (uint32_t d = lane; d < (uint32_t)keep * nw; d += kWave) {
-                    const uint32_t r = d / nw, v = d - r * nw;
-                    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(rows + (w * kWave + s_map[w][r]) * n);
-                    uint32_t x = s32[v];
-                    if (v == (uint32_t)(j >> 2)) x -= 1u << (8 * (j & 3));
-                    d32[d] = x;
+        const int scale = valid && A.mode ? (int)row[first] + 1 : 1;
+        int from = valid ? first : n;
+        while (__ballot(from < n)) {
+            int have = 0;
+            uint64_t vars = from < n ? next_vars(row, n, from, have) : 0;
+            for (int k = 0;; ++k, vars >>= 8) {
+                const unsigned long long bal = __ballot(k < have);
+                if (bal == 0) break;
+                if (k < have) {
+                    const int j = (int)(vars & 0xffu);
+                    int64_t o = s_run[j] + __popcll(s_mask[w][j] & lt);
+                    for (int q = 0; q < w; ++q) o += __popcll(s_mask[q][j]);
+                    if (o < A.capacity) A.out_coefs[o] = A.keep_coefs ? c : c * (double)(scale * (int)row[j]);
+                    else set_status(A.status, A.overflow_code);
+                    const int at = __popcll(bal & lt);
+                    s_out[w][at] = o;
+                    s_from[w][at] = (uint32_t)lane | (uint32_t)j << 8;
                 }
-            } else {
-                uint8_t *d8 = A.out_exps + o0 * n;
-                for (uint32_t d = lane; d < (uint32_t)keep * (uint32_t)n; d += kWave) {
-                    const uint32_t r = d / (uint32_t)n, v = d - r * (uint32_t)n;
-                    const uint8_t *src = rows + (w * kWave + s_map[w][r]) * n;
-                    d8[d] = (uint8_t)(src[v] - (v == (uint32_t)j ? 1 : 0));
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                // the step's rows side by side (exponent j decremented: it is
+                // >= 1 in a survivor), rows past the capacity dropped
+                const uint32_t len = words ? (uint32_t)n >> 2 : (uint32_t)n, step = kWave / len, rest = kWave % len;
+                uint32_t at = (uint32_t)lane / len, v = (uint32_t)lane % len;
+                const uint32_t all = (uint32_t)__popcll(bal);
+                while (at < all) {
+                    const int64_t o = s_out[w][at];
+                    const uint32_t src = s_from[w][at], j = src >> 8;
+                    const uint8_t *sr = rows + (w * kWave + (int)(src & 0xffu)) * n;
+                    if (o < A.capacity) {
+                        if (words) {
+                            uint32_t x = reinterpret_cast<const uint32_t *>(sr)[v];
+                            if (v == (j >> 2)) x -= 1u << (8 * (j & 3));
+                            reinterpret_cast<uint32_t *>(A.out_exps + o * n)[v] = x;
+                        } else {
+                            A.out_exps[o * n + v] = (uint8_t)(sr[v] - (v == j ? 1 : 0));
+                        }
+                    }
+                    at += step;
+                    v += rest;
+                    if (v >= len) {
+                        v -= len;
+                        ++at;
+                    }
                 }
+                __builtin_amdgcn_wave_barrier();   // s_out is rewritten by the next step
             }
-            __builtin_amdgcn_wave_barrier();   // s_map is rewritten by the next group
         }
         __syncthreads();
         for (int64_t g = threadIdx.x; g < A.ngroups; g += JAC_THREADS) {
             int64_t sum = 0;
-            for (int q = 0; q < JAC_THREADS / kWave; ++q) sum += s_wc[q][g];
+            for (int q = 0; q < W; ++q) sum += __popcll(s_mask[q][g]);
             s_run[g] += sum;
         }
         __syncthreads();
     }
 }
-
 
 // ---------------------------------------------------------- support encoding
 
@@ -258,36 +325,6 @@ __device__ inline const uint8_t *encode_row(const uint8_t *exps, int64_t lim, in
         return t < lim ? reinterpret_cast<const uint8_t *>(s_rows) + threadIdx.x * n : nullptr;
     }
     return t < lim ? exps + t * n : nullptr;
-}
-
-// put(i, e) for the exponents e > 0 of a row, in variable order.  Eight at a
-// time: most are zero, and a loop over all of them waits for one LDS read
-// after another (100 variables, 100,000 terms of degree 4: 29 us against 17).
-template <class Put>
-__device__ inline void for_exponents(const uint8_t *row, int n, Put put)
-{
-    auto four = [&](uint32_t x, int i) {
-        while (x) {
-            const int b = (__ffs((int)x) - 1) & 24;
-            put(i + (b >> 3), (x >> b) & 0xffu);
-            x &= ~(0xffu << b);
-        }
-    };
-    if (((n | (int)(uintptr_t)row) & 3) == 0) {
-        for (int i0 = 0; i0 < n; i0 += 8) {
-            const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row + i0);
-            const uint32_t x = r4[0], y = i0 + 4 < n ? r4[1] : 0;
-            four(x, i0);
-            four(y, i0 + 4);
-        }
-    } else {
-        int i0 = 0;
-        for (; i0 + 4 <= n; i0 += 4)
-            four((uint32_t)row[i0] | (uint32_t)row[i0 + 1] << 8 | (uint32_t)row[i0 + 2] << 16 | (uint32_t)row[i0 + 3] << 24,
-                 i0);
-        for (; i0 < n; ++i0)
-            if (row[i0]) put(i0, row[i0]);
-    }
 }
 
 __global__ void __launch_bounds__(256) k_encode_support(const uint8_t *exps, int64_t T, int n, uint64_t *enc,
