@@ -306,13 +306,13 @@ poly_status poly_concat(const poly_csr *const *ins, int32_t nin, poly_csr *out, 
  *   D[pt*n + i] = (Q [A^-1 (h - |g| / (n + 1) a); -1])_i
  * (independent of the choice of Q_T; the regularization reg >= 0 enters
  * every tangent solve), and gnorm[pt] = |g| (gnorm may be NULL).
- * The gradient and Hessian come from the poly_grad / poly_hess paths; the
- * third-order term is contracted per monomial, so no n^3 tensor is formed.
+ * The gradient, the Hessian and the third-order term are summed per monomial
+ * from its factors, so no n^3 tensor is formed.
  * Terms of total degree above 12 are not supported (device status
  * POLY_ERR_UNSUPPORTED).  A singular regularized tangent block, or g = 0,
  * gives non-finite output for that point.  X [N*n] row-major; D [N*n].
- * Up to n = 128 each point's n x n work matrix lives in LDS; beyond, in the
- * point's Hessian slot of the workspace (the same results, HBM-bound). */
+ * Up to n = 129 each point's work matrix lives in LDS; beyond, in a slot of
+ * the workspace that its workgroup holds. */
 poly_status poly_affine_normal_workspace(const poly_csr *f, int64_t N, size_t *ws_bytes);
 poly_status poly_affine_normal(const poly_csr *f, const double *X, int64_t N, double reg,
                                double *D, double *gnorm, void *ws, size_t ws_bytes, void *stream);
