@@ -742,9 +742,9 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_terms_short(EvalArgs A, con
 // The same for batches of degree class <= 8 in at most RE_MAX_N variables,
 // coordinates in registers.  Bound by the issue of scalar and vector
 // instructions.  A quartic of 100,000 terms in 100 variables at 8,192 points
-// (one point a lane, 254 registers): 364 us from LDS, 227 us; gradients of 256
+// (one point a lane, 254 registers): 364 us from LDS, 215 us; gradients of 256
 // polynomials of degree 6 in 20 variables, 4.3 million derivative terms at
-// 1,000 points (two points a lane, 128 registers): 3,400 us, 1,033 us.
+// 1,000 points (two points a lane, 128 registers): 3,400 us, 1,000 us.
 template <int NR>
 __global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
     k_eval_terms_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
@@ -825,7 +825,7 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_wsum_short(EvalArgs A, cons
 }
 
 // The same for batches of degree class <= 8, coordinates in registers (the
-// quartic's 400,000 derivative terms: 1,118 us from LDS, 625 us).
+// quartic's 400,000 derivative terms: 1,118 us from LDS, 580 us).
 template <int NR>
 __global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
     k_eval_wsum_reg(EvalArgs A, const uint32_t *__restrict__ enc, const double *__restrict__ coefs,
@@ -898,7 +898,7 @@ __global__ void __launch_bounds__(256) k_eval_reduce(EvalArgs A, const double *p
 // (regeval.h): lanes are points, a wave takes segments of a polynomial's terms
 // and leaves one sum per term and tile in partial[tile][T].  Bound by the
 // issue of vector instructions.  A quartic of 100,000 terms in 100 variables,
-// 8,192 points: 332 us; lanes as terms, which gather coordinates from LDS with
+// 8,192 points: 325 us; lanes as terms, which gather coordinates from LDS with
 // bank conflicts, 830.  Dynamic LDS: the tile, then RD_BUF doubles per wave.
 template <int NR>
 __global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
