@@ -703,7 +703,10 @@ void run_form(const FormPlan &fp, FormArgs A, void *ws, hipStream_t s)
     hipLaunchKernelGGL(k_form_count, dim3((unsigned)fp.W), dim3(JAC_THREADS), 0, s, A);
     launch_scan(A.cnt, fp.W * fp.G, off, tmp, A.status, s);
     hipLaunchKernelGGL(k_form_rowptr, dim3(grid1(A.P * fp.G + 1, 256)), dim3(256), 0, s, A, (const int64_t *)off);
-    hipLaunchKernelGGL(k_form_write, dim3((unsigned)fp.W), dim3(JAC_THREADS), 0, s, A, (const int64_t *)off);
+    if (A.n >= FORM_MASKS_MIN)
+        hipLaunchKernelGGL(k_form_write_masks, dim3((unsigned)fp.W), dim3(JAC_THREADS), 0, s, A, (const int64_t *)off);
+    else
+        hipLaunchKernelGGL(k_form_write, dim3((unsigned)fp.W), dim3(JAC_THREADS), 0, s, A, (const int64_t *)off);
 }
 
 // --------------------------------------------------------- kernel timing

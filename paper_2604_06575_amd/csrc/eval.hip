@@ -50,6 +50,15 @@ __device__ inline int64_t item_poly(const int64_t *item_start, int64_t P, int64_
     return lo;
 }
 
+// multiplier of term row `row` of source polynomial p in group g (0 = the
+// term vanishes); the formed row is `row` with exponent g decremented
+__device__ inline int group_mult(const FormArgs &A, const uint8_t *row, int64_t p, int64_t g)
+{
+    if (A.mode == 0) return row[g];
+    const int jj = (int)(p % A.n);
+    return g >= jj ? ((int)row[jj] + 1) * (int)row[g] : 0;
+}
+
 // Up to eight of the variables from `from` on that have an exponent in a row,
 // one byte each, count in cnt; `from` moves behind the last one, to n or more
 // at the row's end.
@@ -200,12 +209,105 @@ __global__ void k_form_rowptr(FormArgs A, const int64_t *off)
     A.out_rp[idx] = off[A.item_start[p] * G + g * nch];
 }
 
-// The survivors of a group keep the source order.  A wave marks its lanes in
-// one mask per group, so a survivor's place is a count of bits, and takes the
-// lanes' first variables together, then their second ones, and so on: as many
-// steps as a term has variables (a ballot per group: 79 us for 100,000 terms
-// in 100 variables, 40).
+// The survivors of a group keep the source order: group by group, a ballot per
+// wave ranks them.  For few variables (FORM_MASKS_MIN).
 __global__ void __launch_bounds__(JAC_THREADS) k_form_write(FormArgs A, const int64_t *off)
+{
+    __shared__ int s_wc[JAC_THREADS / kWave][DF_MAX_GROUPS];
+    __shared__ uint8_t s_map[JAC_THREADS / kWave][kWave];   // survivor rank -> lane, per wave
+    __shared__ int64_t s_run[DF_MAX_GROUPS];
+    __shared__ uint32_t s_rows[JAC_THREADS * ROW_STAGE_MAX_N / 4];
+    const int64_t item = blockIdx.x;
+    const int64_t p = item_poly(A.item_start, A.P, item);
+    const int64_t nch = A.item_start[p + 1] - A.item_start[p];
+    const int64_t chunk = item - A.item_start[p];
+    if (chunk >= nch) return;   // grid larger than the work items (inconsistent host row_ptr)
+    const int64_t base = A.rp[p];
+    const int64_t T = A.rp[p + 1] - base;
+    const int64_t t0 = chunk * A.chunk;
+    const int64_t t1 = t0 + A.chunk < T ? t0 + A.chunk : T;
+    const int w = threadIdx.x >> 6;
+    const int lane = lane_id();
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int64_t cb = A.item_start[p] * A.ngroups;
+    const int n = A.n;
+    const bool staged = n <= ROW_STAGE_MAX_N;
+    const bool words = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(A.exps) | reinterpret_cast<uintptr_t>(A.out_exps)) & 3) == 0;
+    for (int64_t g = threadIdx.x; g < A.ngroups; g += JAC_THREADS) s_run[g] = off[cb + g * nch + chunk];
+    __syncthreads();
+    for (int64_t c0 = t0; c0 < t1; c0 += JAC_THREADS) {
+        const int64_t t = c0 + threadIdx.x;
+        const bool valid = t < t1;
+        const int cnt = (int)(t1 - c0 < JAC_THREADS ? t1 - c0 : JAC_THREADS);
+        if (staged) stage_rows(A.exps, base + c0, cnt, n, s_rows);
+        const uint8_t *rows = staged ? reinterpret_cast<const uint8_t *>(s_rows) : A.exps + (base + c0) * n;
+        if (staged) __syncthreads();
+        const uint8_t *row = rows + threadIdx.x * n;
+        for (int64_t g = 0; g < A.ngroups; ++g) {
+            const int m = valid ? group_mult(A, row, p, g) : 0;
+            const unsigned long long bal = __ballot(m > 0);
+            if (lane == 0) s_wc[w][g] = __popcll(bal);
+        }
+        __syncthreads();
+        const double c = valid ? A.coefs[base + t] : 0.0;
+        for (int64_t g = 0; g < A.ngroups; ++g) {
+            const int j = (int)g;
+            const int m = valid ? group_mult(A, row, p, g) : 0;
+            const unsigned long long bal = __ballot(m > 0);
+            if (bal == 0) continue;
+            // the wave's survivors take consecutive output slots from o0
+            int64_t o0 = s_run[g];
+            for (int q = 0; q < w; ++q) o0 += s_wc[q][g];
+            const int rank = __popcll(bal & lt);
+            const int nsurv = __popcll(bal);
+            if (m > 0) {
+                const int64_t o = o0 + rank;
+                if (o < A.capacity) A.out_coefs[o] = A.keep_coefs ? c : c * (double)m;
+                else set_status(A.status, A.overflow_code);
+                s_map[w][rank] = (uint8_t)lane;
+            }
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // their rows (exponent j decremented: it is >= 1 in a survivor) as
+            // one contiguous output run, lane by lane, rows past the capacity
+            // dropped
+            const int64_t keep = o0 >= A.capacity ? 0 : (A.capacity - o0 < nsurv ? A.capacity - o0 : nsurv);
+            if (words) {
+                const uint32_t nw = (uint32_t)n >> 2;
+                uint32_t *d32 = reinterpret_cast<uint32_t *>(A.out_exps + o0 * n);
+                for (uint32_t d = lane; d < (uint32_t)keep * nw; d += kWave) {
+                    const uint32_t r = d / nw, v = d - r * nw;
+                    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(rows + (w * kWave + s_map[w][r]) * n);
+                    uint32_t x = s32[v];
+                    if (v == (uint32_t)(j >> 2)) x -= 1u << (8 * (j & 3));
+                    d32[d] = x;
+                }
+            } else {
+                uint8_t *d8 = A.out_exps + o0 * n;
+                for (uint32_t d = lane; d < (uint32_t)keep * (uint32_t)n; d += kWave) {
+                    const uint32_t r = d / (uint32_t)n, v = d - r * (uint32_t)n;
+                    const uint8_t *src = rows + (w * kWave + s_map[w][r]) * n;
+                    d8[d] = (uint8_t)(src[v] - (v == (uint32_t)j ? 1 : 0));
+                }
+            }
+            __builtin_amdgcn_wave_barrier();   // s_map is rewritten by the next group
+        }
+        __syncthreads();
+        for (int64_t g = threadIdx.x; g < A.ngroups; g += JAC_THREADS) {
+            int64_t sum = 0;
+            for (int q = 0; q < JAC_THREADS / kWave; ++q) sum += s_wc[q][g];
+            s_run[g] += sum;
+        }
+        __syncthreads();
+    }
+}
+
+// The same for many variables: a wave marks its lanes in one mask per group, so
+// a survivor's place is a count of bits, and takes the lanes' first variables
+// together, then their second ones, and so on: as many steps as a term has
+// variables (a ballot per group: 79 us for 100,000 terms in 100 variables; 40).
+__global__ void __launch_bounds__(JAC_THREADS) k_form_write_masks(FormArgs A, const int64_t *off)
 {
     constexpr int W = JAC_THREADS / kWave;
     __shared__ unsigned long long s_mask[W][DF_MAX_GROUPS];

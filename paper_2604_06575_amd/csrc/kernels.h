@@ -230,6 +230,11 @@ __global__ void k_item_count(const int64_t *rp, int64_t P, int64_t chunk, int64_
 __global__ void k_form_count(FormArgs A);
 __global__ void k_form_rowptr(FormArgs A, const int64_t *off);
 __global__ void k_form_write(FormArgs A, const int64_t *off);
+__global__ void k_form_write_masks(FormArgs A, const int64_t *off);
+// variables from which on the masks are used: 7 variables, 10,000 terms of
+// degree 7: 10 us by ballots, 16 by masks; 20 variables, 740,000 terms of degree
+// 6: 84 and 79; 100 variables, 100,000 terms of degree 4: 79 and 40
+constexpr int FORM_MASKS_MIN = 17;
 
 // ----------------------------------------------------------------- sparse eval
 constexpr int EV_WAVES = 8;

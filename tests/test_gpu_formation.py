@@ -26,7 +26,7 @@ def _jacobian(rp, e, c):
     return np.cumsum(sizes), np.concatenate(E), np.concatenate(C)
 
 
-@pytest.mark.parametrize("n,most", [(1, 1), (3, 3), (8, 8), (9, 8), (12, 8), (66, 9), (100, 4), (128, 8), (130, 5), (255, 8)])
+@pytest.mark.parametrize("n,most", [(1, 1), (3, 3), (8, 8), (9, 8), (12, 8), (16, 9), (17, 9), (66, 9), (100, 4), (128, 8), (130, 5), (255, 8)])
 def test_formation(n, most):
     rng = np.random.default_rng(10 * n + most)
     sizes = [0, 1, 63, 65, 255, 256, 257, 0, 1030]
