@@ -186,8 +186,17 @@ __global__ void __launch_bounds__(256) k_md_sort(MulDenseArgs A, const int64_t *
         if (b > A.nr) return;
         uint64_t key = ~0ull;
         if (b < A.nr) {
+            // A product's exponents are below the radix, the range's first
+            // monomial's need not be: from one that is not, the key is the
+            // smallest above every product with the same leading exponents
+            // (that digit the radix, the later ones zero; at most radix^n).
             key = 0;
-            unrank((uint32_t)(b * A.cpr), A.n, A.D, A.table, [&](int, int e) { key = key * A.radix + (uint64_t)e; });
+            bool past = false;
+            unrank((uint32_t)(b * A.cpr), A.n, A.D, A.table, [&](int, int e) {
+                const uint64_t v = (uint64_t)e < A.radix ? (uint64_t)e : A.radix;
+                key = key * A.radix + (past ? 0 : v);
+                past = past || v == A.radix;
+            });
         }
         bounds[b] = key;
         return;
@@ -352,6 +361,7 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
         s_claim[c] = ~0u;
     }
     bool any = false;
+    bool outside = false;   // a product's cell is in another range: never, if the cuts are those of its keys
     for (int64_t r0 = 0; r0 < rows; r0 += SR) {
         // ---- rows of this step that meet the range, in row order
         const int64_t rb = r0 + tid * RB;
@@ -452,7 +462,8 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
 #pragma unroll
                 for (int u = 0; u < IT; ++u) {
                     const uint32_t c = A.cells - 1u - cell[u] - c0;
-                    cell[u] = c < A.cpr ? c : 0;   // past the range only where a row broke its bounds (status set)
+                    outside |= c >= A.cpr;
+                    cell[u] = c < A.cpr ? c : 0;
                 }
             }
             // ---- rounds: the earliest pending product of each cell is added.
@@ -482,6 +493,7 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
             } while (block_any<NT>(pend != 0));
         }
     }
+    if (outside) set_status(A.status, POLY_ERR_EXPONENT);
     __syncthreads();
     // ---- kept cells in order
     const uint32_t span = c1 - c0;

@@ -1,6 +1,9 @@
 """Products formed on a dense range of monomials (the route that mul and
 mtimes take once both operands' degrees are known): bit for bit the oracle's,
 and the general route's, at the edges of chunks, ranges and steps."""
+import itertools
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -110,3 +113,59 @@ def test_general_route_agrees():
     T = int(rp[-1])
     assert np.array_equal(rp, x.row_ptr_host)
     assert torch.equal(y.exps[:T], x.exps) and torch.equal(y.coefs[:T], x.coefs)
+
+
+def _capped(rng, n, d, cap, t):
+    """t distinct monomials of degree <= d with exponents <= cap; the largest
+    exponent and the largest degree are both met."""
+    e = np.zeros((0, n), np.uint8)
+    while len(e) < t:
+        u = np.zeros((4 * t, n), np.uint8)
+        for r in u:
+            for i in rng.integers(0, n, rng.integers(0, d + 1)):
+                r[i] = min(r[i] + 1, cap)
+        e = np.unique(np.concatenate([e, u]), axis=0)
+    e = e[rng.permutation(len(e))[:t]]
+    top = np.zeros(n, np.uint8)
+    for k in range(d):
+        top[k // cap] += 1
+    if not (e == top).all(axis=1).any():
+        e[0] = top
+    return e, rng.standard_normal(t)
+
+
+# Exponents bounded below the degree: a product key's radix, amax + bmax + 1,
+# is then at most the product's degree, and a range may begin at a monomial
+# that no product can be (keys as large as 3^16, 4^13, 5^9, 2^16).
+@pytest.mark.parametrize("n,d,amax,bmax,t", [
+    (7, 3, 1, 1, 64), (8, 3, 1, 1, 93), (10, 3, 1, 1, 150), (16, 3, 1, 1, 400), (11, 4, 1, 1, 350),
+    (8, 4, 1, 2, 150), (9, 3, 2, 1, 150), (5, 6, 2, 2, 130), (6, 5, 3, 1, 180), (13, 3, 1, 2, 300), (6, 4, 1, 0, 64),
+])
+def test_exponent_bounds_below_the_degree(n, d, amax, bmax, t):
+    rng = W.rng_for(74000 + 1000 * n + 100 * d + 10 * amax + bmax)
+    a = _capped(rng, n, d, amax, t if amax > 1 else min(t, sum(math.comb(n, k) for k in range(d + 1))))
+    if bmax:
+        b = _capped(rng, n, min(d, n * bmax), bmax, t if bmax > 1 else min(t, sum(math.comb(n, k) for k in range(d + 1))))
+    else:
+        b = np.zeros((t, n), np.uint8), rng.standard_normal(t)
+    e, c = oracle.mul(*a, *b)
+    _same(ph.mul(_batch([a], n, amax), _batch([b], n, bmax)), (np.array([0, len(c)]), e, c))
+
+
+def test_inferred_exponent_bounds():
+    """max_exp left to batch_from_numpy is the largest exponent: all 93
+    multilinear monomials of degree <= 3 in 8 variables, squared, as one pair,
+    as a batch and as a matrix product."""
+    rng = W.rng_for(74001)
+    n = 8
+    e = np.array([[1 if i in s else 0 for i in range(n)] for k in range(4) for s in itertools.combinations(range(n), k)],
+                 np.uint8)
+    polys = [(e, rng.standard_normal(len(e))) for _ in range(6)]
+    rp, ee, cc = W.csr_from_list(polys, n)
+    one = [ph.batch_from_numpy([0, len(e)], *p, n=n) for p in polys]
+    x, c = oracle.mul(*polys[0], *polys[1])
+    _same(ph.mul(one[0], one[1]), (np.array([0, len(c)]), x, c))
+    many = ph.batch_from_numpy(rp, ee, cc, n=n)
+    assert many.max_exp == 1
+    _same(ph.mul(many, many), W.csr_from_list([oracle.mul(*p, *p) for p in polys], n))
+    _same(ph.mtimes(many, many, 2, 3, 2), oracle.mtimes(rp, ee, cc, rp, ee, cc, 2, 3, 2))
