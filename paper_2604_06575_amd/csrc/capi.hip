@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <climits>
+#include <cmath>
 
 #include <algorithm>
 #include <atomic>
@@ -1499,6 +1500,32 @@ struct MulDensePlan {
     size_t ka, wa, kb, wb, kb_s, wb_s, cb_s, table, pairs, bounds, cut, count, out_off, tmp, st_cell, st_coef, total;
 };
 
+// Whether the route pays: its own costs in us against what the general route
+// costs beyond it.  The costs are those that do not come with the raw products:
+// every range looks at every row of its entry (7 ps each: 300,000 terms times
+// 4 in 10 variables, 280 ranges, 1,033 us; 312 by the general route), a right
+// operand's terms are sorted by counting (0.35 ps for each pair of them: 64
+// products of 10 by 10,000 terms 2,949 us; 1,336), and the products of a cell
+// are added one after another, which shows where no other entry's run beside
+// them (1 us for each, more with larger workgroups: 16 products of 50 by 50
+// terms into one entry of 1,001 cells, 193 us; 140).  Near the line: 64
+// products of 1 by 4,000 terms 602 / 661 us (not taken), 400 of 30 by 4,000
+// 3,255 / 5,337 (taken); 12,000 terms times 32 in 6 variables 189 / 222
+// (taken), 40,000 times 32 in 7 variables 284 / 256 (not taken).
+static bool dense_product_pays(const MulDensePlan &m, const poly_csr *b, int64_t left_rows, int64_t raw)
+{
+    double pairs = 0.0;
+    for (int64_t p = 0; p < b->npolys; ++p) {
+        const double t = (double)(b->row_ptr_host[p + 1] - b->row_ptr_host[p]);
+        pairs += t * t;
+    }
+    const double r = (double)raw;
+    double cost = 7e-6 * (double)m.nr * (double)left_rows + 0.35e-6 * pairs;
+    if (m.entries > 1) return cost <= 300.0 + 80e-6 * r;
+    cost += r / (double)m.cells * std::sqrt((double)m.threads / kWave);
+    return cost <= 30.0 + 25e-6 * r;
+}
+
 // The route is taken where it can be (few variables, keys of 63 bits, cell
 // numbers of 31, an entry's rows in LDS) and where an output entry is dense
 // enough: every cell is cleared, scanned and unpacked whether or not a product
@@ -1544,6 +1571,7 @@ static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t
     }
     m.nr = ceil_div(m.cells, (int64_t)m.cpr);
     m.ranges = m.entries * m.nr;
+    if (!dense_product_pays(m, b, left_rows, raw)) return m;
     m.kb_lds = b->npolys == 1;   // at most 128 KB
     m.lds = 12 * (size_t)m.cpr + 4 * pairs + 10 * (size_t)m.threads * MD_STEP_ROWS + 16;
     if (m.lds > MD_LDS_MAX || m.ranges >= (int64_t(1) << 31) || m.ranges * (int64_t)m.cpr > (int64_t(1) << 30) ||

@@ -1,0 +1,62 @@
+"""Which products are formed on a dense range of monomials: a rule on the
+operands' sizes and degrees that the host plans by.  The route shows in the
+workspace it asks for."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+
+import paper_2604_06575_amd as ph
+
+pytestmark = pytest.mark.skipif(not os.path.exists(ph.library_path()), reason="library not built")
+
+
+def _csr(n, max_exp, sizes):
+    rp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    c = ph.PolyCSR()
+    c.nvars, c.max_exp, c.npolys, c.capacity = n, max_exp, len(sizes), int(rp[-1])
+    c.row_ptr_host = rp.ctypes.data
+    c.row_ptr = c.exps = c.coefs = rp.ctypes.data   # planning looks at neither
+    c.keep = rp
+    return c
+
+
+def _bytes(n, da, db, sa, sb, mt=None):
+    """Workspace bytes with the degrees known and with them unknown."""
+    a, b = _csr(n, da, sa), _csr(n, db, sb)
+    out = []
+    for x, y in ((da, db), (-1, -1)):
+        ws, raw = ctypes.c_size_t(), ctypes.c_int64()
+        args = [ctypes.byref(a), ctypes.byref(b), *(mt or ()), x, y, ctypes.byref(ws), ctypes.byref(raw)]
+        assert (ph.lib().mtimes_bounded_workspace if mt else ph.lib().mul_bounded_workspace)(*args) == 0
+        out.append(ws.value)
+    return out
+
+
+def _dense(*args):
+    known, unknown = _bytes(*args)
+    return known != unknown
+
+
+@pytest.mark.parametrize("n,da,db,sa,sb,mt", [
+    (10, 8, 8, [5000], [5000], None), (4, 6, 6, [200], [200], None), (8, 4, 4, [60] * 600, [300] * 600, None),
+    (10, 7, 1, [4000] * 8, [3] * 8, None), (8, 2, 7, [10] * 8, [4000] * 8, None), (6, 3, 9, [30] * 400, [4000] * 400, None),
+    (8, 4, 4, [300] * 9, [300] * 9, (3, 3, 3)), (6, 4, 4, [200] * 64, [200] * 64, (8, 8, 8)),
+])
+def test_taken(n, da, db, sa, sb, mt):
+    assert _dense(n, da, db, sa, sb, mt)
+
+
+# long operands by short ones: every range looks at every row, the right
+# operand's terms are sorted by counting; a single entry whose cells are
+# crowded adds one product after another
+@pytest.mark.parametrize("n,da,db,sa,sb,mt", [
+    (10, 12, 3, [646646], [1], None), (10, 12, 3, [646646], [100], None), (10, 12, 1, [300000], [4], None),
+    (7, 14, 2, [100000], [32], None), (4, 30, 6, [40000], [1], None), (4, 30, 6, [40000], [100], None),
+    (10, 1, 7, [1] * 64, [10000] * 64, None), (10, 1, 7, [10] * 64, [10000] * 64, None),
+    (6, 3, 9, [1] * 400, [4000] * 400, None), (8, 2, 7, [3] * 400, [4000] * 400, None),
+    (4, 6, 30, [4], [12000], None), (4, 5, 5, [50] * 16, [50] * 16, (1, 16, 1)), (8, 4, 4, [200] * 16, [200] * 16, (1, 16, 1)),
+])
+def test_not_taken(n, da, db, sa, sb, mt):
+    assert not _dense(n, da, db, sa, sb, mt)
