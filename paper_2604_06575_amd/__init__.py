@@ -140,7 +140,8 @@ def lib():
     # entry points of this binding with C++ linkage (not part of the C ABI):
     # products with bounds on the operands' total degrees
     inner = {
-        "max_degrees": ("PK8poly_csrS2_PvPlS3_", [pcsr, pcsr, P, P, P]),
+        "simplify_degree": ("PK8poly_csrPvPlS3_", [pcsr, P, P, P]),
+        "product_degrees": ("PK8poly_csrS2_llPvPlS3_", [pcsr, pcsr, i64, i64, P, P, P]),
         "read_back": ("PKvPKllPlPv", [P, P, i64, P, P]),
         "simplify_bounded_workspace": ("PK8poly_csriPm", [pcsr, i32, psz]),
         "simplify_bounded": ("PK8poly_csriPS0_dPvmS4_", [pcsr, i32, pcsr, d, P, ctypes.c_size_t, P]),
@@ -365,9 +366,9 @@ def simplify(b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | N
     if out is None:
         out = _result(b.n, b.npolys, b.nterms, b.max_exp, b.coefs.device)
     cout = out.csr()
-    # the terms' degree, for a call that waits for its result anyway: 2,048 terms
-    # in 20 variables 92 against 110 us, 1,024 terms 89 us either way
-    deg = _degrees(cin, b.coefs.device)[0] if finish and b.nterms >= 2048 else -1
+    deg = -1
+    if finish and b.nterms >= 2048:   # smaller ones are ruled out anyway
+        deg = _degrees("simplify_degree", b.coefs.device, ctypes.byref(cin))[0]
     need = ctypes.c_size_t()
     _check(L.simplify_bounded_workspace(ctypes.byref(cin), deg, ctypes.byref(need)), "poly_simplify_workspace")
     if ws is None or ws.numel() < need.value:
@@ -457,22 +458,14 @@ def mul_workspace(a: Batch, b: Batch) -> tuple[int, int]:
     return int(ws_bytes.value), int(raw.value)
 
 
-def _degrees(ca: PolyCSR, device, cb: PolyCSR | None = None) -> tuple[int, int]:
-    """Total degrees of one or two batches, read back from the device."""
+def _degrees(which: str, device, *args) -> tuple[int, int]:
+    """Total degrees of a batch or of two operands, read back from the device
+    for a call that waits for its result anyway; (-1, -1) where the sizes rule
+    out the route that they are for."""
     words = _host_words(2)
     scratch = _workspace(16, device)
-    _check(lib().max_degrees(ctypes.byref(ca), ctypes.byref(cb) if cb is not None else None, scratch.data_ptr(),
-                             words.ctypes.data, _stream()), "max_degrees")
+    _check(getattr(lib(), which)(*args, scratch.data_ptr(), words.ctypes.data, _stream()), which)
     return int(words[0]), int(words[1])
-
-
-def _product_degrees(ca: PolyCSR, cb: PolyCSR, raw: int, finish: bool, device) -> tuple[int, int]:
-    """Total degrees of both operands, read back from the device, for a call
-    that waits for its result anyway and whose product can be formed on a
-    dense range of monomials; (-1, -1) otherwise."""
-    if not finish or ca.nvars > 16 or raw < 4096:
-        return -1, -1
-    return _degrees(ca, device, cb)
 
 
 def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tensor | None = None,
@@ -487,7 +480,9 @@ def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tenso
     if out is None:
         out = _result(a.n, a.npolys, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
-    da, db = _product_degrees(ca, cb, raw.value, finish, dev)
+    da = db = -1
+    if finish and raw.value >= 4096:   # smaller ones are ruled out anyway
+        da, db = _degrees("product_degrees", dev, ctypes.byref(ca), ctypes.byref(cb), a.npolys, raw)
     if da >= 0:
         _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(ws_bytes),
                                        ctypes.byref(raw)), "poly_mul_workspace")
@@ -521,7 +516,9 @@ def mtimes(a: Batch, b: Batch, I: int, K: int, J: int, tol: float = 0.0, trim: b
     if out is None:
         out = _result(a.n, I * J, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
-    da, db = _product_degrees(ca, cb, raw.value, finish, dev)
+    da = db = -1
+    if finish and raw.value >= 4096:   # smaller ones are ruled out anyway
+        da, db = _degrees("product_degrees", dev, ctypes.byref(ca), ctypes.byref(cb), I * J, raw)
     if da >= 0:
         _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(ws_bytes),
                                           ctypes.byref(raw)), "poly_mtimes_workspace")

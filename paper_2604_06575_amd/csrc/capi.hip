@@ -1512,18 +1512,39 @@ struct MulDensePlan {
 // products of 1 by 4,000 terms 602 / 661 us (not taken), 400 of 30 by 4,000
 // 3,255 / 5,337 (taken); 12,000 terms times 32 in 6 variables 189 / 222
 // (taken), 40,000 times 32 in 7 variables 284 / 256 (not taken).
-static bool dense_product_pays(const MulDensePlan &m, const poly_csr *b, int64_t left_rows, int64_t raw)
+static double dense_sort_cost(const poly_csr *b)
 {
     double pairs = 0.0;
     for (int64_t p = 0; p < b->npolys; ++p) {
         const double t = (double)(b->row_ptr_host[p + 1] - b->row_ptr_host[p]);
         pairs += t * t;
     }
-    const double r = (double)raw;
-    double cost = 7e-6 * (double)m.nr * (double)left_rows + 0.35e-6 * pairs;
-    if (m.entries > 1) return cost <= 300.0 + 80e-6 * r;
-    cost += r / (double)m.cells * std::sqrt((double)m.threads / kWave);
-    return cost <= 30.0 + 25e-6 * r;
+    return 0.35e-6 * pairs;
+}
+
+static double dense_general_cost(int64_t entries, int64_t raw)
+{
+    return entries > 1 ? 300.0 + 80e-6 * (double)raw : 30.0 + 25e-6 * (double)raw;
+}
+
+static bool dense_product_pays(const MulDensePlan &m, const poly_csr *b, int64_t left_rows, int64_t raw)
+{
+    double cost = 7e-6 * (double)m.nr * (double)left_rows + dense_sort_cost(b);
+    if (m.entries == 1) cost += (double)raw / (double)m.cells * std::sqrt((double)m.threads / kWave);
+    return cost <= dense_general_cost(m.entries, raw);
+}
+
+// What the operands' sizes say before their degrees are known.
+static bool dense_product_possible(const poly_csr *a, const poly_csr *b, int64_t entries, int64_t raw)
+{
+    if (entries < 1 || a->nvars > MD_MAX_N || raw < 4096 || raw >= (int64_t(1) << 32)) return false;
+    unsigned __int128 span = 1;
+    for (int i = 0; i < a->nvars; ++i) {
+        span *= (unsigned)(a->max_exp + b->max_exp + 1);
+        if (span > ((unsigned __int128)1 << 63)) return false;
+    }
+    return max_segment(b->row_ptr_host, b->npolys) <= MD_MAX_PARTNERS &&
+           dense_sort_cost(b) <= dense_general_cost(entries, raw);
 }
 
 // The route is taken where it can be (few variables, keys of 63 bits, cell
@@ -1535,22 +1556,21 @@ static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t
 {
     MulDensePlan m;
     const int n = a->nvars;
-    if (da < 0 || db < 0 || da + db > 255 || n > MD_MAX_N || raw < 4096 || raw >= (int64_t(1) << 32)) return m;
-    m.D = da + db;
-    m.radix = (uint64_t)a->max_exp + (uint64_t)b->max_exp + 1;
-    unsigned __int128 span = 1, cells = 1;
-    for (int i = 0; i < n; ++i) {
-        span *= m.radix;
-        cells = cells * (unsigned)(m.D + i + 1) / (unsigned)(i + 1);   // C(D + i + 1, i + 1), exact
-        if (span > ((unsigned __int128)1 << 63) || cells >= ((unsigned __int128)1 << 31)) return m;
-    }
     m.entries = J ? I * J : I;
     m.K = K;
     m.J = J;
+    if (da < 0 || db < 0 || da + db > 255 || !dense_product_possible(a, b, m.entries, raw)) return m;
+    m.D = da + db;
+    m.radix = (uint64_t)a->max_exp + (uint64_t)b->max_exp + 1;
+    unsigned __int128 cells = 1;
+    for (int i = 0; i < n; ++i) {
+        cells = cells * (unsigned)(m.D + i + 1) / (unsigned)(i + 1);   // C(D + i + 1, i + 1), exact
+        if (cells >= ((unsigned __int128)1 << 31)) return m;
+    }
     if ((double)m.entries * (double)cells > 8.0 * (double)raw) return m;
     m.max_partners = max_segment(b->row_ptr_host, b->npolys);
     const size_t pairs = (size_t)((n + 1) / 2) * (m.D + 1) * (m.D + 1);
-    if (m.max_partners > 16384 || 4 * pairs > MD_TABLE_MAX) return m;
+    if (4 * pairs > MD_TABLE_MAX) return m;
     m.cells = (uint32_t)cells;
     // Workgroup size and cells per range.  A range's chunk (4 raw products per
     // thread) should be no longer than the range is wide.  Every range looks at
@@ -2922,17 +2942,19 @@ poly_status poly_eval_backward2(const poly_csr *f, const double *X, int64_t N, c
 
 namespace polyhip {
 
-// Largest total degree of a's and (b not null) b's terms, into host[0] and
-// host[1]: launches and waits for the stream, so it may not be called under
-// capture.  scratch: 16 bytes of device memory; host: memory that the device
-// can write.
-poly_status max_degrees(const poly_csr *a, const poly_csr *b, void *scratch, int64_t *host, void *stream)
+// Whether a batch's sizes leave room for simplify by monomial ranks, whatever
+// its terms' degree.  From 2,048 terms on the wait for the degree pays: 2,048
+// terms in 20 variables 92 against 110 us, 1,024 terms 89 us either way.
+static bool segrank_possible(const poly_csr *in)
 {
-    poly_status st = check_csr(a, true);
-    if (st != POLY_OK) return st;
-    if (b && (st = check_csr(b, true)) != POLY_OK) return st;
-    if (!scratch || !host || (b && b->nvars != a->nvars)) return POLY_ERR_ARG;
-    hipStream_t s = (hipStream_t)stream;
+    return in->nvars <= SR_MAX_N && total_terms(in) >= 2048 && in->npolys < (int64_t(1) << 31) &&
+           max_segment(in->row_ptr_host, in->npolys) <= SR_MAX_TERMS;
+}
+
+// Largest total degree of a's and (b not null) b's terms, into host[0] and
+// host[1]: launches and waits for the stream.
+static poly_status max_degrees(const poly_csr *a, const poly_csr *b, void *scratch, int64_t *host, hipStream_t s)
+{
     const int64_t Ta = total_terms(a), Tb = b ? total_terms(b) : 0;
     // one block takes eight terms per thread in about the time of a launch
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ceil_div(Ta + Tb, 8192), 512));
@@ -2941,6 +2963,32 @@ poly_status max_degrees(const poly_csr *a, const poly_csr *b, void *scratch, int
                        (int)a->nvars, (uint32_t *)scratch, host);
     LAUNCH_CHECK();
     return hipStreamSynchronize(s) == hipSuccess ? POLY_OK : POLY_ERR_HIP;
+}
+
+// Degrees for simplify_bounded, mul_bounded and mtimes_bounded, read back from
+// the device: launches and waits for the stream, so they may not be called
+// under capture.  Where the sizes alone rule out the route that needs them,
+// nothing is launched and they are -1.  scratch: 16 bytes of device memory;
+// host: two words of memory that the device can write.
+poly_status simplify_degree(const poly_csr *in, void *scratch, int64_t *host, void *stream)
+{
+    poly_status st = check_csr(in, true);
+    if (st != POLY_OK) return st;
+    if (!scratch || !host) return POLY_ERR_ARG;
+    host[0] = host[1] = -1;
+    return segrank_possible(in) ? max_degrees(in, nullptr, scratch, host, (hipStream_t)stream) : POLY_OK;
+}
+
+// entries: of the product; raw: its raw terms
+poly_status product_degrees(const poly_csr *a, const poly_csr *b, int64_t entries, int64_t raw, void *scratch,
+                            int64_t *host, void *stream)
+{
+    poly_status st = check_csr(a, true);
+    if (st != POLY_OK) return st;
+    if ((st = check_csr(b, true)) != POLY_OK) return st;
+    if (!scratch || !host || b->nvars != a->nvars) return POLY_ERR_ARG;
+    host[0] = host[1] = -1;
+    return dense_product_possible(a, b, entries, raw) ? max_degrees(a, b, scratch, host, (hipStream_t)stream) : POLY_OK;
 }
 
 // The device status of a finished call (poly_read_status) and its row pointer
@@ -2973,10 +3021,9 @@ static SegRankPlan plan_segrank(const poly_csr *in, int deg)
     SegRankPlan m;
     const int n = in->nvars;
     const int64_t T = total_terms(in), P = in->npolys;
-    if (deg < 0 || deg > 255 || n < 1 || n > SR_MAX_N || T < 1 || P >= (int64_t(1) << 31)) return m;
+    if (deg < 0 || deg > 255 || !segrank_possible(in)) return m;
     for (int64_t p = 0; p < P; ++p) {
         const int64_t t = in->row_ptr_host[p + 1] - in->row_ptr_host[p];
-        if (t > SR_MAX_TERMS) return m;
         ++m.count[(t < 8192) + (t < 1024) + (t < 256)];
     }
     unsigned __int128 cells = 1;

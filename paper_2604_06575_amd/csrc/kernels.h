@@ -123,6 +123,7 @@ __global__ void k_mul_rowptr(const int64_t *out_off, const int64_t *pb_start, in
 // products on a dense range of monomials (muldense.hip)
 constexpr int MD_MAX_N = 16;            // pair words: two of four 16-bit pairs
 constexpr int MD_ITEMS = 4;             // raw products per thread and chunk
+constexpr int64_t MD_MAX_PARTNERS = 16384;   // terms of a right polynomial: keys of 128 KB, counts of 16 bits
 constexpr int MD_STEP_ROWS = 4;         // rows per thread and step
 constexpr size_t MD_TABLE_MAX = 32 * 1024;   // LDS of the pair tables
 constexpr size_t MD_LDS_MAX = 156 * 1024;

@@ -60,3 +60,31 @@ def test_taken(n, da, db, sa, sb, mt):
 ])
 def test_not_taken(n, da, db, sa, sb, mt):
     assert not _dense(n, da, db, sa, sb, mt)
+
+
+def _degrees(call, *args):
+    """The degrees' words after a call that may launch nothing: there is no
+    device memory behind its operands."""
+    words = np.full(2, 7, np.int64)
+    scratch = np.zeros(16, np.uint8)
+    assert call(*args, scratch.ctypes.data, words.ctypes.data, None) == 0
+    return words.tolist()
+
+
+# more variables than the route has pair words; few raw products; keys past 63
+# bits; a right operand too long for 16-bit counts; one too long to be sorted by counting
+@pytest.mark.parametrize("n,ea,eb,sa,sb", [
+    (17, 2, 2, [500], [500]), (4, 6, 6, [63], [65]), (16, 8, 8, [500], [500]), (4, 30, 30, [500], [16385]),
+    (10, 1, 7, [10] * 64, [10000] * 64),
+])
+def test_product_degrees_not_read_where_sizes_rule_the_route_out(n, ea, eb, sa, sb):
+    a, b = _csr(n, ea, sa), _csr(n, eb, sb)
+    raw = sum(x * y for x, y in zip(sa, sb))
+    assert _degrees(ph.lib().product_degrees, ctypes.byref(a), ctypes.byref(b), len(sa), raw) == [-1, -1]
+
+
+# a polynomial past 20,480 terms among others; more than 128 variables; few terms
+@pytest.mark.parametrize("n,sizes", [(20, [20481]), (20, [100] * 50 + [20481]), (129, [500] * 20), (20, [2047])])
+def test_simplify_degree_not_read_where_sizes_rule_the_route_out(n, sizes):
+    c = _csr(n, 6, sizes)
+    assert _degrees(ph.lib().simplify_degree, ctypes.byref(c)) == [-1, -1]
