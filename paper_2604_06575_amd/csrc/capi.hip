@@ -1496,6 +1496,7 @@ struct MulDensePlan {
     uint64_t radix = 0;
     int64_t entries = 0, K = 1, J = 0, nr = 0, ranges = 0, max_partners = 0;
     uint32_t cells = 0, cpr = 0;
+    double sort_cost = 0.0;   // us
     size_t lds = 0;
     size_t ka, wa, kb, wb, kb_s, wb_s, cb_s, table, pairs, bounds, cut, count, out_off, tmp, st_cell, st_coef, total;
 };
@@ -1512,30 +1513,20 @@ struct MulDensePlan {
 // products of 1 by 4,000 terms 602 / 661 us (not taken), 400 of 30 by 4,000
 // 3,255 / 5,337 (taken); 12,000 terms times 32 in 6 variables 189 / 222
 // (taken), 40,000 times 32 in 7 variables 284 / 256 (not taken).
-static double dense_sort_cost(const poly_csr *b)
-{
-    double pairs = 0.0;
-    for (int64_t p = 0; p < b->npolys; ++p) {
-        const double t = (double)(b->row_ptr_host[p + 1] - b->row_ptr_host[p]);
-        pairs += t * t;
-    }
-    return 0.35e-6 * pairs;
-}
-
 static double dense_general_cost(int64_t entries, int64_t raw)
 {
     return entries > 1 ? 300.0 + 80e-6 * (double)raw : 30.0 + 25e-6 * (double)raw;
 }
 
-static bool dense_product_pays(const MulDensePlan &m, const poly_csr *b, int64_t left_rows, int64_t raw)
+static bool dense_product_pays(const MulDensePlan &m, int64_t left_rows, int64_t raw)
 {
-    double cost = 7e-6 * (double)m.nr * (double)left_rows + dense_sort_cost(b);
+    double cost = 7e-6 * (double)m.nr * (double)left_rows + m.sort_cost;
     if (m.entries == 1) cost += (double)raw / (double)m.cells * std::sqrt((double)m.threads / kWave);
     return cost <= dense_general_cost(m.entries, raw);
 }
 
 // What the operands' sizes say before their degrees are known.
-static bool dense_product_possible(const poly_csr *a, const poly_csr *b, int64_t entries, int64_t raw)
+static bool dense_product_possible(MulDensePlan &m, const poly_csr *a, const poly_csr *b, int64_t entries, int64_t raw)
 {
     if (entries < 1 || a->nvars > MD_MAX_N || raw < 4096 || raw >= (int64_t(1) << 32)) return false;
     unsigned __int128 span = 1;
@@ -1543,8 +1534,15 @@ static bool dense_product_possible(const poly_csr *a, const poly_csr *b, int64_t
         span *= (unsigned)(a->max_exp + b->max_exp + 1);
         if (span > ((unsigned __int128)1 << 63)) return false;
     }
-    return max_segment(b->row_ptr_host, b->npolys) <= MD_MAX_PARTNERS &&
-           dense_sort_cost(b) <= dense_general_cost(entries, raw);
+    m.max_partners = max_segment(b->row_ptr_host, b->npolys);
+    if (m.max_partners > MD_MAX_PARTNERS) return false;
+    int64_t pairs = 0;   // at most 2^32 * 2^14
+    for (int64_t p = 0; p < b->npolys; ++p) {
+        const int64_t t = b->row_ptr_host[p + 1] - b->row_ptr_host[p];
+        pairs += t * t;
+    }
+    m.sort_cost = 0.35e-6 * (double)pairs;
+    return m.sort_cost <= dense_general_cost(entries, raw);
 }
 
 // The route is taken where it can be (few variables, keys of 63 bits, cell
@@ -1559,7 +1557,7 @@ static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t
     m.entries = J ? I * J : I;
     m.K = K;
     m.J = J;
-    if (da < 0 || db < 0 || da + db > 255 || !dense_product_possible(a, b, m.entries, raw)) return m;
+    if (da < 0 || db < 0 || da + db > 255 || !dense_product_possible(m, a, b, m.entries, raw)) return m;
     m.D = da + db;
     m.radix = (uint64_t)a->max_exp + (uint64_t)b->max_exp + 1;
     unsigned __int128 cells = 1;
@@ -1568,7 +1566,6 @@ static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t
         if (cells >= ((unsigned __int128)1 << 31)) return m;
     }
     if ((double)m.entries * (double)cells > 8.0 * (double)raw) return m;
-    m.max_partners = max_segment(b->row_ptr_host, b->npolys);
     const size_t pairs = (size_t)((n + 1) / 2) * (m.D + 1) * (m.D + 1);
     if (4 * pairs > MD_TABLE_MAX) return m;
     m.cells = (uint32_t)cells;
@@ -1591,7 +1588,7 @@ static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t
     }
     m.nr = ceil_div(m.cells, (int64_t)m.cpr);
     m.ranges = m.entries * m.nr;
-    if (!dense_product_pays(m, b, left_rows, raw)) return m;
+    if (!dense_product_pays(m, left_rows, raw)) return m;
     m.kb_lds = b->npolys == 1;   // at most 128 KB
     m.lds = 12 * (size_t)m.cpr + 4 * pairs + 10 * (size_t)m.threads * MD_STEP_ROWS + 16;
     if (m.lds > MD_LDS_MAX || m.ranges >= (int64_t(1) << 31) || m.ranges * (int64_t)m.cpr > (int64_t(1) << 30) ||
@@ -2956,8 +2953,10 @@ static bool segrank_possible(const poly_csr *in)
 static poly_status max_degrees(const poly_csr *a, const poly_csr *b, void *scratch, int64_t *host, hipStream_t s)
 {
     const int64_t Ta = total_terms(a), Tb = b ? total_terms(b) : 0;
-    // one block takes eight terms per thread in about the time of a launch
-    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ceil_div(Ta + Tb, 8192), 512));
+    // one block takes eight terms of 16 bytes per thread in about the time of a
+    // launch (by the terms alone, 150,000 rows of 125 bytes: 445 us more than now)
+    const int64_t bytes = (Ta + Tb) * std::max<int64_t>(a->nvars, 16);
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(ceil_div(bytes, 8192 * 16), 512));
     if (blocks > 1) clear_u64((unsigned long long *)scratch, 2, s);
     hipLaunchKernelGGL(k_max_degree, dim3((unsigned)blocks), dim3(1024), 0, s, a->exps, Ta, b ? b->exps : nullptr, Tb,
                        (int)a->nvars, (uint32_t *)scratch, host);
@@ -2988,7 +2987,8 @@ poly_status product_degrees(const poly_csr *a, const poly_csr *b, int64_t entrie
     if ((st = check_csr(b, true)) != POLY_OK) return st;
     if (!scratch || !host || b->nvars != a->nvars) return POLY_ERR_ARG;
     host[0] = host[1] = -1;
-    return dense_product_possible(a, b, entries, raw) ? max_degrees(a, b, scratch, host, (hipStream_t)stream) : POLY_OK;
+    MulDensePlan m;
+    return dense_product_possible(m, a, b, entries, raw) ? max_degrees(a, b, scratch, host, (hipStream_t)stream) : POLY_OK;
 }
 
 // The device status of a finished call (poly_read_status) and its row pointer
@@ -3021,9 +3021,10 @@ static SegRankPlan plan_segrank(const poly_csr *in, int deg)
     SegRankPlan m;
     const int n = in->nvars;
     const int64_t T = total_terms(in), P = in->npolys;
-    if (deg < 0 || deg > 255 || !segrank_possible(in)) return m;
+    if (deg < 0 || deg > 255 || n > SR_MAX_N || T < 1 || P >= (int64_t(1) << 31)) return m;
     for (int64_t p = 0; p < P; ++p) {
         const int64_t t = in->row_ptr_host[p + 1] - in->row_ptr_host[p];
+        if (t > SR_MAX_TERMS) return m;
         ++m.count[(t < 8192) + (t < 1024) + (t < 256)];
     }
     unsigned __int128 cells = 1;

@@ -63,13 +63,19 @@ __global__ void __launch_bounds__(1024) k_max_degree(const uint8_t *ea, int64_t 
 {
     __shared__ uint32_t s_m[2][16];
     uint32_t m[2] = {0, 0};
+    auto rows = [&](auto sum) {   // sum(row): its exponents'
 #pragma unroll 2
-    for (int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x; t < Ta + Tb; t += (int64_t)gridDim.x * 1024) {
-        const bool second = t >= Ta;
-        const uint8_t *row = second ? eb + (t - Ta) * n : ea + t * n;
-        uint32_t d = 0;
-        if (((reinterpret_cast<uintptr_t>(row) | (uintptr_t)n) & 3) == 0) {
+        for (int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x; t < Ta + Tb; t += (int64_t)gridDim.x * 1024) {
+            const bool second = t >= Ta;
+            const uint32_t d = sum(second ? eb + (t - Ta) * n : ea + t * n);
+            if (second) m[1] = d > m[1] ? d : m[1];
+            else m[0] = d > m[0] ? d : m[0];
+        }
+    };
+    if (((reinterpret_cast<uintptr_t>(ea) | reinterpret_cast<uintptr_t>(eb) | (uintptr_t)n) & 3) == 0) {
+        rows([&](const uint8_t *row) {
             const uint32_t *r4 = reinterpret_cast<const uint32_t *>(row);
+            uint32_t d = 0;
             int i = 0;
             for (; i + 4 <= n / 4; i += 4) {
                 uint32_t x[4];
@@ -78,11 +84,18 @@ __global__ void __launch_bounds__(1024) k_max_degree(const uint8_t *ea, int64_t 
                 for (int k = 0; k < 4; ++k) d = __builtin_amdgcn_sad_u8(x[k], 0u, d);
             }
             for (; i < n / 4; ++i) d = __builtin_amdgcn_sad_u8(r4[i], 0u, d);
-        } else {
-            for (int i = 0; i < n; ++i) d += row[i];
-        }
-        if (second) m[1] = d > m[1] ? d : m[1];
-        else m[0] = d > m[0] ? d : m[0];
+            return d;
+        });
+    } else {   // the bytes before the row's first whole word, its words, the bytes after the last
+        rows([&](const uint8_t *row) {
+            uint32_t d = 0;
+            int i = 0;
+            for (; i < n && ((reinterpret_cast<uintptr_t>(row) + i) & 3) != 0; ++i) d += row[i];
+#pragma unroll 4
+            for (; i + 4 <= n; i += 4) d = __builtin_amdgcn_sad_u8(*reinterpret_cast<const uint32_t *>(row + i), 0u, d);
+            for (; i < n; ++i) d += row[i];
+            return d;
+        });
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {

@@ -3,6 +3,8 @@ for bit against the general path, which finish=False takes, and the oracle: at
 the polynomial sizes where the workgroup changes, with runs longer than a round,
 one monomial only, rows that are no whole words, and just past the sizes,
 degrees and variables that the rank path takes."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -56,3 +58,23 @@ def test_capacity_and_exponent_status():
         ph.simplify(b, out=small)
     with pytest.raises(ph.PolyError):
         ph.simplify(ph.batch_from_numpy(rp, e, c, n=6, max_exp=3))
+
+
+# rows that begin and end within words, in one block and in many; the largest
+# degree in the last row, the first, and one that ends at a block's edge
+@pytest.mark.parametrize("n,T", [(3, 2048), (5, 2049), (7, 30000), (21, 9000), (33, 4000), (61, 2500), (127, 2100), (127, 9001), (128, 5000)])
+def test_degree_is_read_whole(n, T):
+    rng = np.random.default_rng(n + T)
+    e = np.zeros((T, n), np.uint8)
+    e[np.arange(T), rng.integers(0, n, T)] = 1
+    for t, i in ((T - 1, n - 1), (0, 0), (1023 if T > 1023 else T // 2, n // 2)):
+        x = e.copy()
+        x[t] = 0
+        x[t, i] = 4
+        b = ph.batch_from_numpy([0, T // 2, T], x, np.ones(T), n=n)
+        words = torch.zeros(2, dtype=torch.int64, pin_memory=True)
+        scratch = torch.zeros(16, dtype=torch.uint8, device="cuda")
+        c = b.csr()
+        assert ph.lib().simplify_degree(ctypes.byref(c), scratch.data_ptr(), words.data_ptr(),
+                                        torch.cuda.current_stream().cuda_stream) == 0
+        assert int(words[0]) == 4
