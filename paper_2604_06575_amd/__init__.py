@@ -458,6 +458,20 @@ def mul_workspace(a: Batch, b: Batch) -> tuple[int, int]:
     return int(ws_bytes.value), int(raw.value)
 
 
+def _workspace_of(ws: torch.Tensor | None, need: int, least: int, device) -> torch.Tensor:
+    """`ws`, or a new workspace where it has less than `need` bytes; where
+    there is no memory for that many, one of at least `least` (the general
+    route's)."""
+    if ws is not None and ws.numel() >= need:
+        return ws
+    try:
+        return _workspace(need, device)
+    except torch.OutOfMemoryError:
+        if need <= least:
+            raise
+        return _workspace_of(ws, least, least, device)
+
+
 def _degrees(which: str, device, *args) -> tuple[int, int]:
     """Total degrees of a batch or of two operands, read back from the device
     for a call that waits for its result anyway; (-1, -1) where the sizes rule
@@ -480,14 +494,16 @@ def mul(a: Batch, b: Batch, tol: float = 0.0, trim: bool = True, ws: torch.Tenso
     if out is None:
         out = _result(a.n, a.npolys, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
+    least = ws_bytes.value
     da = db = -1
     if finish and raw.value >= 4096:   # smaller ones are ruled out anyway
         da, db = _degrees("product_degrees", dev, ctypes.byref(ca), ctypes.byref(cb), a.npolys, raw)
     if da >= 0:
         _check(L.mul_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(ws_bytes),
                                        ctypes.byref(raw)), "poly_mul_workspace")
-    if ws is None or ws.numel() < ws_bytes.value:
-        ws = _workspace(ws_bytes.value, dev)
+    ws = _workspace_of(ws, ws_bytes.value, least, dev)
+    if ws.numel() < ws_bytes.value:
+        da = db = -1
     _check(L.mul_bounded(ctypes.byref(ca), ctypes.byref(cb), da, db, ctypes.byref(cout), float(tol),
                          ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mul")
     if not finish:
@@ -516,14 +532,16 @@ def mtimes(a: Batch, b: Batch, I: int, K: int, J: int, tol: float = 0.0, trim: b
     if out is None:
         out = _result(a.n, I * J, raw.value, a.max_exp + b.max_exp, dev)
     cout = out.csr()
+    least = ws_bytes.value
     da = db = -1
     if finish and raw.value >= 4096:   # smaller ones are ruled out anyway
         da, db = _degrees("product_degrees", dev, ctypes.byref(ca), ctypes.byref(cb), I * J, raw)
     if da >= 0:
         _check(L.mtimes_bounded_workspace(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(ws_bytes),
                                           ctypes.byref(raw)), "poly_mtimes_workspace")
-    if ws is None or ws.numel() < ws_bytes.value:
-        ws = _workspace(ws_bytes.value, dev)
+    ws = _workspace_of(ws, ws_bytes.value, least, dev)
+    if ws.numel() < ws_bytes.value:
+        da = db = -1
     _check(L.mtimes_bounded(ctypes.byref(ca), ctypes.byref(cb), I, K, J, da, db, ctypes.byref(cout), float(tol),
                             ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream()), "poly_mtimes")
     if not finish:

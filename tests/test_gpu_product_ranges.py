@@ -169,3 +169,32 @@ def test_inferred_exponent_bounds():
     assert many.max_exp == 1
     _same(ph.mul(many, many), W.csr_from_list([oracle.mul(*p, *p) for p in polys], n))
     _same(ph.mtimes(many, many, 2, 3, 2), oracle.mtimes(rp, ee, cc, rp, ee, cc, 2, 3, 2))
+
+
+@pytest.mark.parametrize("own", [False, True])
+def test_no_memory_for_the_staged_cells(monkeypatch, own):
+    """Cells take more memory than the general route's raw products where the
+    product is sparse: without it the call takes the general route, in a
+    workspace of its own or the caller's."""
+    rng = W.rng_for(75001)
+    n, d, P, t = 8, 4, 400, 45
+    a, b = (_batch([_poly(rng, n, d, t) for _ in range(P)], n, d) for _ in range(2))
+    want = ph.mul(a, b)
+    need, raw = ph.mul_workspace(a, b)
+    asked = []
+    make = ph._workspace
+
+    def limited(nbytes, device):
+        asked.append(nbytes)
+        if nbytes > need:
+            raise torch.OutOfMemoryError("no memory")
+        return make(nbytes, device)
+
+    monkeypatch.setattr(ph, "_workspace", limited)
+    got = ph.mul(a, b, ws=make(need, "cuda") if own else None)
+    assert max(asked) > need   # the route was tried
+    assert np.array_equal(got.row_ptr_host, want.row_ptr_host)
+    assert torch.equal(got.exps, want.exps) and torch.equal(got.coefs, want.coefs)
+    with pytest.raises(torch.OutOfMemoryError):
+        monkeypatch.setattr(ph, "_workspace", lambda nbytes, device: (_ for _ in ()).throw(torch.OutOfMemoryError()))
+        ph.mul(a, b)
