@@ -2656,8 +2656,16 @@ struct BackwardPlan {
     GradPlan g;             // dX from the formed Jacobian
     size_t senc = 0, part = 0;   // dC
     int cp = 0;
-    int64_t nchunks = 0, tiles = 0;   // point chunks of the dC kernels
+    int64_t nchunks = 0;         // point chunks of k_backward_dc
+    int64_t S = 1;               // segments of a polynomial (k_backward_dc_reg)
+    int64_t tiles = 0, rows = 0; // its point tiles, 0 where it does not pay, and as many as a pass takes
 };
+
+// Partial sums that a pass of k_backward_dc_reg keeps at most, where those of
+// k_backward_dc are fewer: its tiles have 64 or 128 points, the chunks up to
+// 512 (100,000 terms in 20 variables at a million points: 6.3 GB for all tiles,
+// 2.1 for the chunks).
+constexpr int64_t BWC_PART_BYTES = int64_t(256) << 20;
 
 static BackwardPlan plan_backward(const poly_csr *f, int64_t N, Layout &L)
 {
@@ -2674,8 +2682,18 @@ static BackwardPlan plan_backward(const poly_csr *f, int64_t N, Layout &L)
     b.senc = L.take(factor_bytes(n, T));   // factor lists of the dC kernel
     b.cp = std::max(1, std::min(BWC_POINTS, 8192 / (n + 1)));
     b.nchunks = ceil_div(N, b.cp);
-    b.tiles = n <= RE_MAX_N ? ceil_div(N, kWave * regeval_points(regeval_rows(n))) : 0;
-    b.part = L.take(8 * T * std::max(b.nchunks, b.tiles));
+    if (n <= RE_MAX_N && T > 0 && N > 0) {
+        const int64_t tiles = ceil_div(N, kWave * regeval_points(regeval_rows(n)));
+        // passes of equal length
+        const int64_t rows = ceil_div(tiles, ceil_div(tiles, std::max(b.nchunks, BWC_PART_BYTES / (8 * T))));
+        // segments of at least 512 terms, about four for each resident wave
+        b.S = std::max<int64_t>(1, std::min(ceil_div((int64_t)8192, P * rows), T / (P * 512)));
+        if (regeval_pays(n, 8, T, P * b.S, N)) {   // at any degree class
+            b.tiles = tiles;
+            b.rows = rows;
+        }
+    }
+    b.part = L.take(8 * T * std::max(b.nchunks, b.rows));
     return b;
 }
 
@@ -2716,8 +2734,6 @@ static void launch_dc(const poly_csr *f, const double *X, int64_t N, const doubl
         clear_u64((unsigned long long *)dC, T, s);
         return;
     }
-    // segments of at least 512 terms, about four for each resident wave
-    const int64_t S = std::max<int64_t>(1, std::min(ceil_div((int64_t)8192, std::max<int64_t>(P * b.tiles, 1)), T / (P * 512)));
     EvalArgs A;
     memset(&A, 0, sizeof(A));
     A.rp = f->row_ptr;
@@ -2726,25 +2742,35 @@ static void launch_dc(const poly_csr *f, const double *X, int64_t N, const doubl
     A.N = N;
     A.Q = P;
     A.term_limit = T;
-    A.ranges = P * S;
+    A.ranges = P * b.S;
     A.words_cap = word_plane(T);
-    const bool reg = regeval_pays(n, 8, T, A.ranges, N);   // at any degree class
+    const bool reg = b.tiles > 0;
     if (reg) A.maxdeg = at<uint32_t>(ws, 8);
     hipLaunchKernelGGL(k_encode_factors, dim3(grid1(T, 256)), dim3(256), 0, s, f->exps, T, n, senc,
                        (const int64_t *)nullptr, reg ? at<uint32_t>(ws, 8) : nullptr,
                        reg ? factor_words(senc, n, T) : nullptr);
-    if (reg)
-        with_regeval_rows(n, [&](auto nr) {
-            constexpr int NR = decltype(nr)::value;
-            hipLaunchKernelGGL((k_backward_dc_reg<NR>), regeval_grid(N, NR, P * S, T, P == 1), dim3(EV_THREADS),
-                               regeval_lds(NR) + EV_WAVES * RD_BUF * sizeof(double), s, A, (const uint32_t *)senc,
-                               (const uint32_t *)factor_words(senc, n, T), gY, T, S, part);
-        });
-    const size_t lds = (size_t)cp * (n + 1) * sizeof(double);
-    hipLaunchKernelGGL(k_backward_dc, dim3(grid1(T, BWC_TERMS * BWC_THREADS), (unsigned)nchunks), dim3(BWC_THREADS),
-                       lds, s, f->row_ptr, P, f->exps, n, T, X, N, gY, part, nchunks, (const uint4 *)senc, cp, A);
-    hipLaunchKernelGGL(k_backward_dc_reduce, dim3(grid1(T, 256)), dim3(256), 0, s, (const double *)part, T, nchunks,
-                       dC, A, b.tiles);
+    // The register kernel's tiles in passes whose partial sums fit; each pass
+    // goes on from the sum of the tiles before, so the passes change no bit.
+    int64_t tile0 = 0;
+    do {
+        const int64_t rows = std::min(b.rows, b.tiles - tile0);
+        if (reg)
+            with_regeval_rows(n, [&](auto nr) {
+                constexpr int NR = decltype(nr)::value;
+                const int64_t points = std::min(N, rows * kWave * regeval_points(NR));
+                hipLaunchKernelGGL((k_backward_dc_reg<NR>), regeval_grid(points, NR, P * b.S, T, P == 1),
+                                   dim3(EV_THREADS), regeval_lds(NR) + EV_WAVES * RD_BUF * sizeof(double), s, A,
+                                   (const uint32_t *)senc, (const uint32_t *)factor_words(senc, n, T), gY, T, b.S,
+                                   part, tile0);
+            });
+        if (tile0 == 0)
+            hipLaunchKernelGGL(k_backward_dc, dim3(grid1(T, BWC_TERMS * BWC_THREADS), (unsigned)nchunks),
+                               dim3(BWC_THREADS), (size_t)cp * (n + 1) * sizeof(double), s, f->row_ptr, P, f->exps, n,
+                               T, X, N, gY, part, nchunks, (const uint4 *)senc, cp, A);
+        hipLaunchKernelGGL(k_backward_dc_reduce, dim3(grid1(T, 256)), dim3(256), 0, s, (const double *)part, T,
+                           nchunks, dC, A, rows, tile0);
+        tile0 += b.rows;
+    } while (tile0 < b.tiles);
 }
 
 }  // namespace
@@ -2913,7 +2939,7 @@ poly_status poly_eval_backward2(const poly_csr *f, const double *X, int64_t N, c
             EvalArgs none;
             memset(&none, 0, sizeof(none));
             hipLaunchKernelGGL(k_backward_dc_reduce, dim3(grid1(T, 256)), dim3(256), 0, s, (const double *)part, T,
-                               b.nchunks, ggC, none, (int64_t)0);
+                               b.nchunks, ggC, none, (int64_t)0, (int64_t)0);
         }
     }
     LAUNCH_CHECK();

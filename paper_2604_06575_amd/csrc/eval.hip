@@ -998,21 +998,21 @@ __global__ void __launch_bounds__(256) k_eval_reduce(EvalArgs A, const double *p
 
 // Partial dC over a tile of points with the coordinates in registers
 // (regeval.h): lanes are points, a wave takes segments of a polynomial's terms
-// and leaves one sum per term and tile in partial[tile][T].  Bound by the
+// and leaves one sum per term and tile in partial[tile - tile0][T].  Bound by the
 // issue of vector instructions.  A quartic of 100,000 terms in 100 variables,
 // 8,192 points: 325 us; lanes as terms, which gather coordinates from LDS with
 // bank conflicts, 830.  Dynamic LDS: the tile, then RD_BUF doubles per wave.
 template <int NR>
 __global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
     k_backward_dc_reg(EvalArgs A, const uint32_t *__restrict__ enc, const uint32_t *__restrict__ words,
-                      const double *gY, int64_t T, int64_t S, double *partial)
+                      const double *gY, int64_t T, int64_t S, double *partial, int64_t tile0)
 {
     constexpr int PT = regeval_points(NR);
     extern __shared__ double s_x[];
     uint32_t md;
     if (!eval_form_runs<NR>(A, md)) return;
     const int lane = lane_id(), w = wave_id();
-    const int64_t pt0 = (int64_t)blockIdx.x * (kWave * PT);
+    const int64_t pt0 = (tile0 + blockIdx.x) * (kWave * PT);
     stage_points<NR>(A, pt0, s_x);
     const double *xl = s_x + lane;
     const uint32_t xa = lds_address(xl);
@@ -1057,11 +1057,11 @@ __global__ void __launch_bounds__(EV_THREADS, NR > 24 ? 2 : 4)
     }
 }
 template __global__ void k_backward_dc_reg<24>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
-                                               int64_t, double *);
+                                               int64_t, double *, int64_t);
 template __global__ void k_backward_dc_reg<56>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
-                                               int64_t, double *);
+                                               int64_t, double *, int64_t);
 template __global__ void k_backward_dc_reg<113>(EvalArgs, const uint32_t *, const uint32_t *, const double *, int64_t,
-                                                int64_t, double *);
+                                                int64_t, double *, int64_t);
 
 // Partial dC over one chunk of points: lanes are terms.  Each lane holds its
 // term's factor list (k_encode_factors: up to EV_MAX_DEG variable indices,
@@ -1134,15 +1134,17 @@ __global__ void __launch_bounds__(BWC_THREADS) k_backward_dc(const int64_t *rp, 
     }
 }
 
-// reg_tiles: the chunks where k_backward_dc_reg ran
+// reg_tiles: the chunks where k_backward_dc_reg ran, for the tiles from tile0
+// on, added to the sum of those before
 __global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC, EvalArgs A,
-                                     int64_t reg_tiles)
+                                     int64_t reg_tiles, int64_t tile0)
 {
     uint32_t md;
     if (eval_form_runs<24>(A, md)) nchunks = reg_tiles;
+    else if (tile0 > 0) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
-    double s = partial[t];
+    double s = tile0 > 0 ? dC[t] + partial[t] : partial[t];
     for (int64_t c = 1; c < nchunks; ++c) s += partial[c * T + t];
     dC[t] = s;
 }

@@ -442,8 +442,8 @@ __global__ void k_backward_dc(const int64_t *rp, int64_t P, const uint8_t *exps,
                               const uint4 *fenc, int cp, EvalArgs A);
 template <int NR>
 __global__ void k_backward_dc_reg(EvalArgs A, const uint32_t *__restrict__ enc, const uint32_t *__restrict__ words,
-                                  const double *gY, int64_t T, int64_t S, double *partial);
+                                  const double *gY, int64_t T, int64_t S, double *partial, int64_t tile0);
 __global__ void k_backward_dc_reduce(const double *partial, int64_t T, int64_t nchunks, double *dC, EvalArgs A,
-                                     int64_t reg_tiles);
+                                     int64_t reg_tiles, int64_t tile0);
 
 }  // namespace polyhip

@@ -109,3 +109,20 @@ def test_dc(n, d):
     v = v * gY[np.searchsorted(rp, t, side="right") - 1].T
     got = dC.cpu().numpy()[t]
     assert np.all(np.abs(got - v.sum(0)) <= (N + d + 5) * U * np.abs(v).sum(0))
+
+
+# more tiles of points than the partial sums of one pass (256 MB) have room
+# for: 2,344 tiles of 128 points, 1,677 a pass; a degree past the register form
+@pytest.mark.parametrize("d", [3, 6, 9])
+def test_dc_in_passes(d):
+    rng = np.random.default_rng(400 + d)
+    n, N = 10, 300_001
+    f, e, rp, c = _batch(rng, n, d, [20001, 7])
+    X, gY = rng.uniform(-1, 1, (N, n)), rng.standard_normal((2, N))
+    _, dC = ph.eval_backward(ph.batch_from_numpy(rp, e, c), torch.from_numpy(X).cuda(), torch.from_numpy(gY).cuda(),
+                             want_dX=False, want_dC=True)
+    t = np.concatenate([rng.integers(0, rp[-1], 12), [0, 20000, 20001, 20007]])
+    x = _padded(X)
+    for k in t:
+        v = np.prod(x[:, f[k]], axis=1) * gY[int(k >= rp[1])]
+        assert np.abs(dC[k].item() - v.sum()) <= (N + d + 5) * U * np.abs(v).sum(), k
