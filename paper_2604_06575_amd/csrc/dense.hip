@@ -1464,9 +1464,26 @@ int dense_ranges(int64_t tiles, int64_t steps, double bytes, double step_us)
 // rows of C (or gY) per workgroup of the FP64 contractions
 inline int dense_f64_bm() { return tunables().dense_f64_rows == 128 ? 128 : 64; }
 
+// Ranges for `bm` rows per workgroup of a contraction of `steps` steps into a
+// P x cols matrix.
+inline int f64_ranges(int bm, int64_t P, int64_t cols, int64_t steps)
+{
+    return dense_ranges(ceil_div(cols, (int64_t)128) * ceil_div(P, bm), steps, 8.0 * (double)P * (double)cols,
+                        1.7 * bm / 128);
+}
+
+// Partial sums of either number of rows, so that a workspace holds when the
+// tunable changes between the query and the call.
+inline size_t f64_partial_bytes(int64_t P, int64_t cols, int64_t steps)
+{
+    const int z = std::max(f64_ranges(64, P, cols, steps), f64_ranges(128, P, cols, steps));
+    return z > 1 ? (size_t)z * P * cols * 8 : 0;
+}
+
 struct DensePlan {
     size_t enc, cs, sigv, part, total;
-    int nz;       // K ranges of the FP64 contraction
+    int bm;       // rows per workgroup of the FP64 contraction
+    int nz;       // its K ranges
     int64_t kz;   // monomials per range
 };
 
@@ -1481,6 +1498,7 @@ DensePlan plan_dense(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec,
     DensePlan d;
     d.enc = take(16 * (size_t)K);
     d.cs = d.sigv = d.part = 0;
+    d.bm = prec == POLY_FP64 ? dense_f64_bm() : 64;
     d.nz = 1;
     d.kz = K;
     if (prec == POLY_SPLIT_BF16) {
@@ -1488,12 +1506,10 @@ DensePlan plan_dense(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec,
         d.cs = take((size_t)S * ceil_div(P, 32) * 32 * Kp * 2);
         d.sigv = take((size_t)ceil_div(Kp, DN_KB) * N * 4);
     } else if (K > 0 && P > 0 && N > 0) {
-        const int bm = dense_f64_bm();
         const int64_t steps = ceil_div(K, D64_KS);
-        d.nz = dense_ranges(ceil_div(N, D64_BN) * ceil_div(P, bm), steps, 8.0 * (double)P * (double)N,
-                            1.7 * bm / 128);
+        d.nz = f64_ranges(d.bm, P, N, steps);
         d.kz = ceil_div(steps, (int64_t)d.nz) * D64_KS;
-        if (d.nz > 1) d.part = take((size_t)d.nz * P * N * 8);
+        d.part = take(f64_partial_bytes(P, N, steps));
     }
     d.total = align_up(off, 256);
     return d;
@@ -1543,9 +1559,9 @@ poly_status dense_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_ex
     if (prec == POLY_SPLIT_BF16 && split_lds_bytes(n, S) > 160 * 1024) return POLY_ERR_UNSUPPORTED;
     // both kernels address one block's rows of C (up to 128 x K doubles, or
     // 256 x Kp BF16 digits of one plane) with 32-bit byte offsets
-    const int bm = prec == POLY_FP64 ? dense_f64_bm() : 64;
-    if ((int64_t)align_up((size_t)K, 32) * 8 * bm + 256 > INT32_MAX) return POLY_ERR_UNSUPPORTED;
     const DensePlan d = plan_dense(n, K, P, N, prec, S);
+    const int bm = d.bm;
+    if ((int64_t)align_up((size_t)K, 32) * 8 * bm + 256 > INT32_MAX) return POLY_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, (unsigned long long *)ws, 0ull, (int64_t)1);
     if (P == 0 || N == 0) return hipGetLastError() == hipSuccess ? POLY_OK : POLY_ERR_HIP;
     uint4 *enc = (uint4 *)((char *)ws + d.enc);
@@ -1624,7 +1640,8 @@ int64_t dx_chunk(int64_t K, int64_t N, poly_prec prec)
 struct DenseBwdPlan {
     size_t fenc, senc, gs, sigw, ct, gyt, w, part, cpart, total;
     int64_t Np, Pp, Nc, Kc;
-    int nz;        // point ranges of the FP64 dC
+    int bm;        // rows per workgroup of the FP64 dC
+    int nz;        // its point ranges
     int64_t nzp;   // points per range
 };
 
@@ -1657,14 +1674,14 @@ DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
         d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
     }
     d.cpart = 0;
+    d.bm = dense_f64_bm();
     d.nz = 1;
     d.nzp = N;
     if (prec == POLY_FP64 && K > 0 && P > 0 && N > 0) {
-        const int bm = dense_f64_bm();
         const int64_t steps = ceil_div(N, DB_KS);
-        d.nz = dense_ranges(ceil_div(K, DB_BN) * ceil_div(P, bm), steps, 8.0 * (double)P * (double)K, 1.7 * bm / 128);
+        d.nz = f64_ranges(d.bm, P, K, steps);
         d.nzp = ceil_div(steps, (int64_t)d.nz) * DB_KS;
-        if (d.nz > 1) d.cpart = take((size_t)d.nz * P * K * 8);
+        d.cpart = take(f64_partial_bytes(P, K, steps));
     }
     if (n <= DB_DX_MAX_N) {
         d.w = take((size_t)d.Kc * d.Nc * 8);
@@ -1790,7 +1807,7 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
             default: launch_bwd_dc_split<5>(n, K, basis, fenc, P, Gs, N, d.Np, X, sig_w, dC, s); break;
             }
         } else {
-            const int bm = dense_f64_bm();
+            const int bm = d.bm;
             const dim3 grid((unsigned)ceil_div(K, DB_BN), (unsigned)ceil_div(P, bm), (unsigned)d.nz);
             const size_t lds = (size_t)2 * DB_KS * (n + 1) * 8;
             double *out = d.nz > 1 ? (double *)((char *)ws + d.cpart) : dC;

@@ -37,3 +37,21 @@ def test_coefficient_gradients(n, P, T, N):
     slices = 8 * N * n * 256
     rest = 8 * T * min(n, 8) * (n + 50) + 24 * T + 64 * (P * n + 1000)
     assert ws.value <= max(8 * T * chunks, 2**28) + rest + (slices if P > 1 else 0)
+
+
+# output tiles few and many, 64 and 128 rows per workgroup
+@pytest.mark.parametrize("K,P,N", [(10626, 500, 5000), (10626, 100, 300), (300, 70, 200), (46376, 4096, 8192), (5000, 1, 5000)])
+def test_dense_workspace_holds_when_the_rows_change(K, P, N):
+    L = ph.lib()
+    old = ph.tune_get("dense_f64_rows")
+    sizes = []
+    try:
+        for rows in (64, 128):
+            ph.tune_set("dense_f64_rows", rows)
+            f, b = ctypes.c_size_t(), ctypes.c_size_t()
+            assert L.poly_eval_dense_workspace(20, K, P, N, 0, 5, ctypes.byref(f)) == 0
+            assert L.poly_eval_dense_backward_workspace(20, K, P, N, 0, 5, ctypes.byref(b)) == 0
+            sizes.append((f.value, b.value))
+    finally:
+        ph.tune_set("dense_f64_rows", old)
+    assert sizes[0] == sizes[1]
