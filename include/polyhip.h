@@ -389,8 +389,10 @@ poly_status poly_eval_dense(int32_t n, int64_t K, const uint8_t *basis, int32_t 
  *   dX[pt*n + j] = sum_k W[k][pt] * d v_k / d x_{j+1} (x_pt),
  *                  W = C^T gY                                   (may be NULL)
  * prec POLY_FP64: both on FP64 MFMA.  dC with V^T formed per step of
- * points; dX per tile of 128 points, the W tile of each 64 monomials formed
- * and contracted at once with the monomials' derivatives (W never stored).
+ * points; dX from W, stored for a chunk of at most 4,096 points and 512 MB at
+ * a time and contracted with the monomials' derivatives.
+ * The query is for both; a call for one of the two takes a workspace of its
+ * part.
  * prec POLY_SPLIT_BF16: the forward's split scheme on nslices (3..5) BF16
  * digits per operand, FP32 sums exact per 128-long block of the
  * contraction, FP64 accumulation across blocks.  dC: digits of gY and V^T
@@ -404,7 +406,8 @@ poly_status poly_eval_dense(int32_t n, int64_t K, const uint8_t *basis, int32_t 
  * outside 3..5 with POLY_SPLIT_BF16 is POLY_ERR_ARG; basis, C and X as in
  * poly_eval_dense.  The split workspace holds the digit planes of gY, C^T
  * and gY^T (2 * nslices bytes per padded element of each), the V^T scales,
- * one W chunk (8 * K * min(N, 4096) bytes) and 16 partial dX chunks. */
+ * one W chunk (8 * K * min(N, 4096) bytes) and its partial dX sums; what only
+ * dC needs shares memory with what only dX needs. */
 poly_status poly_eval_dense_backward_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec,
                                                int32_t nslices, size_t *ws_bytes);
 poly_status poly_eval_dense_backward(int32_t n, int64_t K, const uint8_t *basis, int32_t max_exp, int64_t P,

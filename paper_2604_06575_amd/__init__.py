@@ -138,7 +138,8 @@ def lib():
         f.argtypes = args
         f.restype = res
     # entry points of this binding with C++ linkage (not part of the C ABI):
-    # products with bounds on the operands' total degrees
+    # products and simplify with bounds on the operands' total degrees, and the
+    # dense reverse mode's workspace for what a call asks for
     inner = {
         "simplify_degree": ("PK8poly_csrPvPlS3_", [pcsr, P, P, P]),
         "product_degrees": ("PK8poly_csrS2_llPvPlS3_", [pcsr, pcsr, i64, i64, P, P, P]),
@@ -151,6 +152,8 @@ def lib():
                                      [pcsr, pcsr, i64, i64, i64, i32, i32, psz, ctypes.POINTER(i64)]),
         "mtimes_bounded": ("PK8poly_csrS2_llliiPS0_dPvmS4_",
                            [pcsr, pcsr, i64, i64, i64, i32, i32, pcsr, d, P, ctypes.c_size_t, P]),
+        "dense_bwd_workspace": ("illl9poly_precibbPm",
+                                [i32, i64, i64, i64, i32, i32, ctypes.c_bool, ctypes.c_bool, psz]),
     }
     for name, (signature, args) in inner.items():
         f = getattr(L, f"_ZN7polyhip{len(name)}{name}E{signature}")
@@ -926,7 +929,7 @@ def eval_dense_backward(basis: torch.Tensor, C: torch.Tensor, X: torch.Tensor, g
         raise ValueError(f"gY must be float64 [{P}, {N}]")
     _check_device("gY", gY, C.device)
     ws_bytes = ctypes.c_size_t()
-    _check(L.poly_eval_dense_backward_workspace(n, K, P, N, prec, nslices, ctypes.byref(ws_bytes)),
+    _check(L.dense_bwd_workspace(n, K, P, N, prec, nslices, want_dC, want_dX, ctypes.byref(ws_bytes)),
            "poly_eval_dense_backward_workspace")
     ws = _workspace(ws_bytes.value, C.device)
     dC = torch.empty((P, K), dtype=torch.float64, device=C.device) if want_dC else None

@@ -64,8 +64,8 @@ poly_status dense_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
 poly_status dense_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_exp, int64_t P, const double *C,
                       int64_t N, const double *X, double *Y, poly_prec prec, int32_t nslices, void *ws,
                       size_t ws_bytes, hipStream_t stream, int64_t ys);
-poly_status dense_bwd_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t nslices,
-                                size_t *ws_bytes);
+poly_status dense_bwd_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t nslices, bool dc,
+                                bool dx, size_t *ws_bytes);
 poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t max_exp, int64_t P, const double *C,
                           int64_t N, const double *X, const double *gY, double *dC, double *dX, poly_prec prec,
                           int32_t nslices, void *ws, size_t ws_bytes, hipStream_t s);
@@ -2799,7 +2799,7 @@ poly_status poly_eval_backward_workspace(const poly_csr *f, int64_t N, poly_prec
     if (prec == POLY_SPLIT_BF16) {
         const int64_t K = shared_row_length(f);
         if (K < 0) return POLY_ERR_UNSUPPORTED;
-        return dense_bwd_workspace(f->nvars, K, f->npolys, N, prec, nslices, ws_bytes);
+        return dense_bwd_workspace(f->nvars, K, f->npolys, N, prec, nslices, true, true, ws_bytes);
     }
     if (prec != POLY_FP64) return POLY_ERR_ARG;
     (void)nslices;
@@ -3404,7 +3404,7 @@ poly_status poly_eval_dense(int32_t n, int64_t K, const uint8_t *basis, int32_t 
 poly_status poly_eval_dense_backward_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec,
                                                int32_t nslices, size_t *ws_bytes)
 {
-    return dense_bwd_workspace(n, K, P, N, prec, nslices, ws_bytes);
+    return dense_bwd_workspace(n, K, P, N, prec, nslices, true, true, ws_bytes);
 }
 
 poly_status poly_eval_dense_backward(int32_t n, int64_t K, const uint8_t *basis, int32_t max_exp, int64_t P,

@@ -1646,12 +1646,13 @@ struct DenseBwdPlan {
 };
 
 // workspace: status word, factor lists and support encodings of the basis;
-// split: for dC the gY digit planes [S][ceil(P / 32) * 32][Np] and the scales
-// of V^T [ceil(N / DN_KB)][K]; for dX the digit planes of C^T [S][ceil(K /
-// 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp]; both precisions: one W
-// chunk [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n]; FP64: the
-// partial sums of dC's point ranges [nz][P][K]
-DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S)
+// for dC (dc) in split the gY digit planes [S][ceil(P / 32) * 32][Np] and the
+// scales of V^T [ceil(N / DN_KB)][K], in FP64 the partial sums of its point
+// ranges [nz][P][K]; for dX (dx) in split the digit planes of C^T [S][ceil(K /
+// 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp], in both one W chunk
+// [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n].  dC is done before dX
+// begins, so the two share their memory.
+DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S, bool dc, bool dx)
 {
     size_t off = kWsHeadBytes;
     auto take = [&](size_t b) {
@@ -1662,32 +1663,35 @@ DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
     DenseBwdPlan d;
     d.fenc = take(16 * (size_t)K);
     d.senc = take(16 * (size_t)K);
-    d.gs = d.sigw = d.ct = d.gyt = d.w = d.part = 0;
+    const size_t shared = off;
+    d.gs = d.sigw = d.ct = d.gyt = d.w = d.part = d.cpart = 0;
     d.Np = (int64_t)align_up((size_t)N, SP_KS);
     d.Pp = (int64_t)align_up((size_t)P, SP_KS);
     d.Nc = dx_chunk(K, N, prec);
     d.Kc = prec == POLY_SPLIT_BF16 ? K : std::min(K, DX_K_CHUNK);
-    if (prec == POLY_SPLIT_BF16) {
-        d.gs = take((size_t)S * ceil_div(P, 32) * 32 * d.Np * 2);
-        d.sigw = take((size_t)ceil_div(N, DN_KB) * K * 4);
-        d.ct = take((size_t)S * ceil_div(K, 32) * 32 * d.Pp * 2);
-        d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
-    }
-    d.cpart = 0;
     d.bm = dense_f64_bm();
     d.nz = 1;
     d.nzp = N;
-    if (prec == POLY_FP64 && K > 0 && P > 0 && N > 0) {
+    if (dc && prec == POLY_SPLIT_BF16) {
+        d.gs = take((size_t)S * ceil_div(P, 32) * 32 * d.Np * 2);
+        d.sigw = take((size_t)ceil_div(N, DN_KB) * K * 4);
+    } else if (dc && K > 0 && P > 0 && N > 0) {
         const int64_t steps = ceil_div(N, DB_KS);
         d.nz = f64_ranges(d.bm, P, K, steps);
         d.nzp = ceil_div(steps, (int64_t)d.nz) * DB_KS;
         d.cpart = take(f64_partial_bytes(P, K, steps));
     }
-    if (n <= DB_DX_MAX_N) {
+    const size_t end = off;
+    off = shared;
+    if (dx && n <= DB_DX_MAX_N) {
+        if (prec == POLY_SPLIT_BF16) {
+            d.ct = take((size_t)S * ceil_div(K, 32) * 32 * d.Pp * 2);
+            d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
+        }
         d.w = take((size_t)d.Kc * d.Nc * 8);
         d.part = take((size_t)dw_ksplit(d.Nc) * d.Nc * n * 8);
     }
-    d.total = align_up(off, 256);
+    d.total = align_up(std::max(off, end), 256);
     return d;
 }
 
@@ -1735,13 +1739,13 @@ void launch_bwd_dc_split(int n, int64_t K, const uint8_t *basis, const uint4 *en
 
 }  // namespace
 
-poly_status dense_bwd_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S,
-                                size_t *ws_bytes)
+poly_status dense_bwd_workspace(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S, bool dc,
+                                bool dx, size_t *ws_bytes)
 {
     if (!ws_bytes || n < 1 || n > 255 || K < 0 || P < 0 || N < 0) return POLY_ERR_ARG;
     if (prec != POLY_FP64 && prec != POLY_SPLIT_BF16) return POLY_ERR_ARG;
     if (prec == POLY_SPLIT_BF16 && (S < 3 || S > 5)) return POLY_ERR_ARG;
-    *ws_bytes = plan_dense_bwd(n, K, P, N, prec, S).total;
+    *ws_bytes = plan_dense_bwd(n, K, P, N, prec, S, dc, dx).total;
     return POLY_OK;
 }
 
@@ -1750,13 +1754,13 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
                           int32_t S, void *ws, size_t ws_bytes, hipStream_t s)
 {
     size_t need = 0;
-    poly_status st = dense_bwd_workspace(n, K, P, N, prec, S, &need);
+    poly_status st = dense_bwd_workspace(n, K, P, N, prec, S, dC != nullptr, dX != nullptr, &need);
     if (st != POLY_OK) return st;
     if (max_exp < 0 || max_exp > 255) return POLY_ERR_ARG;
     if ((K > 0 && !basis) || (P > 0 && K > 0 && !C) || (N > 0 && !X) || (P > 0 && N > 0 && !gY)) return POLY_ERR_ARG;
     if (!ws || ws_bytes < need) return POLY_ERR_WORKSPACE;
     if (dX && n > DB_DX_MAX_N) return POLY_ERR_UNSUPPORTED;
-    const DenseBwdPlan d = plan_dense_bwd(n, K, P, N, prec, S);
+    const DenseBwdPlan d = plan_dense_bwd(n, K, P, N, prec, S, dC != nullptr, dX != nullptr);
     // split dC: a step's coordinates are at most SW_XR_MAX per thread (n <= 64),
     // and a workgroup's rows of one gY plane stay below 2^31 bytes
     if (prec == POLY_SPLIT_BF16 && dC &&

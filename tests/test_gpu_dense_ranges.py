@@ -85,3 +85,27 @@ def test_dense_fp64_rows_64():
         ph.tune_set("dense_f64_rows", rows)
     assert (np.abs(Y - C @ v) <= 2 * (K + d + 4) * U * (np.abs(C) @ np.abs(v))).all()
     assert (np.abs(dC - gY @ v.T) <= 2 * (N + d + 4) * U * (np.abs(gY) @ np.abs(v).T)).all()
+
+
+# dX forms W in a chunk of 8 K min(N, 4096) bytes, dC leaves partial sums of
+# 8 P K bytes for each range of points: neither is asked for by a call that
+# wants the other alone, and both share memory in a call that wants both
+@pytest.mark.parametrize("prec", [ph.POLY_FP64, ph.POLY_SPLIT_BF16])
+def test_workspace_of_one_gradient(monkeypatch, prec):
+    rng = np.random.default_rng(9)
+    P, K, N, n, d = 300, 4000, 3000, 9, 4
+    t = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    args = t(_basis(rng, n, d, K)), t(rng.standard_normal((P, K))), t(rng.uniform(-1, 1, (N, n))), t(rng.standard_normal((P, N)))
+    asked = []
+    make = ph._workspace
+    monkeypatch.setattr(ph, "_workspace", lambda nbytes, device: (asked.append(nbytes), make(nbytes, device))[1])
+    dC, dX = ph.eval_dense_backward(*args, prec=prec)
+    c, _ = ph.eval_dense_backward(*args, prec=prec, want_dX=False)
+    _, x = ph.eval_dense_backward(*args, prec=prec, want_dC=False)
+    assert torch.equal(c, dC) and torch.equal(x, dX)
+    both, only_c, only_x = asked
+    assert both == max(only_c, only_x)
+    digits = 0 if prec == ph.POLY_FP64 else 5 * 2 * 320 * 3072 + 24 * 4 * K
+    assert only_c <= 16 * 8 * P * K * (prec == ph.POLY_FP64) + digits + 32 * K + 2048
+    if prec == ph.POLY_FP64:
+        assert 8 * K * N <= only_x <= 8 * K * (N + 128) + 64 * 8 * n * (N + 128) + 32 * K + 2048
