@@ -617,6 +617,7 @@ void launch_eval_blocks(EvalArgs A, uint32_t *enc, int64_t cap, bool exact, doub
     const dim3 grid = eval_grid(A.N, kWave, A.Q * S, tunables().eval_blocks_per_cu);
     const size_t lds = (size_t)(A.n + 1) * kWave * sizeof(double);
     A.ranges = A.Q * S;
+    A.terms = exact ? cap : 0;   // the kernels' choice is the host's
     A.words_cap = word_plane(cap);
     TimedLaunch tl(POLY_TIMING_TERMS, s);
     if (A.maxdeg && regeval_pays(A.n, 8, cap, A.ranges, A.N))   // at any degree class

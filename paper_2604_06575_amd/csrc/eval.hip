@@ -718,7 +718,7 @@ template <int FORM>
 __device__ inline bool eval_form_runs(const EvalArgs &A, uint32_t &md)
 {
     md = A.maxdeg ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*A.maxdeg) : 255u;
-    const bool reg = A.maxdeg && regeval_pays(A.n, md, A.rp[A.Q], A.ranges, A.N);
+    const bool reg = A.maxdeg && regeval_pays(A.n, md, A.terms > 0 ? A.terms : A.rp[A.Q], A.ranges, A.N);
     return FORM > EF_SHORT ? reg : (!reg && (FORM == EF_SHORT) == (md <= 4u));
 }
 

@@ -258,6 +258,7 @@ struct EvalArgs {
     int64_t term_limit;           // terms at or beyond this index are never read
     const uint32_t *maxdeg;       // bound on every term's degree (2 .. 6, 8; else 255), recorded by k_encode_factors, or null
     int64_t ranges;               // ranges that the terms are summed in
+    int64_t terms;                // their number where the host has planned by it, else 0 (rp has it)
     int64_t words_cap;            // words from one plane of k_encode_factors to the next
 };
 

@@ -126,3 +126,21 @@ def test_dc_in_passes(d):
     for k in t:
         v = np.prod(x[:, f[k]], axis=1) * gY[int(k >= rp[1])]
         assert np.abs(dC[k].item() - v.sum()) <= (N + d + 5) * U * np.abs(v).sum(), k
+
+
+def test_host_offsets_beyond_the_device_s():
+    """The library plans from the host's offsets and sums by the device's: a
+    batch whose host copy is only a bound is evaluated whole."""
+    rng = np.random.default_rng(500)
+    n, d, N = 20, 3, 1025
+    f, e, rp, c = _batch(rng, n, d, [100_000])
+    X = torch.from_numpy(rng.uniform(-1, 1, (N, n))).cuda()
+    for T in (0, 1, 100, 5000, 99_999):
+        b = ph.batch_from_numpy(rp, e, c)
+        b.row_ptr.copy_(torch.tensor([0, T]))
+        for k in range(4):   # values not written would be these
+            Y = torch.full((1, N), np.nan, dtype=torch.float64, device="cuda")
+        del Y
+        got = ph.eval(b, X).reshape(-1)
+        v = c[:T] * np.prod(_padded(X.cpu().numpy()[:50])[:, f[:T]], axis=2)
+        assert np.all(np.abs(got.cpu().numpy()[:50] - v.sum(1)) <= (T + d + 5) * U * np.abs(v).sum(1)), T
