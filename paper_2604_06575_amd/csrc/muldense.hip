@@ -224,6 +224,7 @@ __global__ void __launch_bounds__(256) k_md_sort(MulDenseArgs A, const int64_t *
         else hi = mid - 1;
     }
     const int64_t b0 = rp[lo], b1 = rp[lo + 1];
+    if (t >= b1) return;   // T is the host's, rp may hold fewer terms
     const uint64_t key = k[t];
     uint32_t before = 0;
 #pragma unroll 4
@@ -286,7 +287,8 @@ __global__ void __launch_bounds__(CUT_THREADS) k_md_cut(MulDenseArgs A, int64_t 
         if (lane == 0) {
             const int64_t a0 = A.a_rp[i0];
             s_dst[w * RPW + u] = (j * Ta + a0) * nb + (t - a0);
-            s_rows[w * RPW + u] = A.a_rp[i0 + A.K] - a0;
+            // none past the batch's last term (Ta is the host's, a_rp may hold fewer)
+            s_rows[w * RPW + u] = t0 + w * RPW + u < Ta && t < A.a_rp[lo + 1] ? A.a_rp[i0 + A.K] - a0 : 0;
         }
     }
     __syncthreads();
@@ -317,7 +319,7 @@ __global__ void __launch_bounds__(CUT_THREADS) k_md_cut(MulDenseArgs A, int64_t 
         __syncthreads();
         for (int i = tid; i < 64 * CUT_ROWS; i += CUT_THREADS) {
             const int b = i / CUT_ROWS, r = i % CUT_ROWS;
-            if (b0 + b < z1 && t0 + r < Ta) cut[s_dst[r] + (b0 + b) * s_rows[r]] = s_tile[b][r];
+            if (b0 + b < z1 && s_rows[r] > 0) cut[s_dst[r] + (b0 + b) * s_rows[r]] = s_tile[b][r];
         }
         __syncthreads();
     }

@@ -198,3 +198,19 @@ def test_no_memory_for_the_staged_cells(monkeypatch, own):
     with pytest.raises(torch.OutOfMemoryError):
         monkeypatch.setattr(ph, "_workspace", lambda nbytes, device: (_ for _ in ()).throw(torch.OutOfMemoryError()))
         ph.mul(a, b)
+
+
+def test_host_offsets_beyond_the_device_s():
+    """The host's offsets plan the launches, the device's say what the
+    operands are: where the host's copy is only a bound, the terms past the
+    device's last offset take no part."""
+    rng = W.rng_for(76001)
+    n, d = 6, 4
+    pa, pb = [_poly(rng, n, d, t) for t in (90, 150)], [_poly(rng, n, d, t) for t in (130, 170)]
+    for ta, tb in ((150, 100), (1, 170), (149, 1), (0, 170), (150, 170)):
+        a, b = _batch(pa, n, d), _batch(pb, n, d)
+        a.row_ptr[2] = 90 + ta
+        b.row_ptr[2] = 130 + tb
+        qa, qb = [pa[0], (pa[1][0][:ta], pa[1][1][:ta])], [pb[0], (pb[1][0][:tb], pb[1][1][:tb])]
+        want = [oracle.mul(*x, *y) if len(x[1]) else (np.zeros((0, n), np.uint8), np.zeros(0)) for x, y in zip(qa, qb)]
+        _same(ph.mul(a, b), W.csr_from_list(want, n))

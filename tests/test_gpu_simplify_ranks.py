@@ -78,3 +78,18 @@ def test_degree_is_read_whole(n, T):
         assert ph.lib().simplify_degree(ctypes.byref(c), scratch.data_ptr(), words.data_ptr(),
                                         torch.cuda.current_stream().cuda_stream) == 0
         assert int(words[0]) == 4
+
+
+def test_host_offsets_beyond_the_device_s():
+    rng = np.random.default_rng(77)
+    sizes = [3000, 20, 400, 9000]
+    rp, e, c = _batch(rng, 7, 4, sizes)
+    for last in (0, 1, 300, 8999):
+        b = ph.batch_from_numpy(rp, e, c)
+        b.row_ptr[4] = int(rp[3]) + last
+        T = int(rp[3]) + last
+        drp = np.append(rp[:4], T)
+        orp, oe, oc = oracle.simplify_batch(drp, e[:T], c[:T], 0.0, n=7)
+        grp, ge, gc = ph.batch_to_numpy(ph.simplify(b))
+        assert np.array_equal(grp, orp) and np.array_equal(ge, oe)
+        assert np.array_equal(gc.view(np.uint64), np.asarray(oc).view(np.uint64))
