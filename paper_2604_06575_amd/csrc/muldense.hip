@@ -376,7 +376,7 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
         s_claim[c] = ~0u;
     }
     bool any = false;
-    bool outside = false;   // a product's cell is in another range: never, if the cuts are those of its keys
+    uint32_t last = 0;   // largest cell met: within the range, if the cuts are those of the products' keys
     for (int64_t r0 = 0; r0 < rows; r0 += SR) {
         // ---- rows of this step that meet the range, in row order
         const int64_t rb = r0 + tid * RB;
@@ -477,8 +477,8 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
 #pragma unroll
                 for (int u = 0; u < IT; ++u) {
                     const uint32_t c = A.cells - 1u - cell[u] - c0;
-                    outside |= c >= A.cpr;
-                    cell[u] = c < A.cpr ? c : 0;
+                    last = c > last ? c : last;
+                    cell[u] = c < A.cpr ? c : A.cpr - 1;
                 }
             }
             // ---- rounds: the earliest pending product of each cell is added.
@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(NT) k_md_range(MulDenseArgs A)
             } while (block_any<NT>(pend != 0));
         }
     }
-    if (outside) set_status(A.status, POLY_ERR_EXPONENT);
+    if (last >= A.cpr) set_status(A.status, POLY_ERR_EXPONENT);
     __syncthreads();
     // ---- kept cells in order
     const uint32_t span = c1 - c0;
