@@ -148,17 +148,21 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
     // 256 apart at first) put theirs on different SIMDs
     const int pw = (int)(blockIdx.x >> 8) % NW;
     const int m = n - 1;
+    // The gradient adds up by waves, in vectors that are free until it is
+    // complete: in the waves' order it is the same from call to call.
+    auto grad_sum = [&](int q) { return q < 7 ? e + q * n : reinterpret_cast<double *>(piv); };
     for (int64_t pt = blockIdx.x; pt < N; pt += gridDim.x) {
         __syncthreads();
         for (int i = tid; i < n; i += NT) {
             x[i] = X[pt * n + i];
-            e[i] = 0.0;
-            w[i] = he[i] = t[i] = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) grad_sum(q)[i] = 0.0;
         }
         if (tid == 0) x[n] = 1.0;
-        // ---- gradient (into e) and Hessian, term by term: the upper triangle
-        // adds up in LDS (in row blocks where the matrix does not fit), then
-        // both triangles are stored
+        // ---- gradient (by waves) and Hessian, term by term: the upper
+        // triangle adds up in LDS (in row blocks where the matrix does not
+        // fit), then both triangles are stored
+        double *const gw = grad_sum(wv);
         const int rows = LDSM ? n : AN_BLOCK_DOUBLES / (n | 1);
         const int pitch = LDSM ? ld : (n | 1);
         for (int r0 = 0; r0 < n; r0 += rows) {
@@ -179,10 +183,10 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
                     const double y0 = x[fi[0]], y1 = x[fi[1]], y2 = x[fi[2]], y3 = x[fi[3]];
                     if (r0 == 0) {
                         const double c01 = c * y0 * y1, c23 = c * y2 * y3;
-                        if (d > 0) lds_add(&e[fi[0]], y1 * c23);
-                        if (d > 1) lds_add(&e[fi[1]], y0 * c23);
-                        if (d > 2) lds_add(&e[fi[2]], y3 * c01);
-                        if (d > 3) lds_add(&e[fi[3]], y2 * c01);
+                        if (d > 0) lds_add(&gw[fi[0]], y1 * c23);
+                        if (d > 1) lds_add(&gw[fi[1]], y0 * c23);
+                        if (d > 2) lds_add(&gw[fi[2]], y3 * c01);
+                        if (d > 3) lds_add(&gw[fi[3]], y2 * c01);
                     }
                     auto pair = [&](int a, int b, double val) {
                         if (b < d && (LDSM || (fi[a] >= r0 && fi[a] < r1)))
@@ -197,7 +201,7 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
                 } else {
                     for (int a = 0; a < d; ++a) {
                         const int fa = factor(f, a);
-                        if (r0 == 0) lds_add(&e[fa], c * product_but(f, d, x, a, a, a));
+                        if (r0 == 0) lds_add(&gw[fa], c * product_but(f, d, x, a, a, a));
                         if (fa < r0 || fa >= r1) continue;
                         for (int b = a + 1; b < d; ++b) {
                             const int fb = factor(f, b);
@@ -220,7 +224,14 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
             __syncthreads();
         }
         double part = 0.0;
-        for (int i = tid; i < n; i += NT) part += e[i] * e[i];
+        for (int i = tid; i < n; i += NT) {
+            double ei = e[i];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) ei += grad_sum(q)[i];
+            e[i] = ei;
+            part += ei * ei;
+            w[i] = he[i] = t[i] = 0.0;
+        }
         const double gn = sqrt(sum_block<NW>(part, s_red));
         const double sgn = e[m] / gn >= 0.0 ? 1.0 : -1.0;
         __syncthreads();

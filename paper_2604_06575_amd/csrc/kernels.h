@@ -346,7 +346,7 @@ __host__ __device__ constexpr size_t affine_lds_bytes(int n)
 {
     const AffineShape s = affine_shape(n);
     return ((n <= AN_MAX_N_LDS ? (size_t)s.L * s.ld : (size_t)AN_BLOCK_DOUBLES) + 8 * (size_t)n + 1) * sizeof(double) +
-           2 * (size_t)s.mp * sizeof(int);
+           sizeof(double) * (size_t)(s.mp > n ? s.mp : n);   // two int [mp], before them double [n]
 }
 template <int NW, int PW, int NB, bool LDSM>
 __global__ void k_affine_normal(int n, const uint4 *__restrict__ enc, const double *__restrict__ coefs, int64_t T,

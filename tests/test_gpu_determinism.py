@@ -3,9 +3,10 @@ same bits.  Keys, counts and order are fixed by construction everywhere;
 coefficients and values are fixed wherever the summation order is (merges
 sum runs left to right in one lane, evaluations sum terms in order, the MFMA
 contractions accumulate in a fixed order).  Paths that add into LDS with
-atomics (the affine-normal kernels' third-derivative contractions, the fused
-derivative kernels, the dense reverse mode's dX) are checked to agree to
-rounding instead."""
+atomics (the affine-normal kernels' Hessians and third-derivative contractions,
+the fused derivative kernels, the dense reverse mode's dX) are checked to agree
+to rounding instead; the affine-normal route's gradient, and with it |g|, adds
+up in a fixed order."""
 import sys
 
 import numpy as np
@@ -108,3 +109,43 @@ def test_affine_paths_agree_to_rounding(ph):
     S2, _, h2 = ph.affine_normal_stochastic(b, X, Z, reg=1e-8, tol=1e-10, maxit=40)
     assert torch.allclose(S1, S2, rtol=1e-12, atol=1e-12)
     assert torch.equal(h1, h2)
+
+
+# four waves per point, eight with the matrix in LDS, eight with it in the
+# workspace; factor lists of one word and longer
+@pytest.mark.parametrize("n,d,terms,N", [(12, 4, 400, 300), (65, 4, 3000, 130), (40, 7, 600, 70), (100, 4, 3000, 40), (160, 4, 4000, 9)])
+def test_affine_gradient_norm(ph, n, d, terms, N):
+    rng = W.rng_for(99 + n)
+    e = np.zeros((terms, n), np.uint8)
+    np.add.at(e, (np.arange(terms)[:, None], rng.integers(0, n, (terms, d))), 1)
+    b = ph.batch_from_numpy([0, terms], e, rng.standard_normal(terms), n=n)
+    X = torch.from_numpy(rng.uniform(-1, 1, (N, n))).cuda()
+    g = [ph.affine_normal(b, X, reg=1.0)[1] for _ in range(6)]
+    for x in g[1:]:
+        assert np.array_equal(bits(g[0]), bits(x))
+
+
+def test_affine_paths_agree_on_an_ill_conditioned_block(ph):
+    """Two runs differ by the rounding of the sums that make up A, the tangent
+    block: by a few n * 2**-53 times its condition number."""
+    import oracle
+    rng = W.rng_for(100)
+    n = 12
+    e = np.zeros((2 * n + 200, n), np.uint8)
+    e[:n][np.arange(n), np.arange(n)] = 2
+    e[n:2 * n][np.arange(n), np.arange(n)] = 1
+    np.add.at(e, (2 * n + np.arange(200)[:, None], rng.integers(0, n, (200, 4))), 1)
+    c = np.concatenate([10.0 ** -np.linspace(0, 8, n), rng.uniform(1, 2, n), 1e-9 * rng.standard_normal(200)])
+    X = rng.uniform(-1, 1, (30, n))
+    b, t = ph.batch_from_numpy([0, len(c)], e, c, n=n), torch.from_numpy(X).cuda()
+    D = [ph.affine_normal(b, t, reg=1e-8) for _ in range(4)]
+    for x in D[1:]:
+        assert np.array_equal(bits(D[0][1]), bits(x[1]))
+    for i in range(len(X)):
+        g, H, _ = oracle.derivatives_at(e, c, X[i])
+        Q = oracle.tangent_frame(g)[:, :n - 1]
+        kappa = np.linalg.cond(Q.T @ H @ Q + 1e-8 * np.eye(n - 1))
+        assert kappa > 1e6
+        for x in D[1:]:
+            diff = (x[0][i] - D[0][0][i]).abs().max().item()
+            assert diff <= 16 * n * 2.0**-53 * kappa * D[0][0][i].abs().max().item()
