@@ -579,14 +579,20 @@ __device__ inline double lane_f64(double v, int k)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// acc + the sum of c_t * m_t(x) over terms [ta, tb), in term order.  Term records
+// Sum of c_t * m_t(x) over terms [ta, tb), in term order.  Term records
 // travel in groups of 64: lane l loads the record of term g0 + l (one
 // coalesced load per field), each term is read out of its lane into scalar
 // registers, and the next group's loads are in flight while the current
 // group is evaluated.  Only the factor words a term's degree needs are read.
 __device__ inline double term_range(const EvalArgs &A, const uint32_t *enc, int64_t ta, int64_t tb,
-                                    const double *xl, double acc = 0.0)
+                                    const double *xl)
 {
+    // the range is the same on every lane: with its bounds in vector registers
+    // every term's loop control is vector work (10 variables, 50,000 terms of
+    // degree 6, 64 points: k_eval_wsum 2,360 us, 2,214)
+    ta = uniform_i64(ta);
+    tb = uniform_i64(tb);
+    double acc = 0.0;
     const uint4 *ev = reinterpret_cast<const uint4 *>(enc);
     const int lane = lane_id();
     uint4 gw = make_uint4(0, 0, 0, 0);
