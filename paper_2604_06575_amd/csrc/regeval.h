@@ -178,24 +178,28 @@ __host__ __device__ constexpr int regeval_points(int rows) { return rows > 56 ? 
 // terms or a segment of them) are evaluated from registers.  A range costs the
 // load of all rows, the wait for the first terms and a few terms from LDS at
 // its end, with two waves on a SIMD to hide them (four up to 23 variables), so
-// short ranges stay in LDS.  Past degree class 4 the LDS form takes a term's
-// record apart lane by lane and the line lies lower.  Measured at 1,024 points,
-// registers / LDS, at ranges just below and above the line: 20 variables,
-// degree 3: 38 terms 208 / 233 us, 19 terms 278 / 250 us; 40 variables, degree
-// 4: 85 terms 90 / 93 us, 32 terms 121 / 99 us; 100 variables, degree 4: 781
-// terms (8,192 points) 227 / 364 us, 93 terms 122 / 107 us.  Degree 6: 20
-// variables 9 terms 769 / 1,015 us, 4 terms 1,498 / 1,416 us; 40 variables 32
-// terms 129 / 166 us, 16 terms 193 / 178 us; 100 variables 64 terms 143 / 178
-// us, 32 terms 204 / 193 us.  The lower line counts from 2^28 terms times
-// points on, and none does below 2^26: the host knows neither the degree nor
-// the number of derivative terms, and the launch of a kernel that turns out
-// not to run would be more than 2% of the call.
+// short ranges stay in LDS.  Measured at 1,024 points, registers / LDS, at
+// ranges just above and below the line: 20 variables, degree 3: 38 terms 208 /
+// 233 us, 19 terms 278 / 250 us; 40 variables, degree 4: 85 terms 90 / 93 us,
+// 32 terms 121 / 99 us; 100 variables, degree 4: 781 terms (8,192 points) 227 /
+// 364 us, 93 terms 122 / 107 us.  Past degree class 4 the LDS form takes a
+// term's record apart lane by lane and the line lies lower, from 2^28 terms
+// times points on; but it reads only the factor words that a term's own degree
+// needs, and the registers all of the class's, so the line is that of terms of
+// every degree up to the class's.  2,048 points, 2^28 terms times points,
+// registers / LDS, for degrees 0 to 6, then for 6 alone: 20 variables, 16 terms
+// 217 / 266, 221 / 321 us, 12 terms 295 / 250, 298 / 321; 40 variables, 48
+// terms 230 / 242, 234 / 301, 32 terms 251 / 236, 257 / 299; 60 variables, 100
+// terms 236 / 236, 240 / 304, 64 terms 246 / 239, 247 / 295.  None does below
+// 2^26: the host knows neither the degree nor the number of derivative terms,
+// and the launch of a kernel that turns out not to run would be more than 2% of
+// the call.
 __host__ __device__ inline bool regeval_pays(int n, uint32_t md, int64_t terms, int64_t ranges, int64_t N)
 {
     if (n > RE_MAX_N || md > 8 || terms * N < ((int64_t)1 << 26)) return false;
     const int rows = regeval_rows(n);
     const bool low = md > 4 && terms * N >= ((int64_t)1 << 28);
-    const int range = low ? (rows == 24 ? 8 : (rows == 56 ? 24 : 48)) : (rows == 24 ? 40 : (rows == 56 ? 80 : 384));
+    const int range = low ? (rows == 24 ? 16 : (rows == 56 ? 40 : 96)) : (rows == 24 ? 40 : (rows == 56 ? 80 : 384));
     return terms >= ranges * range;
 }
 
