@@ -1329,8 +1329,14 @@ __global__ void __launch_bounds__(SP_THREADS) k_split_gemm(int64_t R, int64_t RB
 
 constexpr int DW_WAVES = 4;
 
-// K ranges of k_dx_from_w for a chunk of Nc points: about 1,024 workgroups
-inline int dw_ksplit(int64_t Nc) { return (int)std::max<int64_t>(1, std::min<int64_t>(64, 65536 / std::max<int64_t>(Nc, 1))); }
+// K ranges of k_dx_from_w for a chunk of Nc points: about 1,024 workgroups, but
+// past 16 ranges none shorter than 64 monomials, since k_dx_reduce reads them
+// one after another (70 monomials, 64 points: 17 us for 64 ranges, 5 for 16)
+inline int dw_ksplit(int64_t K, int64_t Nc)
+{
+    const int64_t most = std::min<int64_t>(64, std::max<int64_t>(16, K / 64));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(most, 65536 / std::max<int64_t>(Nc, 1)));
+}
 
 // Partial dX of a chunk of points from W [K x ldw] (FP64): block (point
 // tile of 64, K range q of gridDim.y), wave w the w-th quarter of that range;
@@ -1650,7 +1656,7 @@ struct DenseBwdPlan {
 // scales of V^T [ceil(N / DN_KB)][K], in FP64 the partial sums of its point
 // ranges [nz][P][K]; for dX (dx) in split the digit planes of C^T [S][ceil(K /
 // 32) * 32][Pp] and of gY^T [S][ceil(N / 32) * 32][Pp], in both one W chunk
-// [Kc][Nc] and the partial sums [dw_ksplit(Nc)][Nc][n].  dC is done before dX
+// [Kc][Nc] and the partial sums [dw_ksplit(Kc, Nc)][Nc][n].  dC is done before dX
 // begins, so the two share their memory.
 DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_prec prec, int32_t S, bool dc, bool dx)
 {
@@ -1689,7 +1695,7 @@ DenseBwdPlan plan_dense_bwd(int32_t n, int64_t K, int64_t P, int64_t N, poly_pre
             d.gyt = take((size_t)S * ceil_div(N, 32) * 32 * d.Pp * 2);
         }
         d.w = take((size_t)d.Kc * d.Nc * 8);
-        d.part = take((size_t)dw_ksplit(d.Nc) * d.Nc * n * 8);
+        d.part = take((size_t)dw_ksplit(d.Kc, d.Nc) * d.Nc * n * 8);
     }
     d.total = align_up(std::max(off, end), 256);
     return d;
@@ -1843,7 +1849,7 @@ poly_status dense_bwd_run(int32_t n, int64_t K, const uint8_t *basis, int32_t ma
             hipLaunchKernelGGL(k_split_ct, dim3((unsigned)(ceil_div(N, 32) * nkb)), dim3(DN_KB), 0, s, gY, N, N, P,
                                d.Pp, S, Gts);
         }
-        const int ksplit = dw_ksplit(d.Nc);
+        const int ksplit = dw_ksplit(d.Kc, d.Nc);
         for (int64_t c0 = 0; c0 < N; c0 += d.Nc)
             for (int64_t k0 = 0; k0 < K; k0 += d.Kc) {   // split: one range
                 const int64_t nc = std::min<int64_t>(d.Nc, N - c0), kc = std::min<int64_t>(d.Kc, K - k0);
