@@ -113,6 +113,39 @@ __device__ inline double product_but(const uint4 &f, int d, const double *x, int
     return val;
 }
 
+// A list's runs of one variable: bit r where one begins at slot r; its length.
+// Derivatives of a list longer than a word are formed by runs, a variable's
+// multiplicity as a number, where every lane's are few, else slot by slot, the
+// same slots on every lane.  1,000 terms of degree up to 12 in 8 variables,
+// 1,000 points: 1,570 us by runs, 4,200 by slots; 5,000 terms of degree up to 6
+// in 20 variables, 500 points: 1,275 by runs, 815 by slots.
+__device__ inline uint32_t run_starts(const uint4 &f, int d)
+{
+    uint32_t m = 1;
+    for (int r = 1; r < d; ++r) m |= (uint32_t)(factor(f, r) != factor(f, r - 1)) << r;
+    return m;
+}
+
+__device__ inline int run_length(uint32_t runs, int d, int a)
+{
+    const uint32_t after = runs >> a >> 1;
+    return after ? __ffs((int)after) : d - a;
+}
+
+// Whether the active lanes' lists (d > 4) are taken by runs: an eighth of the
+// steps is the price of slots that differ from lane to lane.
+__device__ inline bool by_runs(uint32_t runs, int d)
+{
+    const int s = __popc(runs);
+    int most = 0, longest = 0;
+#pragma unroll
+    for (int k = 1; k <= EV_MAX_DEG; ++k) {
+        most = __any(s >= k) ? k : most;
+        longest = __any(d >= k) ? k : longest;
+    }
+    return 2 * most * most * (most + 1) <= longest * (longest - 1) * (longest - 2);
+}
+
 }  // namespace
 
 template <int NW, int PW, int NB, bool LDSM>
@@ -199,7 +232,9 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
                     pair(1, 3, c * (y0 * y2));
                     pair(2, 3, c * (y0 * y1));
                 } else {
-                    for (int a = 0; a < d; ++a) {
+                    const uint32_t runs = run_starts(f, d);
+                    const bool whole = by_runs(runs, d);
+                    for (int a = 0; a < d && !whole; ++a) {
                         const int fa = factor(f, a);
                         if (r0 == 0) lds_add(&gw[fa], c * product_but(f, d, x, a, a, a));
                         if (fa < r0 || fa >= r1) continue;
@@ -207,6 +242,17 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
                             const int fb = factor(f, b);
                             const double val = c * product_but(f, d, x, a, b, b);
                             lds_add(&A[(fa - r0) * pitch + fb], fa == fb ? 2.0 * val : val);
+                        }
+                    }
+                    for (uint32_t ma = whole ? runs : 0u; ma; ma &= ma - 1) {
+                        const int a = __ffs((int)ma) - 1, fa = factor(f, a), ka = run_length(runs, d, a);
+                        if (r0 == 0) lds_add(&gw[fa], (double)ka * c * product_but(f, d, x, a, a, a));
+                        if (fa < r0 || fa >= r1) continue;
+                        for (uint32_t mb = ma; mb; mb &= mb - 1) {
+                            const int b = __ffs((int)mb) - 1, kb = b == a ? ka - 1 : run_length(runs, d, b);
+                            if (kb > 0)
+                                lds_add(&A[(fa - r0) * pitch + factor(f, b)],
+                                        (double)(ka * kb) * c * product_but(f, d, x, a, b == a ? a + 1 : b, a));
                         }
                     }
                 }
@@ -472,13 +518,32 @@ __global__ void __launch_bounds__(NW * kWave, NW == 4 ? 4 : 2) k_affine_normal(i
                     lds_add(&w[f3], m01 * y2 + m02 * y1 + m12 * y0);
                 }
             } else {
-                for (int a = 0; a < d; ++a)
+                const uint32_t runs = run_starts(f, d);
+                const bool whole = by_runs(runs, d);
+                for (int a = 0; a < d && !whole; ++a)
                     for (int b = a + 1; b < d; ++b) {
                         const int fa = factor(f, a), fb = factor(f, b);
                         const double mab = c * (entry(fa, fb) + entry(fb, fa));
                         for (int l = 0; l < d; ++l)
                             if (l != a && l != b) lds_add(&w[factor(f, l)], mab * product_but(f, d, x, a, b, l));
                     }
+                for (uint32_t ma = whole ? runs : 0u; ma; ma &= ma - 1) {
+                    const int a = __ffs((int)ma) - 1, fa = factor(f, a), ka = run_length(runs, d, a);
+                    for (uint32_t mb = ma; mb; mb &= mb - 1) {
+                        // slots a and b, and how many pairs of slots are of these variables
+                        const int b0 = __ffs((int)mb) - 1, b = b0 == a ? a + 1 : b0;
+                        const int pairs = b0 == a ? ka * (ka - 1) / 2 : ka * run_length(runs, d, b);
+                        if (pairs == 0) continue;
+                        const int fb = factor(f, b);
+                        const double mab = (double)pairs * c * (entry(fa, fb) + entry(fb, fa));
+                        for (uint32_t ml = runs; ml; ml &= ml - 1) {
+                            const int l0 = __ffs((int)ml) - 1, used = (l0 == a) + (l0 == b0);
+                            const int kl = run_length(runs, d, l0) - used;
+                            if (kl > 0)
+                                lds_add(&w[factor(f, l0)], (double)kl * mab * product_but(f, d, x, a, b, l0 + used));
+                        }
+                    }
+                }
             }
         }
         __syncthreads();

@@ -119,3 +119,58 @@ def test_matrix_in_global_memory(ph):
     wl = W.sparse_quartic(seed=W.SEED_BASE + 221, n=130, npts=1)
     say("affine normal: sparse quartic n=130")
     _check(ph, wl.exps, wl.coefs, wl.X, 1e-8, tol=1e-8)
+
+
+def _by_slots(e, c, x, reg):
+    """The direction at one point, its derivatives summed over the factor slots
+    of each monomial in long double, and the condition of the tangent block."""
+    n = len(x)
+    xl = x.astype(np.longdouble)
+    g, H = np.zeros(n, np.longdouble), np.zeros((n, n), np.longdouble)
+    lists = [np.repeat(np.arange(n), r) for r in e.astype(int)]
+    but = lambda f, out: np.prod(xl[np.delete(f, out)])   # noqa: E731
+    for f, k in zip(lists, c):
+        for a in range(len(f)):
+            g[f[a]] += k * but(f, [a])
+            for b in range(len(f)):
+                if a != b:
+                    H[f[a], f[b]] += k * but(f, [a, b])
+    Q = oracle.tangent_frame(g.astype(np.float64))
+    QT = Q[:, :n - 1]
+    A = QT.T @ H.astype(np.float64) @ QT + reg * np.eye(n - 1)
+    M = QT @ np.linalg.inv(A) @ QT.T
+    w = np.zeros(n, np.longdouble)
+    for f, k in zip(lists, c):
+        for a in range(len(f)):
+            for b in range(len(f)):
+                for l in range(len(f)):
+                    if a != b and a != l and b != l:
+                        w[f[l]] += k * M[f[a], f[b]] * but(f, [a, b, l])
+    gn = np.linalg.norm(g.astype(np.float64))
+    unit = g.astype(np.float64) / gn
+    return M @ (H.astype(np.float64) @ unit - gn / (n + 1) * w.astype(np.float64)) - unit, gn, np.linalg.cond(A)
+
+
+# degrees past one factor word with variables repeated up to the whole degree:
+# a workgroup of four waves, of eight, and with the matrix in the workspace
+# (row blocks of the Hessian)
+@pytest.mark.parametrize("n,d,terms,npts", [(2, 12, 30, 6), (3, 9, 40, 6), (8, 12, 60, 3), (20, 6, 80, 3), (70, 7, 60, 2), (140, 5, 150, 2)])
+def test_repeated_variables(ph, n, d, terms, npts):
+    rng = W.rng_for(7700 + n)
+    e = np.zeros((terms + 2 * n, n), np.uint8)
+    for r in e[:terms]:
+        for i in rng.choice(n, min(n, 3), replace=False)[rng.integers(0, min(n, 3), rng.integers(0, d + 1))]:
+            r[i] += 1
+    e[0] = 0
+    e[0, n - 1] = d
+    e[terms:terms + n][np.arange(n), np.arange(n)] = 2      # a well-conditioned block
+    e[terms + n:][np.arange(n), np.arange(n)] = 1
+    c = np.concatenate([0.1 * rng.standard_normal(terms), rng.uniform(2, 3, n), rng.uniform(0.5, 1, n)])
+    X = rng.uniform(-0.8, 0.8, (npts, n))
+    b = ph.batch_from_numpy([0, len(c)], e, c, n=n)
+    D, gn = ph.affine_normal(b, torch.from_numpy(X).cuda(), reg=1e-3)
+    for i in range(npts):
+        want, norm, kappa = _by_slots(e, c, X[i], 1e-3)
+        tol = 64 * n * 2.0**-53 * kappa
+        assert np.abs(D[i].cpu().numpy() - want).max() <= tol * np.abs(want).max()
+        assert abs(gn[i].item() - norm) <= 8 * (terms + d) * 2.0**-53 * norm
