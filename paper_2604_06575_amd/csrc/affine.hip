@@ -20,7 +20,8 @@
 // added up term by term in LDS from each monomial's factor list (variables in
 // ascending order, degree <= EV_MAX_DEG): every pair of factor slots adds the
 // product of the other factors, so repeated variables get their multiplicity
-// by themselves.  (Streaming the formed derivative polynomials over all
+// by themselves (lists longer than four factors also by runs of a variable).
+// The gradient adds up in a fixed order, the Hessian, H e and w as they come.  (Streaming the formed derivative polynomials over all
 // points, and passing the Hessians through memory, took 0.42 of 1.48 ms at
 // n = 64, 4,096 points, most of it in 29 small launches.)  A is inverted in
 // place by a blocked Gauss-Jordan elimination with partial pivoting:
@@ -36,9 +37,12 @@
 // of the workspace beyond.  n <= AN_WAVE_N takes four waves per point, one of
 // which holds the whole panel (no barrier within it), and four points per CU,
 // so that one point's panel runs beside another's MFMAs; larger n eight waves,
-// four of them for the panel.  Bound by the panels' serial chain:
-// a pivot search, a reciprocal and a row update per column.
-// n = 64, 320 terms, 4,096 points: 1,050 us as the kernels before it, 288 us.
+// four of them for the panel.  At n = 64 the panels, a serial chain of a pivot
+// search, a reciprocal and a row update per column, take 40% of a point's clocks,
+// the updates 24 and the gradient and Hessian 13; at n = 160 the updates take
+// 53%, each going through the matrix in the workspace (0.96 GB of traffic for
+// 256 points), and the panels 28.
+// n = 64, 320 terms, 4,096 points: 1,050 us as the kernels before it, 281 us.
 // n = 160, 800 terms, 256 points: 7,060 us, 473 us.
 #include <limits.h>
 

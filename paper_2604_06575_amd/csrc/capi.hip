@@ -1547,9 +1547,12 @@ static bool dense_product_possible(MulDensePlan &m, const poly_csr *a, const pol
 }
 
 // The route is taken where it can be (few variables, keys of 63 bits, cell
-// numbers of 31, an entry's rows in LDS) and where an output entry is dense
-// enough: every cell is cleared, scanned and unpacked whether or not a product
-// falls on it, which costs about an eighth of a raw product's own work.
+// numbers of 31, an entry's rows in LDS) and for at most eight cells to a raw
+// product.  That line is one of memory, 12 bytes being staged for every cell: 96
+// for a raw product there, against the general route's 16 to 40.  By time it
+// could lie further out: 600 pairs in 8 variables, 8 cells 205 / 322 us, 60
+// cells 184 / 302; 400 pairs in 10 variables, 8 cells 284 / 425, 12 cells 274 /
+// 303, 60 cells 240 / 274.
 static MulDensePlan plan_mul_dense(const poly_csr *a, const poly_csr *b, int64_t I, int64_t K, int64_t J, int da, int db,
                             int64_t raw)
 {

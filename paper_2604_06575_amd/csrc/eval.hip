@@ -849,7 +849,9 @@ __global__ void __launch_bounds__(EV_THREADS) k_eval_terms_short(EvalArgs A, con
 
 // The same for batches of degree class <= 8 in at most RE_MAX_N variables,
 // coordinates in registers.  Bound by the issue of scalar and vector
-// instructions.  A quartic of 100,000 terms in 100 variables at 8,192 points
+// instructions (n = 20, degree 6: vector instructions in 86% of the cycles that
+// a CU is busy, scalar ones in 54%; n = 100: 66% and 73% in k_eval_wsum_reg, two
+// waves to a SIMD).  A quartic of 100,000 terms in 100 variables at 8,192 points
 // (one point a lane, 254 registers): 364 us from LDS, 215 us; gradients of 256
 // polynomials of degree 6 in 20 variables, 4.3 million derivative terms at
 // 1,000 points (two points a lane, 128 registers): 3,400 us, 1,000 us.

@@ -26,11 +26,13 @@
 //     meets few products of one chunk and a handful of rounds do;
 //   * cells with a sum above the tolerance are staged in order; exponents are
 //     recovered from the rank when the result is unpacked.
-// Bound by instruction issue and LDS latency, not by memory: the raw product
-// stays on chip.  5,000 x 5,000 terms in
-// 10 variables (25 million raw products, 5.3 million cells): k_md_range 331 us
-// (75 G raw products/s), k_md_cut 71, the whole call 0.58 ms with read-backs;
-// the radix sort of the raw product's 41-bit keys took 1.36 ms.  600 pairs of
+// The raw product stays on chip.  k_md_range is bound by the latency of its LDS
+// rounds: of the cycles that its CUs are busy, vector instructions take 43% and
+// LDS 44% (20 of them bank conflicts), and a wave waits for 56% of its time.
+// 5,000 x 5,000 terms in 10 variables (25 million raw products, 5.3 million
+// cells): k_md_range 317 us (79 G raw products/s), k_md_cut 71, the whole call
+// 0.56 ms with read-backs; the radix sort of the raw product's 41-bit keys took
+// 1.36 ms.  600 pairs of
 // 6 to 300 terms in 8 variables: 77 + 31 us, the call 0.26 against 0.98 ms.
 // Ordering each chunk by an LDS counting sort instead of claims: 592 us.
 #include "kernels.h"
