@@ -21,10 +21,11 @@
 // ascending order, degree <= EV_MAX_DEG): every pair of factor slots adds the
 // product of the other factors, so repeated variables get their multiplicity
 // by themselves (lists longer than four factors also by runs of a variable).
-// The gradient adds up in a fixed order, the Hessian, H e and w as they come.  (Streaming the formed derivative polynomials over all
-// points, and passing the Hessians through memory, took 0.42 of 1.48 ms at
-// n = 64, 4,096 points, most of it in 29 small launches.)  A is inverted in
-// place by a blocked Gauss-Jordan elimination with partial pivoting:
+// The gradient adds up in a fixed order, the Hessian, H e and w as they come.
+// (Streaming the formed derivative polynomials over all points, and passing the
+// Hessians through memory, took 0.42 of 1.48 ms at n = 64, 4,096 points, most of
+// it in 29 small launches.)  A is inverted in place by a blocked Gauss-Jordan
+// elimination with partial pivoting:
 //   * a panel of NB columns is eliminated with one row per lane in registers,
 //     the pivot row broadcast by readlane (one panel wave) or through LDS (several);
 //     rows are not swapped, the pivots' permutation is applied when the
