@@ -18,8 +18,8 @@
 // that short ones share a CU.  The largest size, one workgroup to a CU, is bound
 // by its end: CUs are busy for 52% of its time, and then vector instructions
 // take 52% of the cycles and LDS 20%.  10.6 million terms in 4,096 polynomials of 10 to
-// 20,000, 20 variables, degree 6: k_sr_merge 172 + 88 + 18 + 18 us, k_sr_unpack
-// 146, k_max_degree 62, the call 610 us; 1,810 with a device-wide radix sort of
+// 20,000, 20 variables, degree 6: k_sr_merge 166 + 85 + 18 + 18 us, k_sr_unpack
+// 146, k_max_degree 76, the call 614 us; 1,810 with a device-wide radix sort of
 // two key words.  1,024 polynomials of 64 terms: 104 against 264 us.
 #include "kernels.h"
 #include "ranks.h"
