@@ -1537,7 +1537,7 @@ static bool dense_product_possible(MulDensePlan &m, const poly_csr *a, const pol
     }
     m.max_partners = max_segment(b->row_ptr_host, b->npolys);
     if (m.max_partners > MD_MAX_PARTNERS) return false;
-    int64_t pairs = 0;   // at most 2^32 * 2^14
+    int64_t pairs = 0;   // at most 2^14 times the terms in memory
     for (int64_t p = 0; p < b->npolys; ++p) {
         const int64_t t = b->row_ptr_host[p + 1] - b->row_ptr_host[p];
         pairs += t * t;
